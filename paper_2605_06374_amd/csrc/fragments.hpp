@@ -28,7 +28,7 @@ __device__ __forceinline__ f32x4 load_frag4(const float* base, int wave, int lan
   return *reinterpret_cast<const f32x4*>(base + ((((size_t)wave * (D / 32) + db) * 4 + rq) * 64 + lane) * 4);
 }
 template <int D> constexpr size_t frag_floats() { return (size_t)kTile * D; }
-// forward partial: O fragment, then running max m[4][64] and row sum l[4][64]
+// forward partial: O fragment, then the reference m[4][64] and row sum l[4][64]
 template <int D> constexpr size_t fwd_partial_floats() { return frag_floats<D>() + 2 * kThreads; }
 
 // bf16 store of one accumulator row set: lane owns row `row`, columns 32 db + 8 rq + 4h + e

@@ -35,7 +35,7 @@ constexpr int kStep = VARLEN_ATTN_STEP_ROWS;  // rows staged per iteration of a 
 constexpr int kThreads = 256;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr float kRescaleTau = 8.0f;  // running max may lag by up to 2^8 before O is rescaled
+constexpr float kRefSumMax = 16777216.f;  // 2^24: row sum of a sub-step above which the forward renews its reference
 
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>): a loop whose body may hold
 // scheduling fences (an ordinary loop that holds one is not unrolled).

@@ -90,6 +90,30 @@ def test_extreme_logit_ranges(gpu, std, d):
     assert_close_full(got, oracle_full(w), f"std {std}", row_tol_scale=4.0)
 
 
+@pytest.mark.parametrize("d,hq,hkv", [(128, 2, 1), (64, 4, 4)])
+@pytest.mark.parametrize("first,then", [(0.02, 12.0), (12.0, 0.02), (1.0, 40.0)])
+def test_forward_renews_its_reference(gpu, first, then, d, hq, hkv):
+    """The forward keeps the maximum of a chunk's first 32 keys as the reference of its exponentials
+    until a row sum exceeds 2^24.  Keys that grow by up to 600 times behind token 96 of each document
+    (logits of a few hundred: renewed in some rows, in later sub-steps, in later chunks) and keys
+    that shrink (the reference stays far above the scores of a whole chunk): O and LSE within the
+    usual bounds (bf16 rounding of P and O relative to the largest |V|, fp32 otherwise)."""
+    w = W.custom("renew", [900, 130, 64, 97, 1], hq, hkv, d, seed=d + hq)
+    vals = w.values()
+    k = W.bf16_bits_to_f32(vals["k"])
+    for s, e in zip(w.cu_seqlens[:-1], w.cu_seqlens[1:]):
+        k[s:min(e, s + 96)] *= np.float32(first)
+        k[min(e, s + 96):e] *= np.float32(then)
+    vals["k"] = W.f32_to_bf16_bits(k)
+    prob = gpu.DeviceProblem(w, values=vals)
+    prob.poison_outputs()
+    prob.forward()
+    got, ref = prob.results(), oracle_full(w, vals)
+    assert np.isfinite(got["o"]).all()
+    assert e1(got["o"], ref["o"]) <= TOL_O
+    assert (np.abs(got["lse"] - ref["lse"]) <= TOL_LSE * np.maximum(1.0, np.abs(ref["lse"]))).all()
+
+
 def test_config1_tiny_full(gpu):
     w = W.config(1)
     prob = run_all(gpu, w)
