@@ -18,7 +18,7 @@ __global__ void __launch_bounds__(kThreads, 2)
 bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
               const __bf16* __restrict__ v, const __bf16* __restrict__ o,
               const __bf16* __restrict__ d_o, const float* __restrict__ lse,
-              float* __restrict__ dsum, float* __restrict__ lse2_out,
+              float* __restrict__ neg_dsum, float* __restrict__ neg_lse,
               const varlen_attn_plan_header* __restrict__ hdr,
               const varlen_attn_unit* __restrict__ units, __bf16* __restrict__ dq,
               float* __restrict__ partials, int N, int Hq, int Hkv, float scale,
@@ -90,11 +90,11 @@ bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   }
   const float dsum_row = half_sum(d_part);
   // rows past the document end get LSE = +huge so that their P is exactly 0
-  const float lse2 = row_valid ? lse[(size_t)head * N + my_row] * kLog2e : 1e30f;
-  // the unit that starts the chain publishes D and LSE * log2(e) for the dK/dV kernel
+  const float lse_row = row_valid ? lse[(size_t)head * N + my_row] : 1e30f, lse2 = lse_row * kLog2e;
+  // the unit that starts the chain publishes -D and -LSE / scale for the dK/dV kernel
   if (it.step_begin == 0 && row_valid && h == 0) {
-    dsum[(size_t)head * N + my_row] = dsum_row;
-    lse2_out[(size_t)head * N + my_row] = lse2;
+    neg_dsum[(size_t)head * N + my_row] = -dsum_row;
+    neg_lse[(size_t)head * N + my_row] = -lse_row / scale;
   }
   FragOffsets<D> fo;
   fo.init(lane);
@@ -177,15 +177,14 @@ bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
 }
 
 // ----------------------------------------------------------------------------------------
-// Fused backward (VARLEN_ATTN_FLAG_FUSED_BWD), first kernel: D = rowsum(dO * O) and
-// LSE * log2(e) for every (token, q head) into the workspace, and the fp32 dQ accumulator
-// cleared.  One group of D / 8 lanes per row (16 bytes per lane); HBM-bound.
+// Fused backward (VARLEN_ATTN_FLAG_FUSED_BWD), first kernel: -D = -rowsum(dO * O) and -LSE / scale
+// for every (token, q head) into the workspace, and the fp32 dQ accumulator cleared.  One group of D / 8 lanes per row (16 bytes per lane); HBM-bound.
 // ----------------------------------------------------------------------------------------
 template <int D>
 __global__ void __launch_bounds__(kThreads)
 bwd_prep_kernel(const __bf16* __restrict__ o, const __bf16* __restrict__ d_o,
-                const float* __restrict__ lse, float* __restrict__ dsum,
-                float* __restrict__ lse2_out, float* __restrict__ dq_acc, int N, int Hq) {
+                const float* __restrict__ lse, float* __restrict__ neg_dsum,
+                float* __restrict__ neg_lse, float* __restrict__ dq_acc, int N, int Hq, float scale) {
   constexpr int kLanesPerRow = D / 8;
   constexpr int kRowsPerBlock = kThreads / kLanesPerRow;
   const long long row = (long long)blockIdx.x * kRowsPerBlock + threadIdx.x / kLanesPerRow;  // t * Hq + h
@@ -206,8 +205,8 @@ bwd_prep_kernel(const __bf16* __restrict__ o, const __bf16* __restrict__ d_o,
   for (int off = kLanesPerRow / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
   if (part == 0 && valid) {
     const int t = (int)(row / Hq), h = (int)(row % Hq);
-    dsum[(size_t)h * N + t] = acc;
-    lse2_out[(size_t)h * N + t] = lse[(size_t)h * N + t] * kLog2e;
+    neg_dsum[(size_t)h * N + t] = -acc;
+    neg_lse[(size_t)h * N + t] = -lse[(size_t)h * N + t] / scale;
   }
 }
 
@@ -286,6 +285,13 @@ __device__ __forceinline__ void dq_tile_combine(int block, const varlen_attn_pla
 // query steps (from the diagonal towards the document end).
 //   S = Q K^T, dP = dO V^T (query rows in registers r, key on the lane),
 //   dV^T += dO^T P,  dK^T += Q^T dS.
+// What bounds it: at d = 128 one wave per SIMD issues everything, so that every instruction beside the
+// matrix instructions costs; hence the direct-to-LDS loads of the next stage between the matrix
+// instructions of M1(0) (a clump of 10 of them behind the barrier left the matrix pipe idle for some
+// 250 clocks of a stage) and accumulators that start from -LSE / scale and -D (no subtractions):
+// 824 -> 769 us at 32768 tokens in 11 documents (205e6 pairs, 4 heads of 128), 305 -> 283 us at 16384
+// tokens with 8 q heads on one kv head.  The registers that the statistics no longer need let the
+// d = 64 form run two workgroups per CU: 58.4 -> 40.6 us at 6144 tokens, 16 q and 4 kv heads.
 // With grouped-query attention, or when the chain is cut, the unit stores fp32 partials
 // [dK | dV] that bwd_combine_kernel adds up over the chunks and the q heads of the group.
 //
@@ -297,10 +303,10 @@ __device__ __forceinline__ void dq_tile_combine(int block, const varlen_attn_pla
 // those additions is not fixed, so dQ is not bit-reproducible in this mode.
 // ----------------------------------------------------------------------------------------
 template <int D, bool FUSED>
-__global__ void __launch_bounds__(kThreads, 1)
+__global__ void __launch_bounds__(kThreads, D == 64 && !FUSED ? 2 : 1)
 bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                const __bf16* __restrict__ v, const __bf16* __restrict__ d_o,
-               const float* __restrict__ lse2, const float* __restrict__ dsum,
+               const float* __restrict__ neg_lse, const float* __restrict__ neg_dsum,
                const varlen_attn_plan_header* __restrict__ hdr,
                const varlen_attn_unit* __restrict__ units, __bf16* __restrict__ dk,
                __bf16* __restrict__ dv, float* __restrict__ partials, int N, int Hq, int Hkv,
@@ -314,13 +320,13 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   // the 16-bit immediate of the read instructions.
   constexpr int NS = 2;
   constexpr int kStageBytes = kStep * D * 2;
-  constexpr int kStatBytes = 512;             // lse2[64] then dsum[64], one copy per wave
-  using Loader = StageLoader<D, kStep>;
-  constexpr int LPS = 2 * Loader::kPerWave + 2;
-  constexpr int kPlainBytes = 2 * NS * kStageBytes + NS * 4 * kStatBytes;
+  constexpr int kStatBytes = 512;             // -LSE / scale [64] then -D [64]; two copies, one per pair of waves
+  using Stream = PairStream<D, kStep>;
+  static_assert(Stream::kPieces == KK, "one piece of the next stage beside each pair of matrix instructions");
+  constexpr int kPlainBytes = 2 * NS * kStageBytes + NS * 2 * kStatBytes;
   constexpr int kKeyTileBytes = FUSED ? kTile * D * 2 : 0;      // the unit's K rows [128][D]
   constexpr int kDsBytes = FUSED ? kTile * kStep * 2 : 0;       // dS of a stage [128 keys][64 queries]
-  // Q stages | dO stages | per-wave stat copies | (fused: K tile | two dS tiles)
+  // Q stages | dO stages | statistics | (fused: K tile | two dS tiles)
   __shared__ __attribute__((aligned(1024))) char smem[kPlainBytes + kKeyTileBytes + 2 * kDsBytes];
   char* const key_tile = smem + kPlainBytes;
   char* const ds_tiles = key_tile + kKeyTileBytes;
@@ -347,10 +353,13 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   }
   if (unit_idx >= n_units) return;
   const int kvh = head / (Hq / Hkv);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, c = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, c = lane & 31;
   const float cs = scale * kLog2e;
 
-  const int wave_kv0 = it.row0 + 32 * wave;
+  // from the thread index, not from the scalar `wave`: the branches between the two forms of a stage
+  // then stay exec-masked, one behind the other, and the accumulators keep their registers; as scalar
+  // branches the register allocator copies up to 270 of them per stage and spills
+  const int wave_kv0 = it.row0 + 32 * (tid >> 6);
   const int my_kv = wave_kv0 + c;
   const bool kv_valid = my_kv < it.doc_end;
   const bool wave_active = wave_kv0 < it.doc_end;
@@ -358,32 +367,43 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
 
   const __bf16* qbase = q + (size_t)head * D;
   const __bf16* dobase = d_o + (size_t)head * D;
-  const float* lse_h = lse2 + (size_t)head * N;
-  const float* dsum_h = dsum + (size_t)head * N;
+  const float* lse_h = neg_lse + (size_t)head * N;
+  const float* dsum_h = neg_dsum + (size_t)head * N;
   float* dq_acc_h = FUSED ? dq_acc + (size_t)head * D : nullptr;
   int heads_left = hpu;
-  const unsigned lds_q = lds_addr_of(smem), lds_do = lds_q + NS * kStageBytes;
-  const unsigned lds_stat = lds_do + NS * kStageBytes + wave * kStatBytes;
-  const char* stat_base = smem + 2 * NS * kStageBytes + wave * kStatBytes;
+  // this wave's share of the stages, and its statistics: wave w loads -LSE / scale (w even) or -D (w odd)
+  // into the copy of its pair and reads both from that copy
+  const unsigned lds_q = lds_addr_of(smem) + wave * 1024, lds_do = lds_q + NS * kStageBytes;
+  const unsigned lds_stat = lds_addr_of(smem) + 2 * NS * kStageBytes + (wave >> 1) * kStatBytes + (wave & 1) * 256;
+  const char* stat_base = smem + 2 * NS * kStageBytes + (wave >> 1) * kStatBytes;
 
-  Loader loader;
-  loader.init(wave, lane, (unsigned)((size_t)Hq * D * 2));
-  // stages are issued in order, one call per step: the wave-uniform addresses of the next
-  // stage's first Q and dO rows live in scalar registers and move on by one stage per call
-  const unsigned long long kStageStride = (unsigned long long)kStep * ((size_t)Hq * D * 2);
-  unsigned long long q_next = 0, do_next = 0;
-  auto restart = [&]() {   // at the first step of a chain (of every head the unit sweeps)
-    const size_t first = (size_t)(it.row0 + kStep * it.step_begin) * ((size_t)Hq * D * 2);
-    q_next = uniform64(reinterpret_cast<const char*>(qbase) + first);
-    do_next = uniform64(reinterpret_cast<const char*>(dobase) + first);
+  // stages are requested in order, one per step, while the stage before them is computed: the
+  // wave-uniform addresses of the next stage's first rows live in scalar registers
+  Stream stream;
+  stream.init(wave, lane, (unsigned)((size_t)Hq * D * 2));
+  unsigned long long stat_next = 0;
+  unsigned stat_voff = 0;
+  auto aim = [&](int st) __attribute__((always_inline)) {   // at step st of the chain
+    const int q0 = it.row0 + kStep * (it.step_begin + st);
+    stream.aim(q0, it.doc_end - 1);
+    if (q0 + kStep > it.doc_end) stat_voff = (unsigned)min(lane, it.doc_end - 1 - q0) * 4;
   };
-  auto issue = [&](int st, int stage) {
-    const int q0 = it.row0 + kStep * (it.step_begin + min(st, n_steps - 1));
-    loader.issue_at(q_next, q0, it.doc_end - 1, lds_q + stage * kStageBytes, wave);
-    loader.issue_at(do_next, q0, it.doc_end - 1, lds_do + stage * kStageBytes, wave);
-    dma_floats64(lse_h, q0, it.doc_end - 1, lds_stat + stage * 4 * kStatBytes, lane);
-    dma_floats64(dsum_h, q0, it.doc_end - 1, lds_stat + stage * 4 * kStatBytes + 256, lane);
-    if (st < n_steps - 1) { q_next += kStageStride; do_next += kStageStride; }
+  auto restart = [&]() __attribute__((always_inline)) {   // at the first step of a chain (of every head the unit sweeps)
+    const int q0 = it.row0 + kStep * it.step_begin;
+    const size_t first = (size_t)q0 * ((size_t)Hq * D * 2);
+    stream.start(reinterpret_cast<const char*>(qbase) + first, reinterpret_cast<const char*>(dobase) + first);
+    stat_next = uniform64((wave & 1 ? dsum_h : lse_h) + q0);
+    stat_voff = lane * 4;
+    aim(0);
+  };
+  // piece P of the next stage into LDS stage ST; the first piece brings the statistics along
+  auto piece = [&](auto piece_c, auto stage_c) __attribute__((always_inline)) {
+    constexpr int P = decltype(piece_c)::value, ST = decltype(stage_c)::value;
+    stream.template piece<P>(lds_q + ST * kStageBytes, lds_do + ST * kStageBytes);
+    if (P == 0) dma4(stat_next, stat_voff, lds_stat + ST * 2 * kStatBytes);
+  };
+  auto all_pieces = [&](auto stage_c) __attribute__((always_inline)) {
+    static_for<KK>([&](auto p) __attribute__((always_inline)) { piece(p, stage_c); });
   };
   bf16x8 kf[KK], vf[KK];
 #pragma unroll
@@ -464,25 +484,29 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   // the vector and LDS work that should ride on it, and the fences keep that order.
   // MASKED: the stage touches the diagonal or runs past the document end (queries there are
   // clamped duplicates): P of a (query, key) pair outside the mask is set to exactly 0.
-  auto stage = [&](const char* qt, const char* dot, const char* st, int q0, char* ds_tile, auto masked_c)
+  // The direct-to-LDS loads of the next stage are issued one by one in M1(0), the phase with the
+  // fewest other instructions per matrix instruction.
+  auto stage = [&](const char* qt, const char* dot, const char* st, int q0, char* ds_tile, auto next_c, auto masked_c)
       __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
     constexpr int EPM = 16 / (2 * KK);  // score elements handled beside each matrix instruction
     bf16x8 qa[KK], da[KK], qb[KK], db_[KK];
     bf16x8 tq0[2][DB], td0[2][DB], tq1[2][DB], td1[2][DB];
-    f32x4 l0[4], d0[4], l1[4], d1[4];
-    // softmax of element r of one block: p = 2^(s cs - lse2), ds = p (dp - D)
+    f32x16 s0, s1, dp0, dp1;
+    // softmax of element r of one block: p = exp(scale s - lse), ds = p (dp - D).  The matrix
+    // instructions of S start from -lse / scale and those of dP from -D (both read from LDS straight
+    // into the accumulators), so that no subtraction is left and no register holds the statistics
     // (r stands for query q0 + 32 qb + 8 (r / 4) + 4 h + r % 4)
     const int t_lo = my_kv - q0 - 4 * h, t_hi = it.doc_end - q0 - 4 * h;   // allowed: t_lo <= 32 qb + 8 (r / 4) + r % 4 < t_hi
-    auto soft = [&](f32x16& sv, const f32x16& dpv, f32x16& pv, const f32x4* l, const f32x4* dd, int r, int qb)
+    auto soft = [&](f32x16& sv, const f32x16& dpv, f32x16& pv, int r, int qb)
         __attribute__((always_inline)) {
-      float e = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[r], cs, -l[r >> 2][r & 3]));
+      float e = __builtin_amdgcn_exp2f(sv[r] * cs);
       if (MASKED) {
         const int t = 32 * qb + 8 * (r >> 2) + (r & 3);
         if (t < t_lo || t >= t_hi) e = 0.f;
       }
       pv[r] = e;
-      sv[r] = e * (dpv[r] - dd[r >> 2][r & 3]);
+      sv[r] = e * dpv[r];
     };
     // ---- R0
 #pragma unroll
@@ -492,36 +516,37 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
     }
 #pragma unroll
     for (int rq = 0; rq < 4; ++rq) {
-      l0[rq] = *reinterpret_cast<const f32x4*>(st + (8 * rq + 4 * h) * 4);
-      d0[rq] = *reinterpret_cast<const f32x4*>(st + 256 + (8 * rq + 4 * h) * 4);
+      set4(s0, rq, *reinterpret_cast<const f32x4*>(st + (8 * rq + 4 * h) * 4));
+      set4(dp0, rq, *reinterpret_cast<const f32x4*>(st + 256 + (8 * rq + 4 * h) * 4));
     }
     __builtin_amdgcn_sched_barrier(0);
     // ---- M1(0) + R1
-    f32x16 s0 = f32x16(0.f), dp0 = f32x16(0.f);
     static_for<KK>([&](auto kk_c) {
       constexpr int kk = decltype(kk_c)::value;
       s0 = mfma(qa[kk], kf[kk], s0);
       qb[kk] = lds_read_frag(qt, fo.row_frag[kk] + 32 * D * 2);
-      if (kk < 4) l1[kk] = *reinterpret_cast<const f32x4*>(st + (32 + 8 * kk + 4 * h) * 4);
+      if (kk < 4) set4(s1, kk, *reinterpret_cast<const f32x4*>(st + (32 + 8 * kk + 4 * h) * 4));
+      __builtin_amdgcn_sched_barrier(0);
+      piece(kk_c, next_c);
       __builtin_amdgcn_sched_barrier(0);
       dp0 = mfma(da[kk], vf[kk], dp0);
       db_[kk] = lds_read_frag(dot, fo.row_frag[kk] + 32 * D * 2);
-      if (kk < 4) d1[kk] = *reinterpret_cast<const f32x4*>(st + 256 + (32 + 8 * kk + 4 * h) * 4);
+      if (kk < 4) set4(dp1, kk, *reinterpret_cast<const f32x4*>(st + 256 + (32 + 8 * kk + 4 * h) * 4));
       __builtin_amdgcn_sched_barrier(0);
     });
     // ---- V(0) with M1(1) + T0
-    f32x16 p0, s1 = f32x16(0.f), dp1 = f32x16(0.f);
+    f32x16 p0;
     bf16x8 pb0[2], dsb0[2];
     static_for<KK>([&](auto kk_c) {
       constexpr int kk = decltype(kk_c)::value;
       s1 = mfma(qb[kk], kf[kk], s1);
 #pragma unroll
-      for (int e = 0; e < EPM; ++e) soft(s0, dp0, p0, l0, d0, EPM * 2 * kk + e, 0);
+      for (int e = 0; e < EPM; ++e) soft(s0, dp0, p0, EPM * 2 * kk + e, 0);
       td0[kk / DB][kk % DB] = read_trans<D>(dot, fo, kk / DB, kk % DB);
       __builtin_amdgcn_sched_barrier(0);
       dp1 = mfma(db_[kk], vf[kk], dp1);
 #pragma unroll
-      for (int e = 0; e < EPM; ++e) soft(s0, dp0, p0, l0, d0, EPM * (2 * kk + 1) + e, 0);
+      for (int e = 0; e < EPM; ++e) soft(s0, dp0, p0, EPM * (2 * kk + 1) + e, 0);
       tq0[kk / DB][kk % DB] = read_trans<D>(qt, fo, kk / DB, kk % DB);
       if ((kk + 1) * 2 * EPM % 8 == 0) {
         constexpr int i = (kk + 1) * 2 * EPM / 8 - 1;
@@ -538,12 +563,12 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
       constexpr int j = decltype(j_c)::value;
       dvacc[j % DB] = mfma(td0[j / DB][j % DB], pb0[j / DB], dvacc[j % DB]);
 #pragma unroll
-      for (int e = 0; e < EPM; ++e) soft(s1, dp1, p1, l1, d1, EPM * 2 * j + e, 1);
+      for (int e = 0; e < EPM; ++e) soft(s1, dp1, p1, EPM * 2 * j + e, 1);
       td1[j / DB][j % DB] = read_trans<D>(dot + 32 * D * 2, fo, j / DB, j % DB);
       __builtin_amdgcn_sched_barrier(0);
       dkacc[j % DB] = mfma(tq0[j / DB][j % DB], dsb0[j / DB], dkacc[j % DB]);
 #pragma unroll
-      for (int e = 0; e < EPM; ++e) soft(s1, dp1, p1, l1, d1, EPM * (2 * j + 1) + e, 1);
+      for (int e = 0; e < EPM; ++e) soft(s1, dp1, p1, EPM * (2 * j + 1) + e, 1);
       tq1[j / DB][j % DB] = read_trans<D>(qt + 32 * D * 2, fo, j / DB, j % DB);
       if ((j + 1) * 2 * EPM % 8 == 0) {
         constexpr int i = (j + 1) * 2 * EPM / 8 - 1;
@@ -564,26 +589,32 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   };
   auto body = [&](int st, auto stage_c) {
     constexpr int ST = decltype(stage_c)::value;
-    wait_vm<(NS - 2) * LPS>();
+    const std::integral_constant<int, 1 - ST> next_c{};
+    wait_vm<0>();
     __syncthreads();
-    issue(st + NS - 1, (ST + NS - 1) % NS);
+    // the last step requests its own stage again (into the other buffer; nobody reads it), so that
+    // every step is the same
+    if (st < n_steps - 1) {
+      stream.advance();
+      stat_next += kStep * 4;
+      aim(st + 1);
+    }
     const int step = it.step_begin + st;
     const int q0 = it.row0 + kStep * step;
     // fused: dQ of the previous stage, whose dS every wave has written before the barrier above
     if (FUSED && st > 0) dq_flush(ds_tiles + (1 - ST) * kDsBytes, q0 - kStep);
-    if (!wave_active) return;
+    // no keys, or every query of the stage lies before this wave's keys
+    if (!wave_active || q0 + kStep - 1 < wave_kv0) { all_pieces(next_c); return; }
     const char* qt = smem + ST * kStageBytes;
     const char* dot = smem + (NS + ST) * kStageBytes;
-    const char* stt = stat_base + ST * 4 * kStatBytes;
-    if (q0 + kStep - 1 < wave_kv0) return;   // every query of the stage lies before this wave's keys
+    const char* stt = stat_base + ST * 2 * kStatBytes;
     char* ds_tile = ds_tiles + ST * kDsBytes;
-    if (q0 < wave_kv0 + 32 || q0 + kStep > it.doc_end) stage(qt, dot, stt, q0, ds_tile, std::true_type{});
-    else stage(qt, dot, stt, q0, ds_tile, std::false_type{});
+    if (q0 < wave_kv0 + 32 || q0 + kStep > it.doc_end) stage(qt, dot, stt, q0, ds_tile, next_c, std::true_type{});
+    else stage(qt, dot, stt, q0, ds_tile, next_c, std::false_type{});
   };
   for (;;) {
     restart();
-#pragma unroll
-    for (int st = 0; st < NS - 1; ++st) issue(st, st);
+    all_pieces(std::integral_constant<int, 0>{});
     for (int st = 0; st < n_steps; st += NS) {
       body(st, std::integral_constant<int, 0>{});
       if (st + 1 >= n_steps) break;

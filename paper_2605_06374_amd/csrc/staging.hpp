@@ -94,18 +94,55 @@ struct StageLoader {
   }
 };
 
-// 64 consecutive floats (clamped at index `last`) -> 256 bytes of LDS, one wave-level load
-__device__ __forceinline__ void dma_floats64(const float* base, int first, int last, unsigned lds,
-                                             int lane) {
-  const unsigned long long b = uniform64(base + first);
-  unsigned voff = (unsigned)lane * 4;
-  if (first + 63 > last) voff = (unsigned)min(lane, last - first) * 4;
+// A wave's direct-to-LDS loads of one stage of two tiles with a common row stride (Q and dO; K and
+// V) as separate pieces, so that a kernel can write each load between matrix instructions: 64
+// addresses keep the vector memory path busy for some 20 clocks, which a clump of them at the top
+// of a stage leaves exposed and which a matrix instruction hides.  The row offsets of the next
+// stage stand ready in `voff`; only a stage that runs past `row_last` changes them (clamped).
+template <int D, int ROWS>
+struct PairStream {
+  using L = StageLoader<D, ROWS>;
+  static constexpr int kPieces = 2 * L::kPerWave;
+  L loader;
+  unsigned voff[L::kPerWave];
+  unsigned long long a_next, b_next;     // first rows of the next stage (wave-uniform)
+  unsigned long long stage_stride;
+  __device__ __forceinline__ void init(int wave, int lane, unsigned stride_bytes) {
+    loader.init(wave, lane, stride_bytes);
+    stage_stride = (unsigned long long)ROWS * stride_bytes;
+  }
+  __device__ __forceinline__ void start(const void* a, const void* b) {
+    a_next = uniform64(a);
+    b_next = uniform64(b);
+#pragma unroll
+    for (int i = 0; i < L::kPerWave; ++i) voff[i] = loader.voff[i];
+  }
+  // the next stage starts at row `row0`
+  __device__ __forceinline__ void aim(int row0, int row_last) {
+    if (row0 + ROWS - 1 > row_last) {
+#pragma unroll
+      for (int i = 0; i < L::kPerWave; ++i)
+        voff[i] = (unsigned)min(loader.row_in_stage[i], row_last - row0) * loader.stride_bytes + loader.col_bytes[i];
+    }
+  }
+  // piece P of the stage: the first tile's loads, then the second's; lds_a, lds_b: this wave's
+  // first kilobyte of the two tiles (wave-uniform)
+  template <int P>
+  __device__ __forceinline__ void piece(unsigned lds_a, unsigned lds_b) const {
+    constexpr int i = P % L::kPerWave;
+    if (P < L::kPerWave) dma16(a_next, voff[i], lds_a + i * 4096);
+    else dma16(b_next, voff[i], lds_b + i * 4096);
+  }
+  __device__ __forceinline__ void advance() { a_next += stage_stride; b_next += stage_stride; }
+};
+
+// 64 consecutive floats at the wave-uniform address -> 256 bytes of LDS, one wave-level load
+__device__ __forceinline__ void dma4(unsigned long long base, unsigned voff, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
                :
-               : "v"(voff), "s"(b), "s"(__builtin_amdgcn_readfirstlane(lds))
+               : "v"(voff), "s"(base), "s"(lds_addr)
                : "memory");
 }
-
 // per-lane byte offsets (inside a stage) of the two kinds of fragment reads
 template <int D>
 struct FragOffsets {

@@ -104,6 +104,12 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int first) {
   return out;
 }
 
+// registers 4 rq .. 4 rq + 3 of an accumulator
+__device__ __forceinline__ void set4(f32x16& v, int rq, f32x4 x) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[4 * rq + e] = x[e];
+}
+
 __device__ __forceinline__ uint2 pack4(float a, float b, float c, float d) {
   f32x2 t0 = {a, b}, t1 = {c, d};
   bf16x2 b0 = __builtin_convertvector(t0, bf16x2), b1 = __builtin_convertvector(t1, bf16x2);

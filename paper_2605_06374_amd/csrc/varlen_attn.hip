@@ -135,7 +135,7 @@ bool layout_of(const varlen_attn_params* p, varlen_attn_workspace_layout* L, int
   L->col_units_offset = off; off = align_up(off + sizeof(varlen_attn_unit) * L->max_units, 256);
   L->row_combine_offset = off; off = align_up(off + sizeof(varlen_attn_combine_item) * L->max_combine, 256);
   L->col_combine_offset = off; off = align_up(off + sizeof(varlen_attn_combine_item) * L->max_combine, 256);
-  // D = rowsum(dO * O) [Hq, N], then LSE * log2(e) [Hq, N]
+  // -D = -rowsum(dO * O) [Hq, N], then -LSE / scale [Hq, N]
   L->dsum_offset = off; off = align_up(off + 2 * sizeof(float) * (size_t)Hq * p->total_tokens, 256);
   L->row_partials_offset = off; off = align_up(off + fwd_part * Hq * L->max_row_slots, 256);
   L->col_partials_offset = off; off = align_up(off + 2 * frag * Hq * L->max_col_slots, 256);
@@ -258,21 +258,21 @@ void launch_bwd(const varlen_attn_params* p, const void* q, const void* k, const
                 const Regions& R, const varlen_attn_workspace_layout& L, hipStream_t stream) {
   const int N = p->total_tokens, Hq = p->num_q_heads, Hkv = p->num_kv_heads;
   const float scale = p->softmax_scale;
-  float* lse2 = R.dsum + (size_t)Hq * N;
+  float* neg_lse = R.dsum + (size_t)Hq * N;
   const bool fused = (p->flags & VARLEN_ATTN_FLAG_FUSED_BWD) != 0;
   if (fused) {
-    // D = rowsum(dO * O), LSE * log2(e), and the dQ accumulator cleared
+    // -D = -rowsum(dO * O), -LSE / scale, and the dQ accumulator cleared
     ScopedKernelTimer timer(kPrep, stream);
     constexpr int kRowsPerBlock = kThreads / (D / 8);
     const long long rows = (long long)N * Hq;
     bwd_prep_kernel<D><<<dim3((unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock)), kThreads, 0, stream>>>(
-        (const __bf16*)o, (const __bf16*)d_o, lse, R.dsum, lse2, R.dq_acc, N, Hq);
+        (const __bf16*)o, (const __bf16*)d_o, lse, R.dsum, neg_lse, R.dq_acc, N, Hq, scale);
   } else {
-    // also writes D = rowsum(dO * O) and LSE * log2(e), which the dK/dV kernel reads
+    // also writes -D = -rowsum(dO * O) and -LSE / scale, which the dK/dV kernel reads
     ScopedKernelTimer timer(kDq, stream);
     bwd_dq_kernel<D><<<dim3(grid_for(L.max_units, Hq)), kThreads, 0, stream>>>(
         (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)o, (const __bf16*)d_o,
-        lse, R.dsum, lse2, R.hdr, R.row_units, (__bf16*)dq, R.row_part, N, Hq, Hkv, scale,
+        lse, R.dsum, neg_lse, R.hdr, R.row_units, (__bf16*)dq, R.row_part, N, Hq, Hkv, scale,
         L.max_units);
   }
   const bool split = !(p->flags & VARLEN_ATTN_FLAG_NO_SPLIT);
@@ -284,7 +284,7 @@ void launch_bwd(const varlen_attn_params* p, const void* q, const void* k, const
     // one kernel for dQ, dK and dV; dQ is summed in fp32 in the workspace and rounded afterwards
     ScopedKernelTimer timer(kFusedBwd, stream);
     bwd_dkv_kernel<D, true><<<dim3(unit_blocks), kThreads, 0, stream>>>(
-        (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)d_o, lse2, R.dsum, R.hdr,
+        (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)d_o, neg_lse, R.dsum, R.hdr,
         R.col_units, (__bf16*)dk, (__bf16*)dv, R.col_part, N, Hq, Hkv, scale, L.max_units,
         (int)unit_blocks, R.row_comb, L.max_combine, R.row_part, (__bf16*)dq, R.dq_acc);
   } else {
@@ -292,7 +292,7 @@ void launch_bwd(const varlen_attn_params* p, const void* q, const void* k, const
     const unsigned dq_blocks = split ? (unsigned)cut_tiles * Hq : 0u;
     ScopedKernelTimer timer(kDkv, stream);
     bwd_dkv_kernel<D, false><<<dim3(unit_blocks + dq_blocks), kThreads, 0, stream>>>(
-        (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)d_o, lse2, R.dsum, R.hdr,
+        (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)d_o, neg_lse, R.dsum, R.hdr,
         R.col_units, (__bf16*)dk, (__bf16*)dv, R.col_part, N, Hq, Hkv, scale, L.max_units,
         (int)unit_blocks, R.row_comb, L.max_combine, R.row_part, (__bf16*)dq, nullptr);
   }
