@@ -342,6 +342,20 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
                const float* __restrict__ row_partials, __bf16* __restrict__ dq,
                float* __restrict__ dq_acc) {
   constexpr int KK = D / 16, DB = D / 32;
+  static_assert(KK == 2 * DB, "the phases of a stage have the same number of matrix instructions");
+  // S and dP of the d = 128 form in vector registers: with more than 256 registers in use the
+  // compiler puts every matrix result into accumulation registers, which the vector ALU cannot
+  // read, and copies each score (64 of 426 instructions of a stage; 767 -> 733 us at 32768 tokens in
+  // 11 documents, 285 -> 272 us at 16384 tokens, 8 q heads).
+  constexpr bool kVgprScores = D == 128 && !FUSED;
+  // The compiler does not see that these results take time: nothing may read them until two further
+  // matrix instructions have been issued.  The softmax of a block therefore starts beside the third
+  // matrix instruction of the phase behind it (SKEW), fences before and after.
+  constexpr int SKEW = kVgprScores ? 2 : 0;
+  auto mfma_s = [&](f32x16& c, const bf16x8& a, const bf16x8& b) __attribute__((always_inline)) {
+    if constexpr (kVgprScores) mfma_vgpr(c, a, b);
+    else c = mfma(a, b, c);
+  };
   // Two stages of kStep = 64 query rows: one stage of lookahead is a whole stage of compute
   // (this kernel runs one workgroup per CU), and 64 KB of tiles keeps every LDS offset inside
   // the 16-bit immediate of the read instructions.
@@ -516,93 +530,90 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   auto stage = [&](const char* qt, const char* dot, const char* st, int q0, char* ds_tile, auto next_c, auto masked_c)
       __attribute__((always_inline)) {
     constexpr bool MASKED = decltype(masked_c)::value;
-    constexpr int EPM = 16 / (2 * KK);  // score elements handled beside each matrix instruction
     bf16x8 qa[KK], da[KK], qb[KK], db_[KK];
     bf16x8 tq0[2][DB], td0[2][DB], tq1[2][DB], td1[2][DB];
+    bf16x8 pb0[2], dsb0[2], pb1[2], dsb1[2];
     f32x16 s0, s1, dp0, dp1;
     // softmax of element r of one block: p = exp(scale s - lse), ds = p (dp - D).  The matrix
     // instructions of S start from -lse / scale and those of dP from -D (both read from LDS straight
     // into the accumulators), so that no subtraction is left and no register holds the statistics
     // (r stands for query q0 + 32 qb + 8 (r / 4) + 4 h + r % 4)
     const int t_lo = my_kv - q0 - 4 * h, t_hi = it.doc_end - q0 - 4 * h;   // allowed: t_lo <= 32 qb + 8 (r / 4) + r % 4 < t_hi
-    auto soft = [&](f32x16& sv, const f32x16& dpv, f32x16& pv, int r, int qb)
+    auto soft = [&](f32x16& sv, const f32x16& dpv, bf16x8 (&pb)[2], bf16x8 (&dsb)[2], int r, int qb)
         __attribute__((always_inline)) {
       float e = __builtin_amdgcn_exp2f(sv[r] * cs);
       if (MASKED) {
         const int t = 32 * qb + 8 * (r >> 2) + (r & 3);
         if (t < t_lo || t >= t_hi) e = 0.f;
       }
-      pv[r] = e;
-      sv[r] = e * dpv[r];
+      sv[r] = e;
+      if (r & 1) {   // the pair r - 1, r as bf16
+        const f32x2 p = {sv[r - 1], e}, ds = {sv[r - 1] * dpv[r - 1], e * dpv[r]};
+        const bf16x2 p2 = __builtin_convertvector(p, bf16x2), ds2 = __builtin_convertvector(ds, bf16x2);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) { pb[r >> 3][(r & 7) - 1 + i] = p2[i]; dsb[r >> 3][(r & 7) - 1 + i] = ds2[i]; }
+      }
+    };
+    // elements of the softmax beside matrix instruction i of 2 KK: none beside the first SKEW (their
+    // scores are still in the matrix pipe), the rest evenly
+    auto soft_slot = [&](f32x16& sv, const f32x16& dpv, bf16x8 (&pb)[2], bf16x8 (&dsb)[2], auto i_c, int qb)
+        __attribute__((always_inline)) {
+      constexpr int i = decltype(i_c)::value;
+      constexpr int slots = 2 * KK - SKEW;
+      constexpr int first = i < SKEW ? 0 : 16 * (i - SKEW) / slots, last = i < SKEW ? 0 : 16 * (i + 1 - SKEW) / slots;
+#pragma unroll
+      for (int e = first; e < last; ++e) soft(sv, dpv, pb, dsb, e, qb);
     };
     // ---- R0
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      qa[kk] = lds_read_frag(qt, fo.row_frag[kk]);
-      da[kk] = lds_read_frag(dot, fo.row_frag[kk]);
-    }
 #pragma unroll
     for (int rq = 0; rq < 4; ++rq) {
       set4(s0, rq, *reinterpret_cast<const f32x4*>(st + (8 * rq + 4 * h) * 4));
       set4(dp0, rq, *reinterpret_cast<const f32x4*>(st + 256 + (8 * rq + 4 * h) * 4));
     }
     __builtin_amdgcn_sched_barrier(0);
+    static_for<KK>([&](auto kk) __attribute__((always_inline)) {
+      qa[kk] = lds_read_frag(qt, fo.row_frag[kk]);
+      da[kk] = lds_read_frag(dot, fo.row_frag[kk]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
     // ---- M1(0) + R1
     static_for<KK>([&](auto kk_c) {
       constexpr int kk = decltype(kk_c)::value;
-      s0 = mfma(qa[kk], kf[kk], s0);
+      mfma_s(s0, qa[kk], kf[kk]);
       qb[kk] = lds_read_frag(qt, fo.row_frag[kk] + 32 * D * 2);
       if (kk < 4) set4(s1, kk, *reinterpret_cast<const f32x4*>(st + (32 + 8 * kk + 4 * h) * 4));
       __builtin_amdgcn_sched_barrier(0);
       piece(kk_c, next_c);
       __builtin_amdgcn_sched_barrier(0);
-      dp0 = mfma(da[kk], vf[kk], dp0);
+      mfma_s(dp0, da[kk], vf[kk]);
       db_[kk] = lds_read_frag(dot, fo.row_frag[kk] + 32 * D * 2);
       if (kk < 4) set4(dp1, kk, *reinterpret_cast<const f32x4*>(st + 256 + (32 + 8 * kk + 4 * h) * 4));
       __builtin_amdgcn_sched_barrier(0);
     });
     // ---- V(0) with M1(1) + T0
-    f32x16 p0;
-    bf16x8 pb0[2], dsb0[2];
     static_for<KK>([&](auto kk_c) {
       constexpr int kk = decltype(kk_c)::value;
-      s1 = mfma(qb[kk], kf[kk], s1);
-#pragma unroll
-      for (int e = 0; e < EPM; ++e) soft(s0, dp0, p0, EPM * 2 * kk + e, 0);
+      mfma_s(s1, qb[kk], kf[kk]);
+      soft_slot(s0, dp0, pb0, dsb0, std::integral_constant<int, 2 * kk>{}, 0);
       td0[kk / DB][kk % DB] = read_trans<D>(dot, fo, kk / DB, kk % DB);
       __builtin_amdgcn_sched_barrier(0);
-      dp1 = mfma(db_[kk], vf[kk], dp1);
-#pragma unroll
-      for (int e = 0; e < EPM; ++e) soft(s0, dp0, p0, EPM * (2 * kk + 1) + e, 0);
+      mfma_s(dp1, db_[kk], vf[kk]);
+      soft_slot(s0, dp0, pb0, dsb0, std::integral_constant<int, 2 * kk + 1>{}, 0);
       tq0[kk / DB][kk % DB] = read_trans<D>(qt, fo, kk / DB, kk % DB);
-      if ((kk + 1) * 2 * EPM % 8 == 0) {
-        constexpr int i = (kk + 1) * 2 * EPM / 8 - 1;
-        pb0[i] = pack8(p0, 8 * i);
-        dsb0[i] = pack8(s0, 8 * i);
-        if (FUSED) ds_store(ds_tile, dsb0[i], 0, i);
-      }
+      if (FUSED && (kk == KK / 2 - 1 || kk == KK - 1)) ds_store(ds_tile, dsb0[kk == KK - 1], 0, kk == KK - 1);
       __builtin_amdgcn_sched_barrier(0);
     });
     // ---- M2(0) with V(1) + T1
-    f32x16 p1;
-    bf16x8 pb1[2], dsb1[2];
     static_for<2 * DB>([&](auto j_c) {
       constexpr int j = decltype(j_c)::value;
       dvacc[j % DB] = mfma(td0[j / DB][j % DB], pb0[j / DB], dvacc[j % DB]);
-#pragma unroll
-      for (int e = 0; e < EPM; ++e) soft(s1, dp1, p1, EPM * 2 * j + e, 1);
+      soft_slot(s1, dp1, pb1, dsb1, std::integral_constant<int, 2 * j>{}, 1);
       td1[j / DB][j % DB] = read_trans<D>(dot + 32 * D * 2, fo, j / DB, j % DB);
       __builtin_amdgcn_sched_barrier(0);
       dkacc[j % DB] = mfma(tq0[j / DB][j % DB], dsb0[j / DB], dkacc[j % DB]);
-#pragma unroll
-      for (int e = 0; e < EPM; ++e) soft(s1, dp1, p1, EPM * (2 * j + 1) + e, 1);
+      soft_slot(s1, dp1, pb1, dsb1, std::integral_constant<int, 2 * j + 1>{}, 1);
       tq1[j / DB][j % DB] = read_trans<D>(qt + 32 * D * 2, fo, j / DB, j % DB);
-      if ((j + 1) * 2 * EPM % 8 == 0) {
-        constexpr int i = (j + 1) * 2 * EPM / 8 - 1;
-        pb1[i] = pack8(p1, 8 * i);
-        dsb1[i] = pack8(s1, 8 * i);
-        if (FUSED) ds_store(ds_tile, dsb1[i], 1, i);
-      }
+      if (FUSED && (j == KK / 2 - 1 || j == KK - 1)) ds_store(ds_tile, dsb1[j == KK - 1], 1, j == KK - 1);
       __builtin_amdgcn_sched_barrier(0);
     });
     // ---- M2(1)

@@ -79,6 +79,12 @@ __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// The same with the accumulator kept in vector registers whatever the compiler would choose.  The
+// compiler's wait states do not cover its result: see the one place that uses it.
+__device__ __forceinline__ void mfma_vgpr(f32x16& c, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+
 // value held by the same column in the other half of the wave (lane ^ 32), combined by op
 __device__ __forceinline__ float half_max(float x) {
   unsigned u = __builtin_bit_cast(unsigned, x);
