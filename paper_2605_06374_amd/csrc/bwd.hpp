@@ -681,64 +681,58 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   }
 }
 
-// Adds up fp32 partial fragments in a fixed order (chunks in chain order, then the q heads of
-// the group) and stores bf16 rows.  NT tensors per partial (dQ: 1; [dK | dV]: 2), G partial
-// heads per output head; tensor 0 is multiplied by `scale0`.  Elementwise: thread t owns
-// float4 number t of the fragment.
-template <int D, int NT>
-__device__ __forceinline__ void sum_combine(int block, int n_items,
-                                            const varlen_attn_combine_item* __restrict__ items,
-                                            const float* __restrict__ partials,
-                                            __bf16* __restrict__ out0, __bf16* __restrict__ out1,
-                                            int Hin, int G, float scale0, int hpu = 1) {
-  constexpr int DB = D / 32;
-  constexpr int kBlocksPerItem = kTile * D / 4 / kThreads;
-  const int Hout = Hin / G;
-  const int sub = block % kBlocksPerItem;
-  int rest = block / kBlocksPerItem;
-  const int tensor = rest % NT; rest /= NT;
-  const int idx = rest / Hout, oh = rest % Hout;
-  if (idx >= n_items) return;
-  const varlen_attn_combine_item it = items[idx];
-  const int t = sub * kThreads + threadIdx.x;
-  const int lane = t & 63, rq = (t >> 6) & 3, db = (t >> 8) % DB, wave = (t >> 8) / DB;
-  const int h = lane >> 5, c = lane & 31;
-  const int my_row = it.row0 + 32 * wave + c;
-  if (my_row >= it.doc_end) return;
-  const size_t psize = NT * frag_floats<D>();
-  const float* p0 = partials + ((size_t)it.slot0 * Hin + oh * G) * psize + tensor * frag_floats<D>() +
-                    (size_t)t * 4;
-  // partial number j = ch * G + gh sits (ch * Hin + gh) partial sizes after the first; four
-  // loads are kept in flight, the additions stay in index order (deterministic)
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  // of the G heads of a group only every hpu-th holds a partial (its unit swept hpu heads)
-  const int Gp = G / hpu;
-  const int n_parts = it.n_chunks * Gp;
-  auto part = [&](int j) {
-    return *reinterpret_cast<const f32x4*>(p0 + ((size_t)(j / Gp) * Hin + (j % Gp) * hpu) * psize);
-  };
-  int j = 0;
-  for (; j + 4 <= n_parts; j += 4) {
-    const f32x4 x0 = part(j), x1 = part(j + 1), x2 = part(j + 2), x3 = part(j + 3);
-    acc += x0; acc += x1; acc += x2; acc += x3;
-  }
-  for (; j < n_parts; ++j) acc += part(j);
-  const float mul = tensor == 0 ? scale0 : 1.0f;
-  __bf16* out = tensor == 0 ? out0 : out1;
-  *reinterpret_cast<uint2*>(out + ((size_t)my_row * Hout + oh) * D + 32 * db + 8 * rq + 4 * h) =
-      pack4(acc[0] * mul, acc[1] * mul, acc[2] * mul, acc[3] * mul);
-}
-
-// The [dK | dV] reduction (over chunks and the q heads of a group); the dQ partials are summed
-// at the end of the dK/dV kernel's grid.
+// Adds up the [dK | dV] fp32 partial fragments of cut or grouped column tiles in a fixed order
+// (chunks in chain order, then the q heads of the group) and stores bf16 rows; dK is multiplied by
+// `scale`.  Elementwise, work dealt as in fwd_combine_kernel (two column blocks of one wave's rows
+// of one tensor; up to four partials in flight; a fixed number of workgroups walks over the items).
+// The dQ partials are summed at the end of the dK/dV kernel's grid.
 template <int D>
 __global__ void __launch_bounds__(kThreads)
 bwd_combine_kernel(const varlen_attn_plan_header* __restrict__ hdr,
-                   const varlen_attn_combine_item* __restrict__ col_items,
-                   const float* __restrict__ col_partials, __bf16* __restrict__ dk,
+                   const varlen_attn_combine_item* __restrict__ items, int max_items,
+                   const float* __restrict__ partials, __bf16* __restrict__ dk,
                    __bf16* __restrict__ dv, int Hq, int Hkv, float scale) {
-  sum_combine<D, 2>(blockIdx.x, hdr->n_col_combine, col_items, col_partials, dk, dv, Hq, Hq / Hkv, scale,
-                    hdr->col_heads_per_unit);
+  constexpr int DB = D / 32;
+  constexpr int kPieces = 2 * 4 * DB / 2;   // of an (item, kv head): dK and dV, 4 waves, pairs of column blocks
+  constexpr int kFlight = 4;
+  constexpr size_t psize = 2 * frag_floats<D>();
+  const int lane = threadIdx.x & 63, rq = threadIdx.x >> 6, h = lane >> 5, c = lane & 31;
+  const int n_items = hdr->n_col_combine, hpu = hdr->col_heads_per_unit;
+  const int G = Hq / Hkv;
+  for (int work = blockIdx.x; work < max_items * Hkv * kPieces; work += gridDim.x) {
+    const int piece = work % kPieces, rest = work / kPieces;
+    const int idx = rest / Hkv, oh = rest % Hkv;
+    const varlen_attn_combine_item it = items[idx];   // in flight together with n_items
+    if (idx >= n_items) return;
+    const int tensor = piece & 1, wave = (piece >> 1) / (DB / 2), db = 2 * ((piece >> 1) % (DB / 2));
+    const int my_row = it.row0 + 32 * wave + c;
+    if (my_row >= it.doc_end) continue;
+    const float* p0 = partials + ((size_t)it.slot0 * Hq + oh * G) * psize + tensor * frag_floats<D>() +
+                      (size_t)(wave * DB + db) * kThreads * 4 + (size_t)threadIdx.x * 4;
+    // of the G heads of a group only every hpu-th holds a partial (its unit swept hpu heads);
+    // partial number j = ch * Gp + g sits (ch * Hq + g * hpu) partial sizes after the first
+    const int Gp = G / hpu, n_parts = it.n_chunks * Gp;
+    f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+#pragma unroll 1
+    for (int j0 = 0; j0 < n_parts; j0 += kFlight) {
+      f32x4 xa[kFlight], xb[kFlight];
+#pragma unroll
+      for (int j = 0; j < kFlight; ++j) {
+        xa[j] = xb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (j0 + j < n_parts) {   // the same for the whole workgroup
+          const size_t off = ((size_t)((j0 + j) / Gp) * Hq + ((j0 + j) % Gp) * hpu) * psize;
+          xa[j] = *reinterpret_cast<const f32x4*>(p0 + off);
+          xb[j] = *reinterpret_cast<const f32x4*>(p0 + off + kThreads * 4);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < kFlight; ++j) { acc0 += xa[j]; acc1 += xb[j]; }
+    }
+    const float mul = tensor == 0 ? scale : 1.0f;
+    __bf16* out = (tensor == 0 ? dk : dv) + ((size_t)my_row * Hkv + oh) * D + 32 * db + 8 * rq + 4 * h;
+    *reinterpret_cast<uint2*>(out) = pack4(acc0[0] * mul, acc0[1] * mul, acc0[2] * mul, acc0[3] * mul);
+    *reinterpret_cast<uint2*>(out + 32) = pack4(acc1[0] * mul, acc1[1] * mul, acc1[2] * mul, acc1[3] * mul);
+  }
 }
 
 }  // namespace

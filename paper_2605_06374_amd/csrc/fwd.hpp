@@ -235,43 +235,76 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
 }
 
 // Sums the chunks of a cut row chain:  O = sum_c 2^(m_c - m) O_c / sum_c 2^(m_c - m) l_c.
-// Elementwise over the fragment layout: thread t of an (item, head) owns float4 number t of
-// every partial (so all loads are contiguous), chunks are taken in chain order.
+// Elementwise over the fragment layout: a workgroup takes two neighbouring column blocks of one
+// wave's rows of an (item, head), thread t of it float4 number t of both (so all loads are
+// contiguous), chunks in chain order.  What bounds it is the chain of dependent round trips to
+// data that another kernel has just written, so the loads of up to four chunks are in flight
+// together, and a fixed number of workgroups walks over the items: launching one workgroup for
+// every piece of every tile that might be cut took 5 us of the kernel's 7.
 template <int D>
 __global__ void __launch_bounds__(kThreads)
 fwd_combine_kernel(const varlen_attn_plan_header* __restrict__ hdr,
-                   const varlen_attn_combine_item* __restrict__ items,
+                   const varlen_attn_combine_item* __restrict__ items, int max_items,
                    const float* __restrict__ partials, __bf16* __restrict__ o,
                    float* __restrict__ lse, int N, int Hq) {
   constexpr int DB = D / 32;
-  constexpr int kBlocksPerItem = kTile * D / 4 / kThreads;
-  const int sub = blockIdx.x % kBlocksPerItem, rest = blockIdx.x / kBlocksPerItem;
-  const int idx = rest / Hq, head = rest % Hq;
-  if (idx >= hdr->n_row_combine) return;
-  const varlen_attn_combine_item it = items[idx];
-  const int t = sub * kThreads + threadIdx.x;  // float4 index inside the fragment
-  const int lane = t & 63, rq = (t >> 6) & 3, db = (t >> 8) % DB, wave = (t >> 8) / DB;
-  const int h = lane >> 5, c = lane & 31;
-  const int my_row = it.row0 + 32 * wave + c;
-  if (my_row >= it.doc_end) return;
+  constexpr int kPieces = 4 * DB / 2;   // of an (item, head): 4 waves, pairs of column blocks
+  constexpr int kFlight = 4;
+  const int lane = threadIdx.x & 63, rq = threadIdx.x >> 6, h = lane >> 5, c = lane & 31;
   const size_t pstride = (size_t)Hq * fwd_partial_floats<D>();
-  const float* p0 = partials + ((size_t)it.slot0 * Hq + head) * fwd_partial_floats<D>();
-  const float* st = p0 + frag_floats<D>() + wave * 64;  // m[lane], then l[lane] 256 floats on
-  float m = -INFINITY;
-  for (int ch = 0; ch < it.n_chunks; ++ch) m = __builtin_fmaxf(m, st[ch * pstride + lane]);
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  float l = 0.f;
-  for (int ch = 0; ch < it.n_chunks; ++ch) {
-    const float w = __builtin_amdgcn_exp2f(st[ch * pstride + lane] - m);
-    l += w * (st[ch * pstride + kThreads + c] + st[ch * pstride + kThreads + 32 + c]);
-    const f32x4 x = *reinterpret_cast<const f32x4*>(p0 + ch * pstride + (size_t)t * 4);
-    acc += w * x;
+  const int n_items = hdr->n_row_combine;
+  for (int work = blockIdx.x; work < max_items * Hq * kPieces; work += gridDim.x) {
+    const int piece = work % kPieces, rest = work / kPieces;
+    const int idx = rest / Hq, head = rest % Hq;
+    const varlen_attn_combine_item it = items[idx];   // in flight together with n_items
+    if (idx >= n_items) return;
+    const int wave = piece / (DB / 2), db = 2 * (piece % (DB / 2));
+    const int my_row = it.row0 + 32 * wave + c;
+    if (my_row >= it.doc_end) continue;
+    const float* p0 = partials + ((size_t)it.slot0 * Hq + head) * fwd_partial_floats<D>();
+    const float* st = p0 + frag_floats<D>() + wave * 64;  // m[lane], then l[lane] 256 floats on
+    const float* x0 = p0 + (size_t)(wave * DB + db) * kThreads * 4 + (size_t)threadIdx.x * 4;
+    float m = -INFINITY, l = 0.f;
+    f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+#pragma unroll 1
+    for (int ch = 0; ch < it.n_chunks; ch += kFlight) {
+      float mc[kFlight], la[kFlight], lb[kFlight];
+      f32x4 xa[kFlight], xb[kFlight];
+      float m_new = m;
+#pragma unroll
+      for (int j = 0; j < kFlight; ++j) {
+        mc[j] = -INFINITY; la[j] = lb[j] = 0.f; xa[j] = xb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (ch + j < it.n_chunks) {   // the same for the whole workgroup
+          const size_t off = (size_t)(ch + j) * pstride;
+          mc[j] = st[off + lane];
+          la[j] = st[off + kThreads + c];
+          lb[j] = st[off + kThreads + 32 + c];
+          xa[j] = *reinterpret_cast<const f32x4*>(x0 + off);
+          xb[j] = *reinterpret_cast<const f32x4*>(x0 + off + kThreads * 4);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < kFlight; ++j) m_new = __builtin_fmaxf(m_new, mc[j]);
+      if (ch > 0) {
+        const float w = __builtin_amdgcn_exp2f(m - m_new);
+        l *= w; acc0 *= w; acc1 *= w;
+      }
+      m = m_new;
+#pragma unroll
+      for (int j = 0; j < kFlight; ++j) {
+        const float w = __builtin_amdgcn_exp2f(mc[j] - m);
+        l += w * (la[j] + lb[j]);
+        acc0 += w * xa[j];
+        acc1 += w * xb[j];
+      }
+    }
+    const float inv = 1.0f / l;
+    __bf16* out = o + ((size_t)my_row * Hq + head) * D + 32 * db + 8 * rq + 4 * h;
+    *reinterpret_cast<uint2*>(out) = pack4(acc0[0] * inv, acc0[1] * inv, acc0[2] * inv, acc0[3] * inv);
+    *reinterpret_cast<uint2*>(out + 32) = pack4(acc1[0] * inv, acc1[1] * inv, acc1[2] * inv, acc1[3] * inv);
+    if (db == 0 && rq == 0 && h == 0)
+      lse[(size_t)head * N + my_row] = (m + __builtin_amdgcn_logf(l)) * kLn2;
   }
-  const float inv = 1.0f / l;
-  *reinterpret_cast<uint2*>(o + ((size_t)my_row * Hq + head) * D + 32 * db + 8 * rq + 4 * h) =
-      pack4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
-  if (db == 0 && rq == 0 && h == 0)
-    lse[(size_t)head * N + my_row] = (m + __builtin_amdgcn_logf(l)) * kLn2;
 }
 
 }  // namespace

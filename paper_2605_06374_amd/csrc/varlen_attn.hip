@@ -227,6 +227,10 @@ int launch_plan(const varlen_attn_params* p, const int32_t* cu, const Regions& R
   return hipGetLastError() == hipSuccess ? VARLEN_ATTN_OK : VARLEN_ATTN_LAUNCH_FAILED;
 }
 
+// Workgroups of a reduction launch at most: four per compute unit, which start within 1 us (the
+// dispatcher starts about 1200 workgroups per us; 512, 1024 and 2048 measure the same).
+constexpr int kCombineGroups = 1024;
+
 // self_plan: the forward launch makes the plan itself (no plan launch went before)
 template <int D>
 void launch_fwd(const varlen_attn_params* p, const void* q, const void* k, const void* v, void* o,
@@ -247,8 +251,9 @@ void launch_fwd(const varlen_attn_params* p, const void* q, const void* k, const
   if (!(p->flags & VARLEN_ATTN_FLAG_NO_SPLIT)) {
     ScopedKernelTimer timer(kFwdCombine, stream);
     const int cut_tiles = std::max(1, std::min(L.max_combine, L.max_row_slots / 2));   // see launch_bwd
-    fwd_combine_kernel<D><<<dim3((unsigned)cut_tiles * Hq * (kTile * D / 4 / kThreads)), kThreads, 0, stream>>>(
-        R.hdr, R.row_comb, R.row_part, (__bf16*)o, lse, N, Hq);
+    const long long pieces = (long long)cut_tiles * Hq * (D / 16);   // see fwd_combine_kernel
+    fwd_combine_kernel<D><<<dim3((unsigned)std::min<long long>(pieces, kCombineGroups)), kThreads, 0, stream>>>(
+        R.hdr, R.row_comb, cut_tiles, R.row_part, (__bf16*)o, lse, N, Hq);
   }
 }
 
@@ -303,12 +308,12 @@ void launch_bwd(const varlen_attn_params* p, const void* q, const void* k, const
         R.dq_acc, (__bf16*)dq, n8, scale);
   }
   if (split || Hq != Hkv) {
-    constexpr int kBlocksPerItem = kTile * D / 4 / kThreads;
     // grouped-query attention: every tile's [dK | dV] is summed over the group; else cut tiles only
     const int col_items = Hq != Hkv ? L.max_combine : cut_tiles;
+    const long long pieces = (long long)col_items * Hkv * (D / 8);   // see bwd_combine_kernel
     ScopedKernelTimer timer(kBwdCombine, stream);
-    bwd_combine_kernel<D><<<dim3((unsigned)(col_items * Hkv * 2 * kBlocksPerItem)), kThreads, 0, stream>>>(
-        R.hdr, R.col_comb, R.col_part, (__bf16*)dk, (__bf16*)dv, Hq, Hkv, scale);
+    bwd_combine_kernel<D><<<dim3((unsigned)std::min<long long>(pieces, kCombineGroups)), kThreads, 0, stream>>>(
+        R.hdr, R.col_comb, col_items, R.col_part, (__bf16*)dk, (__bf16*)dv, Hq, Hkv, scale);
   }
 }
 
