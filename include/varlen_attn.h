@@ -91,7 +91,9 @@ extern "C" {
                                          4 N Hq d bytes: pass it to varlen_attn_workspace_bytes and
                                          to the forward call as well.  On MI355X this form is the
                                          slower one (the atomic adds bound it) and exists for
-                                         comparison. */
+                                         comparison.  Microbatches that are small enough for the
+                                         small-microbatch kernels (one launch for dQ, dK and dV,
+                                         reproducible) take those whether it is given or not. */
 #define VARLEN_ATTN_FLAG_PLAN_FIRST 32 /* testing: the plan in a launch of its own in front of the forward
                                          also on small microbatches (by default, with at most 64
                                          documents and 256 tiles, the forward workgroups work out

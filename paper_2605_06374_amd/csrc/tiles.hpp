@@ -85,6 +85,21 @@ __device__ __forceinline__ void mfma_vgpr(f32x16& c, const bf16x8& a, const bf16
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
 
+// ... and the first of a sum starts from zero: its accumulator is not written by vector instructions
+// right in front of it (a hazard that the compiler does not see either).
+template <bool FIRST>
+__device__ __forceinline__ void mfma_vgpr_acc(f32x16& c, const bf16x8& a, const bf16x8& b) {
+  if constexpr (FIRST) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
+  else mfma_vgpr(c, a, b);
+}
+// Between the last mfma_vgpr of an accumulator and the first vector instruction that reads it: 16
+// wait states (an 8-pass matrix instruction needs 12), fenced on both sides.
+__device__ __forceinline__ void mfma_vgpr_settle() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_nop 15");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // value held by the same column in the other half of the wave (lane ^ 32), combined by op
 __device__ __forceinline__ float half_max(float x) {
   unsigned u = __builtin_bit_cast(unsigned, x);
@@ -96,6 +111,14 @@ __device__ __forceinline__ float half_sum(float x) {
   unsigned u = __builtin_bit_cast(unsigned, x);
   auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
+// acc + a . b, pairs of products added in fp32
+__device__ __forceinline__ float dot8(const bf16x8& a, const bf16x8& b, float acc) {
+#pragma unroll
+  for (int e = 0; e < 8; e += 2)
+    acc = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{a[e], a[e + 1]}, bf16x2{b[e], b[e + 1]}, acc, false);
+  return acc;
 }
 
 __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int first) {

@@ -9,7 +9,7 @@
 //
 // Sources: tiles.hpp (types, MFMA, LDS tile addressing and the register conventions),
 // staging.hpp (direct-to-LDS loads), plan.hpp, fragments.hpp (partial-result layout), fwd.hpp,
-// bwd.hpp; this file holds the profiler, the host side and the C ABI.
+// bwd.hpp, short.hpp (small microbatches in one launch each way); this file holds the profiler, the host side and the C ABI.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,16 +28,18 @@
 #include "fragments.hpp"
 #include "fwd.hpp"
 #include "bwd.hpp"
+#include "short.hpp"
 
 namespace {
 
 // ----------------------------------------------------------------------------------------
 // Optional per-kernel timing (host-side HIP events only; off by default).
 // ----------------------------------------------------------------------------------------
-enum KernelId { kPlan = 0, kFwd, kFwdCombine, kDq, kDkv, kBwdCombine, kPrep, kFusedBwd, kDqFinish, kNumKernels };
+enum KernelId { kPlan = 0, kFwd, kFwdCombine, kDq, kDkv, kBwdCombine, kPrep, kFusedBwd, kDqFinish, kFwdShort, kBwdShort, kBwdShortGroup, kNumKernels };
 const char* const kKernelNames[kNumKernels] = {
     "plan_kernel", "fwd_kernel", "fwd_combine_kernel", "bwd_dq_kernel", "bwd_dkv_kernel",
-    "bwd_combine_kernel", "bwd_prep_kernel", "bwd_fused_kernel", "bwd_dq_finish_kernel"};
+    "bwd_combine_kernel", "bwd_prep_kernel", "bwd_fused_kernel", "bwd_dq_finish_kernel",
+    "fwd_short_kernel", "bwd_short_kernel", "bwd_short_group_kernel"};
 struct Profiler {
   std::mutex mu;
   bool enabled = false;
@@ -217,6 +219,24 @@ inline bool self_planned_forward(const varlen_attn_params* p) {
          tiles <= kSelfPlanTiles && tiles * p->num_q_heads <= 3 * kResidentGroups / 2;
 }
 
+// ... and the smallest microbatches take the kernels of short.hpp, forward and backward apart.  Their
+// time follows the number of 32-row tiles (one workgroup each) and the longest document, which the
+// host does not know: one document of N tokens is the worst case, N / B the usual one.  Measured
+// against the chunked kernels over 260 .. 3000 tokens, 1 .. 32 heads, one document, four, and a
+// log-normal mix (time before / time here): at head size 128 forward 1.87 .. 1.1 up to 14000 rows
+// (tokens x q heads), 0.9 .. 0.6 above 18000; backward 2.9 .. 1.1 up to 12000 rows, 0.95 .. 0.6 above
+// 16000, with grouped queries 2.1 .. 1.1 up to 9000; at head size 64 up to 30000 and 20000.  One document on one
+// head crosses 1 between 1500 and 2000 tokens (2000 and 2500 at head size 64), four documents
+// between 2500 and 3000.
+inline bool short_path(const varlen_attn_params* p, bool backward) {
+  const bool wide = p->head_dim == 128;
+  const int max_rows = !backward ? (wide ? 14000 : 30000)
+                                 : !wide ? 20000 : p->num_q_heads > p->num_kv_heads ? 9000 : 12000;
+  const long long max_tokens = (wide ? 1536 : 2048) + 384ll * (p->num_docs - 1);
+  return !(p->flags & VARLEN_ATTN_FLAG_NO_SPLIT) && (p->flags >> 8) == 0 && p->num_docs <= kSelfPlanDocs &&
+         p->total_tokens <= max_tokens && (long long)p->total_tokens * p->num_q_heads <= max_rows;
+}
+
 int launch_plan(const varlen_attn_params* p, const int32_t* cu, const Regions& R,
                 const varlen_attn_workspace_layout& L, int slots_cap, hipStream_t stream,
                 int32_t* status_copy = nullptr) {
@@ -235,14 +255,21 @@ constexpr int kCombineGroups = 1024;
 template <int D>
 void launch_fwd(const varlen_attn_params* p, const void* q, const void* k, const void* v, void* o,
                 float* lse, const Regions& R, const varlen_attn_workspace_layout& L,
-                hipStream_t stream, const PlanArgs* self_plan = nullptr) {
+                hipStream_t stream, const PlanArgs& args, bool self_plan) {
   const int N = p->total_tokens, Hq = p->num_q_heads, Hkv = p->num_kv_heads;
+  if (short_path(p, false)) {
+    ScopedKernelTimer timer(kFwdShort, stream);
+    const int plan_block = self_plan ? 1 : 0;
+    fwd_short_kernel<D><<<dim3(plan_block + grid_for(N / kShortRows + p->num_docs, Hq)), kThreads, 0, stream>>>(
+        (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (__bf16*)o, lse, Hq, Hkv, p->softmax_scale, plan_block, args);
+    return;
+  }
   {
     ScopedKernelTimer timer(kFwd, stream);
     if (self_plan)
       fwd_kernel<D, true><<<dim3(grid_for(L.max_units, Hq) + 1), kThreads, 0, stream>>>(
           (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, R.hdr, R.row_units, (__bf16*)o, lse,
-          R.row_part, N, Hq, Hkv, p->softmax_scale, L.max_units, *self_plan);
+          R.row_part, N, Hq, Hkv, p->softmax_scale, L.max_units, args);
     else
       fwd_kernel<D, false><<<dim3(grid_for(L.max_units, Hq)), kThreads, 0, stream>>>(
           (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, R.hdr, R.row_units, (__bf16*)o, lse,
@@ -260,9 +287,23 @@ void launch_fwd(const varlen_attn_params* p, const void* q, const void* k, const
 template <int D>
 void launch_bwd(const varlen_attn_params* p, const void* q, const void* k, const void* v,
                 const void* o, const float* lse, const void* d_o, void* dq, void* dk, void* dv,
-                const Regions& R, const varlen_attn_workspace_layout& L, hipStream_t stream) {
+                const Regions& R, const varlen_attn_workspace_layout& L, hipStream_t stream, const PlanArgs& args) {
   const int N = p->total_tokens, Hq = p->num_q_heads, Hkv = p->num_kv_heads;
   const float scale = p->softmax_scale;
+  if (short_path(p, true)) {
+    ScopedKernelTimer timer(kBwdShort, stream);
+    const int tiles = N / kShortRows + p->num_docs;
+    const unsigned blocks = grid_for(tiles, Hq);
+    bwd_short_kernel<D><<<dim3(2 * blocks), kThreads, 0, stream>>>(
+        (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)o, (const __bf16*)d_o, lse,
+        (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, Hq, Hkv, scale, (int)blocks, R.col_part, args);
+    if (Hq != Hkv) {
+      ScopedKernelTimer group_timer(kBwdShortGroup, stream);
+      bwd_short_group_kernel<D><<<dim3((unsigned)tiles * Hkv * 2), kThreads, 0, stream>>>(
+          R.col_part, (__bf16*)dk, (__bf16*)dv, Hq, Hkv, args);
+    }
+    return;
+  }
   float* neg_lse = R.dsum + (size_t)Hq * N;
   const bool fused = (p->flags & VARLEN_ATTN_FLAG_FUSED_BWD) != 0;
   if (fused) {
@@ -357,19 +398,17 @@ int varlen_attn_fwd(const varlen_attn_params* params, const void* q, const void*
   if (rc != VARLEN_ATTN_OK) return rc;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const Regions R = regions_of(static_cast<char*>(workspace), L);
-  PlanArgs self;
-  const PlanArgs* self_plan = nullptr;
+  const PlanArgs args = plan_args(params, cu_seqlens, R, L, cap, nullptr);
+  bool self_plan = false;
   if (!(params->flags & VARLEN_ATTN_FLAG_REUSE_PLAN)) {
-    if (self_planned_forward(params)) {
-      self = plan_args(params, cu_seqlens, R, L, cap, nullptr);
-      self_plan = &self;
-    } else {
+    self_plan = self_planned_forward(params);
+    if (!self_plan) {
       rc = launch_plan(params, cu_seqlens, R, L, cap, stream);
       if (rc != VARLEN_ATTN_OK) return rc;
     }
   }
-  if (params->head_dim == 128) launch_fwd<128>(params, q, k, v, o, lse, R, L, stream, self_plan);
-  else launch_fwd<64>(params, q, k, v, o, lse, R, L, stream, self_plan);
+  if (params->head_dim == 128) launch_fwd<128>(params, q, k, v, o, lse, R, L, stream, args, self_plan);
+  else launch_fwd<64>(params, q, k, v, o, lse, R, L, stream, args, self_plan);
   return hipGetLastError() == hipSuccess ? VARLEN_ATTN_OK : VARLEN_ATTN_LAUNCH_FAILED;
 }
 
@@ -395,18 +434,12 @@ int varlen_attn_fwd_static(const varlen_attn_params* params, const void* q, cons
   if (rc != VARLEN_ATTN_OK) return rc;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const Regions R = regions_of(static_cast<char*>(ws), L);
-  PlanArgs self;
-  const PlanArgs* self_plan = nullptr;
-  if (self_planned_forward(params)) {
-    self = plan_args(params, cu_seqlens, R, L, cap, plan_status);
-    self_plan = &self;
-    rc = VARLEN_ATTN_OK;
-  } else {
-    rc = launch_plan(params, cu_seqlens, R, L, cap, stream, plan_status);
-  }
+  const PlanArgs args = plan_args(params, cu_seqlens, R, L, cap, plan_status);
+  const bool self_plan = self_planned_forward(params);
+  if (!self_plan) rc = launch_plan(params, cu_seqlens, R, L, cap, stream, plan_status);
   if (rc != VARLEN_ATTN_OK) return rc;
-  if (params->head_dim == 128) launch_fwd<128>(params, q, k, v, o, lse, R, L, stream, self_plan);
-  else launch_fwd<64>(params, q, k, v, o, lse, R, L, stream, self_plan);
+  if (params->head_dim == 128) launch_fwd<128>(params, q, k, v, o, lse, R, L, stream, args, self_plan);
+  else launch_fwd<64>(params, q, k, v, o, lse, R, L, stream, args, self_plan);
   return hipGetLastError() == hipSuccess ? VARLEN_ATTN_OK : VARLEN_ATTN_LAUNCH_FAILED;
 }
 
@@ -425,8 +458,9 @@ int varlen_attn_bwd(const varlen_attn_params* params, const void* q, const void*
     rc = launch_plan(params, cu_seqlens, R, L, cap, stream);
     if (rc != VARLEN_ATTN_OK) return rc;
   }
-  if (params->head_dim == 128) launch_bwd<128>(params, q, k, v, o, lse, d_o, dq, dk, dv, R, L, stream);
-  else launch_bwd<64>(params, q, k, v, o, lse, d_o, dq, dk, dv, R, L, stream);
+  const PlanArgs args = plan_args(params, cu_seqlens, R, L, cap, nullptr);
+  if (params->head_dim == 128) launch_bwd<128>(params, q, k, v, o, lse, d_o, dq, dk, dv, R, L, stream, args);
+  else launch_bwd<64>(params, q, k, v, o, lse, d_o, dq, dk, dv, R, L, stream, args);
   return hipGetLastError() == hipSuccess ? VARLEN_ATTN_OK : VARLEN_ATTN_LAUNCH_FAILED;
 }
 

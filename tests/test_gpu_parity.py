@@ -568,6 +568,25 @@ def test_random_larger_shapes_sampled(gpu):
         del prob
 
 
+SHORT_EDGES = [([1], 1, 1, 128), ([31, 32, 33], 2, 2, 128), ([95, 1, 96, 97], 1, 1, 64),     # 32-row tiles and their remainders
+               ([127, 128, 129, 130, 0, 2], 4, 4, 128), ([20 + i % 9 for i in range(64)], 2, 2, 128),   # as many documents as it takes
+               ([1536], 1, 1, 128), ([1537], 1, 1, 128),                                    # the longest single document, and one token more
+               ([2048], 2, 1, 64), ([700, 820], 8, 8, 128), ([300, 825], 8, 2, 128),        # near the row limits
+               ([160, 3, 97], 32, 8, 128), ([33, 400], 12, 4, 64)]
+
+
+@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("lengths,hq,hkv,d", SHORT_EDGES)
+def test_small_microbatches_both_ways(gpu, lengths, hq, hkv, d, general):
+    """Small microbatches go through kernels of their own (32-row tiles whose chain the four waves
+    of a workgroup share, dQ and dK / dV in one launch); given chunk lengths send the same
+    microbatches through the general kernels.  Both against the oracle in full."""
+    from paper_2605_06374_amd import binding
+    w = W.custom("short", lengths, hq, hkv, d, seed=sum(lengths) + hq + d)
+    prob = run_all(gpu, w, flags=binding.flag_chunk_steps(5, 9) if general else 0)
+    assert_close_full(prob.results(), oracle_full(w), label=f"short {lengths[:6]} general={general}")
+
+
 def test_forward_reuses_a_plan(gpu):
     """One plan for the attention calls of all layers of a micro-batch: a forward that reuses the
     plan of varlen_attn_plan gives the bits of a forward that plans itself."""
