@@ -85,25 +85,24 @@ bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   // Q and dO fragments stay in registers; the O fragments are only needed for
   // D = rowsum(dO * O): each lane holds half of its row's columns, the other half-wave the rest.
   bf16x8 qf[KK], dof[KK];
+  const int load_row = min(my_row, it.doc_end - 1);   // rows past the document end: duplicates, never stored
+  const size_t row_off = ((size_t)load_row * Hq + head) * D;
+  float lse_row = lse[(size_t)head * N + load_row];
   float d_part = 0.f;
+  {
+    bf16x8 of[KK];
+    load_row_frags<D>(d_o + row_off, h, dof);
+    load_row_frags<D>(o + row_off, h, of);
+    load_row_frags<D>(q + row_off, h, qf);
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk) {
-    uint4 t = {0, 0, 0, 0}, u = {0, 0, 0, 0}, w = {0, 0, 0, 0};
-    if (row_valid) {
-      const size_t off = ((size_t)my_row * Hq + head) * D + 16 * kk + 8 * h;
-      t = *reinterpret_cast<const uint4*>(q + off);
-      u = *reinterpret_cast<const uint4*>(d_o + off);
-      w = *reinterpret_cast<const uint4*>(o + off);
-    }
-    qf[kk] = __builtin_bit_cast(bf16x8, t);
-    dof[kk] = __builtin_bit_cast(bf16x8, u);
-    const bf16x8 of = __builtin_bit_cast(bf16x8, w);
+    for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) d_part += (float)dof[kk][e] * (float)of[e];
+      for (int e = 0; e < 8; ++e) d_part += (float)dof[kk][e] * (float)of[kk][e];
   }
   const float dsum_row = half_sum(d_part);
   // rows past the document end get LSE = +huge so that their P is exactly 0
-  const float lse_row = row_valid ? lse[(size_t)head * N + my_row] : 1e30f, lse2 = lse_row * kLog2e;
+  if (!row_valid) lse_row = 1e30f;
+  const float lse2 = lse_row * kLog2e;
   // the unit that starts the chain publishes -D and -LSE / scale for the dK/dV kernel
   if (it.step_begin == 0 && row_valid && h == 0) {
     neg_dsum[(size_t)head * N + my_row] = -dsum_row;
@@ -112,6 +111,8 @@ bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   FragOffsets<D> fo;
   fo.init(lane);
   wait_all_vm_visible();
+  pin_frags(qf);
+  pin_frags(dof);
 
   f32x16 acc[DB];
 #pragma unroll
@@ -447,16 +448,12 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
     static_for<KK>([&](auto p) __attribute__((always_inline)) { piece(p, stage_c); });
   };
   bf16x8 kf[KK], vf[KK];
+  const size_t kv_off = ((size_t)min(my_kv, it.doc_end - 1) * Hkv + kvh) * D;
+  load_row_frags<D>(k + kv_off, h, kf);
+  load_row_frags<D>(v + kv_off, h, vf);
+  if (FUSED && !kv_valid) {   // rows past the document end must not enter dQ; elsewhere they are never stored
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk) {
-    uint4 t = {0, 0, 0, 0}, u = {0, 0, 0, 0};
-    if (kv_valid) {
-      const size_t off = ((size_t)my_kv * Hkv + kvh) * D + 16 * kk + 8 * h;
-      t = *reinterpret_cast<const uint4*>(k + off);
-      u = *reinterpret_cast<const uint4*>(v + off);
-    }
-    kf[kk] = __builtin_bit_cast(bf16x8, t);
-    vf[kk] = __builtin_bit_cast(bf16x8, u);
+    for (int kk = 0; kk < KK; ++kk) kf[kk] = vf[kk] = __builtin_bit_cast(bf16x8, uint4{0, 0, 0, 0});
   }
   FragOffsets<D> fo;
   fo.init(lane);
@@ -466,6 +463,8 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
     key_loader.issue(k + (size_t)kvh * D, it.row0, it.doc_end - 1, lds_addr_of(key_tile), wave);
   }
   wait_all_vm_visible();
+  pin_frags(kf);
+  pin_frags(vf);
   // this lane's row of the dS tiles: key 32 wave + c; element (key, query) sits in the 16-byte
   // chunk query / 8 of that row, swizzled like every tile
   // dS of one 32-query block, accumulator registers 8 cc .. 8 cc + 7 (queries 32 qb + 16 cc +

@@ -98,18 +98,13 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
   for (int st = 0; st < NS - 1; ++st) issue(st, st);
 
   bf16x8 qf[KK];
-#pragma unroll
-  for (int kk = 0; kk < KK; ++kk) {
-    uint4 t = {0, 0, 0, 0};
-    if (row_valid)
-      t = *reinterpret_cast<const uint4*>(q + ((size_t)my_row * Hq + head) * D + 16 * kk + 8 * h);
-    qf[kk] = __builtin_bit_cast(bf16x8, t);
-  }
+  load_row_frags<D>(q + ((size_t)min(my_row, it.doc_end - 1) * Hq + head) * D, h, qf);
   FragOffsets<D> fo;
   fo.init(lane);
   // Let the compiler see its own loads complete here, once; otherwise it keeps a vmcnt(0)
   // for them inside the loop, which would also wait for every prefetch in flight.
   wait_all_vm_visible();
+  pin_frags(qf);
 
   f32x16 oacc[DB];
 #pragma unroll

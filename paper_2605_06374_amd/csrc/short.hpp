@@ -78,17 +78,6 @@ struct BlockLoader {
   }
 };
 
-// Fragment of 32 rows in registers: A or B operand slices, row `row` on lane column c
-template <int D>
-__device__ __forceinline__ void load_row_frags(const __bf16* base, bool valid, int h, bf16x8 (&f)[D / 16]) {
-#pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) {
-    uint4 t = {0, 0, 0, 0};
-    if (valid) t = *reinterpret_cast<const uint4*>(base + 16 * kk + 8 * h);
-    f[kk] = __builtin_bit_cast(bf16x8, t);
-  }
-}
-
 // One wave's accumulator of a 32-row tile into its LDS region, in fragment order: float4 number
 // (db * 4 + rq) * 64 + lane.
 template <int D>
@@ -153,10 +142,11 @@ fwd_short_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
   };
   if (wave < n_blocks) issue(wave, 0);
   bf16x8 qf[KK];
-  load_row_frags<D>(q + ((size_t)my_row * Hq + head) * D, row_valid, h, qf);
+  load_row_frags<D>(q + ((size_t)min(my_row, it.doc_end - 1) * Hq + head) * D, h, qf);
   FragOffsets<D> fo;
   fo.init(lane);
   wait_all_vm_visible();
+  pin_frags(qf);
 
   f32x16 oacc[DB];
 #pragma unroll
@@ -287,20 +277,24 @@ bwd_short_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
     };
     if (wave < n_blocks) issue(wave, 0);
     bf16x8 qf[KK], dof[KK];
+    const int load_row = min(my_row, it.doc_end - 1);   // rows past the document end: duplicates, never stored
+    const size_t row_off = ((size_t)load_row * Hq + head) * D;
+    const float lse_row = lse[(size_t)head * N + load_row];
     float d_part = 0.f;
     {
       bf16x8 of[KK];
-      const size_t off = ((size_t)my_row * Hq + head) * D;
-      load_row_frags<D>(q + off, row_valid, h, qf);
-      load_row_frags<D>(d_o + off, row_valid, h, dof);
-      load_row_frags<D>(o + off, row_valid, h, of);
+      load_row_frags<D>(d_o + row_off, h, dof);
+      load_row_frags<D>(o + row_off, h, of);
+      load_row_frags<D>(q + row_off, h, qf);
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) d_part = dot8(dof[kk], of[kk], d_part);
     }
     const float dsum = half_sum(d_part);
-    const float lse2 = row_valid ? lse[(size_t)head * N + my_row] * kLog2e : 1e30f;
+    const float lse2 = row_valid ? lse_row * kLog2e : 1e30f;
     fo.init(lane);
     wait_all_vm_visible();
+    pin_frags(qf);
+    pin_frags(dof);
     f32x16 acc[DB];
 #pragma unroll
     for (int i = 0; i < DB; ++i) acc[i] = f32x16(0.f);
@@ -386,10 +380,13 @@ bwd_short_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
     issue_o(wave);
   }
   bf16x8 kf[KK], vf[KK];
-  load_row_frags<D>(k + ((size_t)my_kv * Hkv + kvh) * D, kv_valid, h, kf);
-  load_row_frags<D>(v + ((size_t)my_kv * Hkv + kvh) * D, kv_valid, h, vf);
+  const size_t kv_off = ((size_t)min(my_kv, it.doc_end - 1) * Hkv + kvh) * D;
+  load_row_frags<D>(k + kv_off, h, kf);
+  load_row_frags<D>(v + kv_off, h, vf);
   fo.init(lane);
   wait_all_vm_visible();
+  pin_frags(kf);
+  pin_frags(vf);
   f32x16 dkacc[DB], dvacc[DB];
 #pragma unroll
   for (int i = 0; i < DB; ++i) { dkacc[i] = f32x16(0.f); dvacc[i] = f32x16(0.f); }
