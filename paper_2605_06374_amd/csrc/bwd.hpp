@@ -201,7 +201,9 @@ bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
     store_frag<D>(partials + ((size_t)it.slot * Hq + head) * frag_floats<D>(), acc, wave, lane);
     return;
   }
-  if (row_valid) store_rows<D>(dq + ((size_t)my_row * Hq + head) * D, acc, h, scale);
+  __syncthreads();   // every wave is done with the stages
+  store_rows<D>(smem + wave * RowTile<D>::kBytes, dq + ((size_t)wave_row0 * Hq + head) * D, (size_t)Hq * D,
+                it.doc_end - wave_row0, acc, lane, scale);
 }
 
 // ----------------------------------------------------------------------------------------
@@ -261,8 +263,10 @@ __device__ __forceinline__ void dq_tile_combine(int block, const varlen_attn_pla
                                                 int max_items,
                                                 const varlen_attn_combine_item* __restrict__ items,
                                                 const float* __restrict__ partials,
-                                                __bf16* __restrict__ dq, int Hq, float scale) {
+                                                __bf16* __restrict__ dq, int Hq, float scale, char* lds) {
   constexpr int DB = D / 32;
+  using Tile = RowTile<D>;
+  constexpr int kTiles = 4 / DB;   // [32][D] tiles that four float4s of every thread make up
   constexpr int kPerThread = kTile * D / 4 / kThreads;   // float4s of a fragment per thread
   const int idx = block / Hq, head = block % Hq;
   // both loads in flight together
@@ -294,15 +298,22 @@ __device__ __forceinline__ void dq_tile_combine(int block, const varlen_attn_pla
         for (int u = 0; u < 4; ++u)
           if (c0 + j < it.n_chunks) acc[u] += x[j][u];
     }
+    // float4 s0 + u of a thread: wave (s0 + u) / DB, column block (s0 + u) % DB, register quad = the
+    // thread's wave.  The rows are put together in LDS (two buffers in turn) and stored whole.
+    char* const tiles = lds + ((s0 >> 2) & 1) * kTiles * Tile::kBytes;
+    const int lane = threadIdx.x & 63, rq = threadIdx.x >> 6;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int t = (s0 + u) * kThreads + threadIdx.x;
-      const int lane = t & 63, rq = (t >> 6) & 3, db = (t >> 8) % DB, wave = (t >> 8) / DB;
-      const int h = lane >> 5, c = lane & 31;
-      const int my_row = it.row0 + 32 * wave + c;
-      if (my_row < it.doc_end)
-        *reinterpret_cast<uint2*>(dq + ((size_t)my_row * Hq + head) * D + 32 * db + 8 * rq + 4 * h) =
-            pack4(acc[u][0] * scale, acc[u][1] * scale, acc[u][2] * scale, acc[u][3] * scale);
+    for (int u = 0; u < 4; ++u)
+      Tile::put(tiles + (u / DB) * Tile::kBytes, lane & 31, lane >> 5, 4 * (u % DB) + rq,
+                pack4(acc[u][0] * scale, acc[u][1] * scale, acc[u][2] * scale, acc[u][3] * scale));
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      constexpr int kRows = kThreads / Tile::kChunks;   // 16 or 32: per store of the workgroup
+      const int row = kRows * i + threadIdx.x / Tile::kChunks, chunk = threadIdx.x % Tile::kChunks;
+      const uint4 w = Tile::get(tiles + (row / 32) * Tile::kBytes, row % 32, chunk);
+      const int out_row = it.row0 + 32 * (s0 / DB) + row;
+      if (out_row < it.doc_end) *reinterpret_cast<uint4*>(dq + ((size_t)out_row * Hq + head) * D + 8 * chunk) = w;
     }
   }
 }
@@ -375,7 +386,7 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
 
   // the workgroups behind the units sum the dQ partials that the dQ kernel left
   if (!FUSED && (int)blockIdx.x >= unit_blocks) {
-    dq_tile_combine<D>(blockIdx.x - unit_blocks, hdr, max_items, row_items, row_partials, dq, Hq, scale);
+    dq_tile_combine<D>(blockIdx.x - unit_blocks, hdr, max_items, row_items, row_partials, dq, Hq, scale, smem);
     return;
   }
   int unit_idx, head;
@@ -674,9 +685,12 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
     store_frag<D>(part + frag_floats<D>(), dvacc, wave, lane);
     return;
   }
-  if (kv_valid) {
-    store_rows<D>(dk + ((size_t)my_kv * Hkv + kvh) * D, dkacc, h, scale);
-    store_rows<D>(dv + ((size_t)my_kv * Hkv + kvh) * D, dvacc, h, 1.0f);
+  __syncthreads();   // every wave is done with the stages
+  {
+    char* tile = smem + 2 * wave * RowTile<D>::kBytes;
+    const size_t first = ((size_t)wave_kv0 * Hkv + kvh) * D;
+    store_rows<D>(tile, dk + first, (size_t)Hkv * D, it.doc_end - wave_kv0, dkacc, lane, scale);
+    store_rows<D>(tile + RowTile<D>::kBytes, dv + first, (size_t)Hkv * D, it.doc_end - wave_kv0, dvacc, lane, 1.0f);
   }
 }
 
@@ -695,6 +709,9 @@ bwd_combine_kernel(const varlen_attn_plan_header* __restrict__ hdr,
   constexpr int kPieces = 2 * 4 * DB / 2;   // of an (item, kv head): dK and dV, 4 waves, pairs of column blocks
   constexpr int kFlight = 4;
   constexpr size_t psize = 2 * frag_floats<D>();
+  using Tile = RowTile<64>;
+  __shared__ __attribute__((aligned(16))) char tiles[2][Tile::kBytes];
+  int buf = 0;   // two tiles in turn: one barrier per item
   const int lane = threadIdx.x & 63, rq = threadIdx.x >> 6, h = lane >> 5, c = lane & 31;
   const int n_items = hdr->n_col_combine, hpu = hdr->col_heads_per_unit;
   const int G = Hq / Hkv;
@@ -704,8 +721,8 @@ bwd_combine_kernel(const varlen_attn_plan_header* __restrict__ hdr,
     const varlen_attn_combine_item it = items[idx];   // in flight together with n_items
     if (idx >= n_items) return;
     const int tensor = piece & 1, wave = (piece >> 1) / (DB / 2), db = 2 * ((piece >> 1) % (DB / 2));
-    const int my_row = it.row0 + 32 * wave + c;
-    if (my_row >= it.doc_end) continue;
+    const int row0 = it.row0 + 32 * wave;
+    if (row0 >= it.doc_end) continue;   // (rows past the end inside the block: computed, not stored)
     const float* p0 = partials + ((size_t)it.slot0 * Hq + oh * G) * psize + tensor * frag_floats<D>() +
                       (size_t)(wave * DB + db) * kThreads * 4 + (size_t)threadIdx.x * 4;
     // of the G heads of a group only every hpu-th holds a partial (its unit swept hpu heads);
@@ -728,9 +745,14 @@ bwd_combine_kernel(const varlen_attn_plan_header* __restrict__ hdr,
       for (int j = 0; j < kFlight; ++j) { acc0 += xa[j]; acc1 += xb[j]; }
     }
     const float mul = tensor == 0 ? scale : 1.0f;
-    __bf16* out = (tensor == 0 ? dk : dv) + ((size_t)my_row * Hkv + oh) * D + 32 * db + 8 * rq + 4 * h;
-    *reinterpret_cast<uint2*>(out) = pack4(acc0[0] * mul, acc0[1] * mul, acc0[2] * mul, acc0[3] * mul);
-    *reinterpret_cast<uint2*>(out + 32) = pack4(acc1[0] * mul, acc1[1] * mul, acc1[2] * mul, acc1[3] * mul);
+    Tile::put(tiles[buf], c, h, rq, pack4(acc0[0] * mul, acc0[1] * mul, acc0[2] * mul, acc0[3] * mul));
+    Tile::put(tiles[buf], c, h, 4 + rq, pack4(acc1[0] * mul, acc1[1] * mul, acc1[2] * mul, acc1[3] * mul));
+    __syncthreads();
+    const int out_row = row0 + (threadIdx.x >> 3), chunk = threadIdx.x & 7;
+    const uint4 w = Tile::get(tiles[buf], threadIdx.x >> 3, chunk);
+    if (out_row < it.doc_end)
+      *reinterpret_cast<uint4*>((tensor == 0 ? dk : dv) + ((size_t)out_row * Hkv + oh) * D + 32 * db + 8 * chunk) = w;
+    buf ^= 1;
   }
 }
 

@@ -221,12 +221,12 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
     part[frag_floats<D>() + kThreads + tid] = l_run;
     return;
   }
+  __syncthreads();   // every wave is done with the stages
   if (!wave_active) return;
   const float l_tot = half_sum(l_run);
-  if (row_valid) {
-    store_rows<D>(o + ((size_t)my_row * Hq + head) * D, oacc, h, 1.0f / l_tot);
-    if (h == 0) lse[(size_t)head * N + my_row] = (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2;
-  }
+  store_rows<D>(smem + wave * RowTile<D>::kBytes, o + ((size_t)wave_row0 * Hq + head) * D, (size_t)Hq * D,
+                it.doc_end - wave_row0, oacc, lane, 1.0f / l_tot);
+  if (row_valid && h == 0) lse[(size_t)head * N + my_row] = (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2;
 }
 
 // Sums the chunks of a cut row chain:  O = sum_c 2^(m_c - m) O_c / sum_c 2^(m_c - m) l_c.
@@ -235,7 +235,8 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
 // contiguous), chunks in chain order.  What bounds it is the chain of dependent round trips to
 // data that another kernel has just written, so the loads of up to four chunks are in flight
 // together, and a fixed number of workgroups walks over the items: launching one workgroup for
-// every piece of every tile that might be cut took 5 us of the kernel's 7.
+// every piece of every tile that might be cut took 5 us of the kernel's 7.  The 32 x 64 block of O
+// is put together in LDS and stored in runs of 128 bytes.
 template <int D>
 __global__ void __launch_bounds__(kThreads)
 fwd_combine_kernel(const varlen_attn_plan_header* __restrict__ hdr,
@@ -245,6 +246,9 @@ fwd_combine_kernel(const varlen_attn_plan_header* __restrict__ hdr,
   constexpr int DB = D / 32;
   constexpr int kPieces = 4 * DB / 2;   // of an (item, head): 4 waves, pairs of column blocks
   constexpr int kFlight = 4;
+  using Tile = RowTile<64>;
+  __shared__ __attribute__((aligned(16))) char tiles[2][Tile::kBytes];
+  int buf = 0;   // two tiles in turn: one barrier per item
   const int lane = threadIdx.x & 63, rq = threadIdx.x >> 6, h = lane >> 5, c = lane & 31;
   const size_t pstride = (size_t)Hq * fwd_partial_floats<D>();
   const int n_items = hdr->n_row_combine;
@@ -254,8 +258,8 @@ fwd_combine_kernel(const varlen_attn_plan_header* __restrict__ hdr,
     const varlen_attn_combine_item it = items[idx];   // in flight together with n_items
     if (idx >= n_items) return;
     const int wave = piece / (DB / 2), db = 2 * (piece % (DB / 2));
-    const int my_row = it.row0 + 32 * wave + c;
-    if (my_row >= it.doc_end) continue;
+    const int row0 = it.row0 + 32 * wave, my_row = row0 + c;
+    if (row0 >= it.doc_end) continue;   // (rows past the end inside the block: computed, not stored)
     const float* p0 = partials + ((size_t)it.slot0 * Hq + head) * fwd_partial_floats<D>();
     const float* st = p0 + frag_floats<D>() + wave * 64;  // m[lane], then l[lane] 256 floats on
     const float* x0 = p0 + (size_t)(wave * DB + db) * kThreads * 4 + (size_t)threadIdx.x * 4;
@@ -294,10 +298,14 @@ fwd_combine_kernel(const varlen_attn_plan_header* __restrict__ hdr,
       }
     }
     const float inv = 1.0f / l;
-    __bf16* out = o + ((size_t)my_row * Hq + head) * D + 32 * db + 8 * rq + 4 * h;
-    *reinterpret_cast<uint2*>(out) = pack4(acc0[0] * inv, acc0[1] * inv, acc0[2] * inv, acc0[3] * inv);
-    *reinterpret_cast<uint2*>(out + 32) = pack4(acc1[0] * inv, acc1[1] * inv, acc1[2] * inv, acc1[3] * inv);
-    if (db == 0 && rq == 0 && h == 0)
+    Tile::put(tiles[buf], c, h, rq, pack4(acc0[0] * inv, acc0[1] * inv, acc0[2] * inv, acc0[3] * inv));
+    Tile::put(tiles[buf], c, h, 4 + rq, pack4(acc1[0] * inv, acc1[1] * inv, acc1[2] * inv, acc1[3] * inv));
+    __syncthreads();
+    const int out_row = row0 + (threadIdx.x >> 3), chunk = threadIdx.x & 7;
+    const uint4 w = Tile::get(tiles[buf], threadIdx.x >> 3, chunk);
+    if (out_row < it.doc_end) *reinterpret_cast<uint4*>(o + ((size_t)out_row * Hq + head) * D + 32 * db + 8 * chunk) = w;
+    buf ^= 1;
+    if (db == 0 && rq == 0 && h == 0 && my_row < it.doc_end)
       lse[(size_t)head * N + my_row] = (m + __builtin_amdgcn_logf(l)) * kLn2;
   }
 }
