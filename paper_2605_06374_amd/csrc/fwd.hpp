@@ -34,7 +34,7 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
   if (SELF) {
     // Small microbatch: no plan launch in front.  Workgroup 0 makes the plan (for the reduction
     // of this forward and for the backward) while the others work out their own unit from
-    // cu_seqlens, in the order (tile, chunk), by the plan's rules.
+    // cu_seqlens by the plan's rules (the order: derive_row_unit).
     __shared__ varlen_attn_unit own_unit;
     __shared__ int own_valid;
     if (blockIdx.x == 0) {
@@ -45,7 +45,7 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
     if (threadIdx.x < 64) {
       varlen_attn_unit mine;
       const bool ok = derive_row_unit(plan.cu, plan.B, plan.N, Hq, plan.no_split, plan.force_ch[0],
-                                      plan.slots_cap, unit_idx, threadIdx.x, mine);
+                                      plan.slots_cap, unit_idx, plan.longest_first, threadIdx.x, mine);
       if (threadIdx.x == 0) { own_valid = ok ? 1 : 0; if (ok) own_unit = mine; }
     }
     __syncthreads();

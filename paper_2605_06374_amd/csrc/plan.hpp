@@ -45,6 +45,7 @@ struct PlanArgs {
   varlen_attn_unit* units[2];
   varlen_attn_combine_item* comb[2];
   int max_units, max_combine, max_slots[2], slots_cap;
+  bool longest_first;     // order in which the forward's workgroups take their own units (derive_row_unit)
   int32_t* status_copy;   // optional second place for the status word (device), or null
 };
 
@@ -89,7 +90,7 @@ __device__ __forceinline__ int wave_total(int v) { return lane_value(wave_inclus
 
 // ----------------------------------------------------------------------------------------
 // The u-th row unit of a microbatch of at most 64 documents and 256 tiles, in the order
-// (tile, chunk), worked out by one wave from cu_seqlens alone with the plan's own rules (chunk
+// (tile, chunk) or, `longest_first`, (chunk length of the tile, tile, chunk), worked out by one wave from cu_seqlens alone with the plan's own rules (chunk
 // length, nearly equal chunks, slots of cut tiles numbered in tile order): a forward workgroup
 // of a small microbatch finds its unit this way instead of waiting for the plan.  All 64
 // lanes must call it; every lane gets the same answer.  False: cu_seqlens is malformed (the
@@ -98,7 +99,7 @@ __device__ __forceinline__ int wave_total(int v) { return lane_value(wave_inclus
 constexpr int kSelfPlanDocs = 64, kSelfPlanTiles = 256;
 __device__ __forceinline__ bool derive_row_unit(const int32_t* __restrict__ cu, int B, int N, int Hq,
                                                 int no_split, int forced, int slots_cap, int u,
-                                                int lane, varlen_attn_unit& out) {
+                                                bool longest_first, int lane, varlen_attn_unit& out) {
   int s = 0, e = 0;
   if (lane < B) { s = cu[lane]; e = cu[lane + 1]; }
   const int l = e - s;
@@ -142,14 +143,39 @@ __device__ __forceinline__ bool derive_row_unit(const int32_t* __restrict__ cu, 
     if (no_split || wave_total(cut) <= slots_cap) break;
     ch *= 2;
   }
+  // Longest first: the units of tiles with chunks longer than x come before all others, F(x) of them.
+  // The smallest x with F(x) <= u, found bit by bit, is the length of the unit asked for; among the
+  // tiles of that length it is number u - F(x) in tile order.  One sum over the wave per bit, which
+  // costs a workgroup less than half a microsecond.
+  int in_order[kRounds];   // units of the tile that count towards u
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) in_order[r] = nc[r];
+  if (longest_first) {
+    int len[kRounds];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) len[r] = nc[r] ? (n[r] + nc[r] - 1) / nc[r] : 0;
+    int x = 2 * kSelfPlanTiles * kTile / kStep - 1, before = 0;   // all bits set, no chain is that long
+#pragma unroll 1
+    for (int bit = kSelfPlanTiles * kTile / kStep; bit; bit >>= 1) {
+      int longer = 0;
+#pragma unroll
+      for (int r = 0; r < kRounds; ++r) longer += len[r] > x - bit ? nc[r] : 0;
+      longer = wave_total(longer);
+      if (longer <= u) { x -= bit; before = longer; }
+    }
+    if (x == 0) return false;   // all units come before u
+    u -= before;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) in_order[r] = len[r] == x ? nc[r] : 0;
+  }
   int units_before = 0, slots_before = 0;
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
     if (64 * r < n_tiles) {
       const int cut = nc[r] > 1 ? nc[r] : 0;
-      const int u_incl = wave_inclusive_sum(nc[r]), s_incl = wave_inclusive_sum(cut);
-      const int u0 = units_before + u_incl - nc[r];
-      const unsigned long long hit = __ballot(u0 <= u && u < u0 + nc[r]);
+      const int u_incl = wave_inclusive_sum(in_order[r]), s_incl = wave_inclusive_sum(cut);
+      const int u0 = units_before + u_incl - in_order[r];
+      const unsigned long long hit = __ballot(u0 <= u && u < u0 + in_order[r]);
       if (hit) {
         const int src = __ffsll((long long)hit) - 1;
         const int nn = lane_value(n[r], src), k = lane_value(nc[r], src), c = u - lane_value(u0, src);

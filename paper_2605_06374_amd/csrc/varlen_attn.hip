@@ -184,6 +184,11 @@ Regions regions_of(char* ws, const varlen_attn_workspace_layout& L) {
                  reinterpret_cast<float*>(ws + L.dq_accumulator_offset)};
 }
 
+// (tile, head) pairs at most; up to one round of workgroups their order does not matter
+inline long long tile_heads(const varlen_attn_params* p) {
+  return ((long long)p->total_tokens / kTile + p->num_docs) * p->num_q_heads;
+}
+
 PlanArgs plan_args(const varlen_attn_params* p, const int32_t* cu, const Regions& R,
                    const varlen_attn_workspace_layout& L, int slots_cap, int32_t* status_copy) {
   PlanArgs a;
@@ -197,6 +202,7 @@ PlanArgs plan_args(const varlen_attn_params* p, const int32_t* cu, const Regions
   a.comb[0] = R.row_comb; a.comb[1] = R.col_comb;
   a.max_units = L.max_units; a.max_combine = L.max_combine;
   a.max_slots[0] = L.max_row_slots; a.max_slots[1] = L.max_col_slots; a.slots_cap = slots_cap;
+  a.longest_first = tile_heads(p) > kResidentGroups;
   a.status_copy = status_copy;
   return a;
 }
@@ -208,15 +214,16 @@ inline bool small_plan(const varlen_attn_params* p) {
          tiles <= 4 * kPlanThreadsSmall;
 }
 // ... and, smaller still, needs no plan launch in front of the forward: its workgroups work out
-// their own units while one of them makes the plan (see fwd_kernel).  They take the units in
-// the order (tile, chunk), not longest first, so this is only for microbatches whose units are
-// resident all at once: the plan cuts chains to fill the 512 / Hq workgroup slots per head as
-// long as the tiles take at most three quarters of them (plan_chunk_steps), i.e. up to
-// tiles x Hq <= 768.
+// their own units while one of them makes the plan (see fwd_kernel).  Every workgroup pays for that
+// again, so it is worth it up to three rounds of workgroups.  Forward on a plan launch / here, 82
+// microbatches of 3000 to 32000 tokens, 4 to 32 heads: 1.18 .. 1.00 from 800 to 1536 (tile, head)
+// pairs (head size 64 1.19 .. 1.02), 1.05 .. 0.98 from 1700 to 2200.  Longest first as soon as the
+// units may exceed one round: 10063 of 11918 tokens in one document, 8 heads, 768 pairs, took 288 us
+// in tile order and 263 us on a plan launch.
 inline bool self_planned_forward(const varlen_attn_params* p) {
   const long long tiles = (long long)p->total_tokens / kTile + p->num_docs;
   return small_plan(p) && !(p->flags & VARLEN_ATTN_FLAG_PLAN_FIRST) && p->num_docs <= kSelfPlanDocs &&
-         tiles <= kSelfPlanTiles && tiles * p->num_q_heads <= 3 * kResidentGroups / 2;
+         tiles <= kSelfPlanTiles && tile_heads(p) <= 3 * kResidentGroups;
 }
 
 // ... and the smallest microbatches take the kernels of short.hpp, forward and backward apart.  Their

@@ -487,6 +487,29 @@ def test_self_planned_forward_equals_planned_forward(gpu, lengths, hq, hkv, d):
     assert_close_full(b.results(), oracle_full(w), label="self-planned " + str(lengths[:6]))
 
 
+@pytest.mark.parametrize("no_split", [False, True])
+@pytest.mark.parametrize("lengths,hq,hkv,d", [([1500, 20, 0, 700, 129, 1], 22, 11, 64),   # 528 (tile, head) pairs: just above one round
+                                               ([128 * i for i in range(1, 9)], 16, 4, 128),   # chains of every length, no remainder
+                                               ([5982, 1], 32, 32, 64), ([6144], 32, 8, 128),   # exactly three rounds; one tile more: behind a plan launch
+                                               ([1, 31000, 900], 4, 4, 128), ([64] * 63 + [2000], 8, 4, 64)])
+def test_self_planned_units_longest_first(gpu, lengths, hq, hkv, d, no_split):
+    """Above one round of workgroups the forward workgroups take their own units longest first: every
+    unit is taken once, with the slots of the plan, hence the bits of a forward behind a plan launch
+    (a unit left out leaves the poison, or a partial result of the other run)."""
+    from paper_2605_06374_amd import binding
+    w = W.custom("longest", lengths, hq, hkv, d, seed=sum(lengths) + hq)
+    bits = []
+    for flags in (binding.FLAG_PLAN_FIRST, 0):
+        prob = gpu.DeviceProblem(w, flags=flags | (binding.FLAG_NO_SPLIT if no_split else 0))
+        prob.poison_outputs()
+        prob.forward()
+        got = prob.results()
+        assert np.isfinite(got["o"]).all() and np.isfinite(got["lse"]).all()
+        bits.append({n: b for n, b in prob.result_bits().items() if n in ("o", "lse")})
+    for n in bits[0]:
+        assert np.array_equal(bits[0][n], bits[1][n]), n
+
+
 def _random_shape(rng, kind):
     if kind == 0:     # many short documents
         lengths = rng.integers(0, 40, size=int(rng.integers(1, 70)))
