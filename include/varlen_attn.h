@@ -75,7 +75,9 @@ extern "C" {
                                          preceding varlen_attn_plan / varlen_attn_fwd call with
                                          the same params (apart from this flag) and cu_seqlens
                                          wrote, e.g. for the other layers of the same
-                                         micro-batch; the plan step is then left out */
+                                         micro-batch; the plan step is then left out, and the
+                                         contents of cu_seqlens are not read again (the buffer may
+                                         hold the next micro-batch by then) */
 #define VARLEN_ATTN_FLAG_NO_SPLIT 2   /* never cut a chain: every document is then computed
                                          exactly as if it were alone in the microbatch
                                          (bit-identical results under repacking), at the
@@ -143,7 +145,8 @@ typedef struct {
   int32_t n_chunks;
 } varlen_attn_combine_item;
 
-/* Header at the start of the workspace, written by the plan step. */
+/* Header at the start of the workspace, written by the plan step.  Between it and the row units the
+ * plan keeps data of the library's own. */
 typedef struct {
   int32_t status;          /* VARLEN_ATTN_OK, VARLEN_ATTN_BAD_CU_SEQLENS or VARLEN_ATTN_PLAN_OVERFLOW */
   int32_t n_row_units;     /* units of the forward / dQ direction */

@@ -36,6 +36,16 @@ constexpr int kTargetUnits = 512;   // (unit, head) pairs from cut chains to aim
 constexpr long long kGroupSweepMinUnits = 512;  // column workgroups that must remain when units sweep several q heads
 constexpr int kNoSplitSteps = 1 << 28;
 
+// Behind the header the plan of at most kSelfPlanDocs documents and 65535 tokens keeps the documents'
+// ends, so that the kernels that take their tiles from the documents themselves (short.hpp) need
+// nothing but the plan either: a caller may refill cu_seqlens once the plan is made.  All zero, which
+// is no partition of N tokens, when nothing was planned.
+constexpr int kSelfPlanDocs = 64, kSelfPlanTiles = 256;
+static_assert(sizeof(varlen_attn_plan_header) + 2 * kSelfPlanDocs <= 256, "the unit arrays start at byte 256");
+__device__ __forceinline__ uint16_t* kept_ends(const varlen_attn_plan_header* hdr) {
+  return reinterpret_cast<uint16_t*>(const_cast<varlen_attn_plan_header*>(hdr) + 1);
+}
+
 struct PlanArgs {
   const int32_t* cu;
   int B, N, Hq, g, no_split;
@@ -96,7 +106,6 @@ __device__ __forceinline__ int wave_total(int v) { return lane_value(wave_inclus
 // lanes must call it; every lane gets the same answer.  False: cu_seqlens is malformed (the
 // plan reports it) or u is past the last unit.
 // ----------------------------------------------------------------------------------------
-constexpr int kSelfPlanDocs = 64, kSelfPlanTiles = 256;
 __device__ __forceinline__ bool derive_row_unit(const int32_t* __restrict__ cu, int B, int N, int Hq,
                                                 int no_split, int forced, int slots_cap, int u,
                                                 bool longest_first, int lane, varlen_attn_unit& out) {
@@ -243,6 +252,7 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
   varlen_attn_plan_header* hdr = a.hdr;
   if (bad) {
     if (tid < (int)(sizeof(varlen_attn_plan_header) / 4)) reinterpret_cast<int32_t*>(hdr)[tid] = 0;
+    if (tid < kSelfPlanDocs) kept_ends(hdr)[tid] = 0;
     __syncthreads();
     if (tid == 0) {
       hdr->status = VARLEN_ATTN_BAD_CU_SEQLENS;
@@ -406,13 +416,15 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
     }
     mode = 1;
   }
+  // The capacities are worst-case bounds (tiles <= N / 128 + B; a cut chain of n > ch steps
+  // takes ceil(n / ch) <= 2 n / ch chunks, and ch was lengthened until those fit), so this
+  // cannot fail; if it ever does, it is an error of its own and nothing is planned.
+  const bool ok = n_units[0] <= a.max_units && n_units[1] <= a.max_units &&
+                  n_comb[0] <= a.max_combine && n_comb[1] <= a.max_combine &&
+                  n_slots[0] <= a.max_slots[0] && n_slots[1] <= a.max_slots[1];
+  // (the last batch of documents, which is the only one here, still stands in LDS)
+  if (a.B <= kSelfPlanDocs && a.N <= 0xFFFF && tid < kSelfPlanDocs) kept_ends(hdr)[tid] = ok ? (uint16_t)doc_e[tid] : 0;
   if (tid == 0) {
-    // The capacities are worst-case bounds (tiles <= N / 128 + B; a cut chain of n > ch steps
-    // takes ceil(n / ch) <= 2 n / ch chunks, and ch was lengthened until those fit), so this
-    // cannot fail; if it ever does, it is an error of its own and nothing is planned.
-    const bool ok = n_units[0] <= a.max_units && n_units[1] <= a.max_units &&
-                    n_comb[0] <= a.max_combine && n_comb[1] <= a.max_combine &&
-                    n_slots[0] <= a.max_slots[0] && n_slots[1] <= a.max_slots[1];
     hdr->status = ok ? VARLEN_ATTN_OK : VARLEN_ATTN_PLAN_OVERFLOW;
     if (a.status_copy) *a.status_copy = hdr->status;
     hdr->n_row_units = ok ? n_units[0] : 0;

@@ -23,13 +23,18 @@ namespace {
 // ----------------------------------------------------------------------------------------
 constexpr int kShortRows = 32;
 
-// The u-th 32-row tile of a microbatch of at most 64 documents, worked out by a whole wave from
-// cu_seqlens; every lane gets the answer.  False: cu_seqlens is malformed or u past the last tile.
+// The u-th 32-row tile of a microbatch of at most 64 documents, worked out by a whole wave from the
+// documents that the plan kept or, while the plan is being made beside it (`planned` false), from
+// cu_seqlens; every lane gets the answer.  False: malformed, nothing planned, or u past the last tile.
 struct ShortTile { int row0, doc_start, doc_end; };
-__device__ __forceinline__ bool derive_short_tile(const int32_t* __restrict__ cu, int B, int N, int u, bool from_end,
+__device__ __forceinline__ bool derive_short_tile(const PlanArgs& plan, bool planned, int u, bool from_end,
                                                   int lane, ShortTile& out) {
+  const int B = plan.B, N = plan.N;
   int s = 0, e = 0;
-  if (lane < B) { s = cu[lane]; e = cu[lane + 1]; }
+  if (planned) {
+    const uint16_t* ends = kept_ends(plan.hdr);
+    if (lane < B) { s = lane ? ends[lane - 1] : 0; e = ends[lane]; }
+  } else if (lane < B) { s = plan.cu[lane]; e = plan.cu[lane + 1]; }
   if (__any(lane < B && e < s) || lane_value(s, 0) != 0 || lane_value(e, B - 1) != N) return false;
   const int T = (e - s + kShortRows - 1) / kShortRows;
   const int incl = wave_inclusive_sum(T);
@@ -119,7 +124,7 @@ fwd_short_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
   int unit, head;
   decode_block(blockIdx.x - plan_block, Hq, unit, head);
   ShortTile it;
-  if (!derive_short_tile(plan.cu, plan.B, N, unit, true, lane, it)) return;
+  if (!derive_short_tile(plan, !plan_block, unit, true, lane, it)) return;
   const int kvh = head / (Hq / Hkv);
   const int my_row = it.row0 + c;
   const bool row_valid = my_row < it.doc_end;
@@ -259,7 +264,7 @@ bwd_short_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
   if (bid >= kv_blocks) {
     // ---------------------------------------------------------------- dQ of 32 queries, one q head
     decode_block(bid - kv_blocks, Hq, unit, head);
-    if (!derive_short_tile(plan.cu, plan.B, N, unit, true, lane, it)) return;
+    if (!derive_short_tile(plan, true, unit, true, lane, it)) return;
     const int kvh = head / (Hq / Hkv);
     const int my_row = it.row0 + c;
     const bool row_valid = my_row < it.doc_end;
@@ -350,7 +355,7 @@ bwd_short_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
 
   // ------------------------------------------------------------------ dK, dV of 32 keys, one q head
   decode_block(bid, Hq, unit, head);
-  if (!derive_short_tile(plan.cu, plan.B, N, unit, false, lane, it)) return;
+  if (!derive_short_tile(plan, true, unit, false, lane, it)) return;
   const int kvh = head / (Hq / Hkv);
   const int my_kv = it.row0 + c;
   const bool kv_valid = my_kv < it.doc_end;
@@ -491,7 +496,7 @@ bwd_short_group_kernel(const float* __restrict__ partials, __bf16* __restrict__ 
   const int g = Hq / Hkv;
   ShortTile it;
   const float* p0 = partials + (((size_t)unit * Hq + kvh * g) * 2 + tensor) * (kShortRows * D) + threadIdx.x * 4;
-  if (!derive_short_tile(plan.cu, plan.B, plan.N, unit, false, lane, it)) return;
+  if (!derive_short_tile(plan, true, unit, false, lane, it)) return;
   f32x4 acc[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};

@@ -625,6 +625,39 @@ def test_forward_reuses_a_plan(gpu):
         assert np.array_equal(fresh[n], got[n]), n
 
 
+@pytest.mark.parametrize("lengths,hq,hkv,d", [([700, 40, 300, 5, 129], 4, 2, 128), ([90, 31, 0, 64, 200, 1], 2, 2, 64),
+                                               ([20 + i % 9 for i in range(64)], 1, 1, 128), ([700, 40, 1300, 5, 1290], 4, 4, 128)])
+@pytest.mark.parametrize("planner", ["plan", "forward", "large"])
+def test_kept_plan_outlives_cu_seqlens(gpu, planner, lengths, hq, hkv, d):
+    """Once the plan is made, forward and backward on it no longer depend on the contents of cu_seqlens,
+    which may hold the next microbatch by then: small microbatches (whose kernels take their tiles
+    from the documents) and an ordinary one give the bits of an undisturbed run."""
+    import torch
+    from paper_2605_06374_amd import binding
+    w = W.custom("kept", lengths, hq, hkv, d, seed=sum(lengths) + d)
+    flags = binding.FLAG_PLAN_LARGE if planner == "large" else 0
+    want = run_all(gpu, w, flags=flags).result_bits()
+    prob = gpu.DeviceProblem(w, flags=flags)
+    prob.poison_outputs()
+    if planner == "forward":
+        prob.forward()
+    else:
+        prob.plan()
+    other = np.concatenate([[0], np.cumsum(lengths[::-1])]).astype(np.int32)   # the same tokens, packed in another order
+    prob.cu.copy_(torch.from_numpy(other))
+    prob.forward(reuse_plan=True)
+    prob.backward(reuse_plan=True)
+    got = prob.result_bits()
+    for n in want:
+        assert np.array_equal(want[n], got[n]), n
+    # a backward that plans for itself reads the buffer as it is now
+    prob.poison_outputs()
+    prob.forward()
+    prob.backward()
+    moved = W.custom("kept", lengths[::-1], hq, hkv, d, seed=sum(lengths) + d)
+    assert_close_full(prob.results(), oracle_full(moved, w.values()), "refilled")
+
+
 def test_bwd_plans_itself_without_reuse_flag(gpu):
     from paper_2605_06374_amd import binding
     w = W.custom("noreuse", [500, 77], 2, 2, 128, seed=21)
