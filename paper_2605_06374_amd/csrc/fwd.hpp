@@ -113,7 +113,7 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
 
   // Reference m of the exponentials: any m with 2^(s - m) far from overflow gives the same O and LSE
   // up to rounding.  It is the row's maximum over the first sub-step (so that a row of one key has
-  // P = 1), and stays until the row sum of a sub-step, which is needed anyway, exceeds 2^24: only
+  // P = 1), and stays until the row sum of a sub-step, which is needed anyway, exceeds 2^8: only
   // then are the scores formed again, their maximum taken and O and the row sum rescaled.  Against
   // a maximum in every sub-step that leaves out 15 of 85 vector instructions and a chain of 17
   // dependent ones between the two contractions: 422 -> 410 us at 32768 tokens in 11 documents
@@ -173,7 +173,7 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
     if (__any(!(psum <= kRefSumMax))) {   // rare (NaN among the scores comes here as well)
       s = scores(kt);
       mask(s, kv0);
-      const float m_new = __builtin_fmaxf(m_run, row_max(s));
+      const float m_new = __builtin_fmaxf(m_run, row_max(s) + kRefRoom);
       const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
       m_run = m_new;
       l_run *= alpha;

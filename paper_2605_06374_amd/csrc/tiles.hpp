@@ -35,7 +35,13 @@ constexpr int kStep = VARLEN_ATTN_STEP_ROWS;  // rows staged per iteration of a 
 constexpr int kThreads = 256;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr float kRefSumMax = 16777216.f;  // 2^24: row sum of a sub-step above which the forward renews its reference
+// The forward renews the reference of its exponentials when the row sum of a sub-step exceeds 2^8, and
+// puts it 12 powers of two above the row's maximum.  The sum bounds P, and with it how far the
+// unnormalised O lies above O: with 2^24 in its place values |V| of 2^100 overflowed.  The room below
+// makes renewals rare where scores keep growing (forward at 32768 tokens in 11 documents, scores with
+// a standard deviation of 9: 499 us without it, 463 us with it, 450 us with a bound of 2^24 and no
+// room; up to a standard deviation of 2 all three are the same).
+constexpr float kRefSumMax = 256.f, kRefRoom = 12.f;
 
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>): a loop whose body may hold
 // scheduling fences (an ordinary loop that holds one is not unrolled).

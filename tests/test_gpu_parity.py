@@ -94,7 +94,7 @@ def test_extreme_logit_ranges(gpu, std, d):
 @pytest.mark.parametrize("first,then", [(0.02, 12.0), (12.0, 0.02), (1.0, 40.0)])
 def test_forward_renews_its_reference(gpu, first, then, d, hq, hkv):
     """The forward keeps the maximum of a chunk's first 32 keys as the reference of its exponentials
-    until a row sum exceeds 2^24.  Keys that grow by up to 600 times behind token 96 of each document
+    until a row sum exceeds 2^8, and renews it with 12 powers of two of room.  Keys that grow by up to 600 times behind token 96 of each document
     (logits of a few hundred: renewed in some rows, in later sub-steps, in later chunks) and keys
     that shrink (the reference stays far above the scores of a whole chunk): O and LSE within the
     usual bounds (bf16 rounding of P and O relative to the largest |V|, fp32 otherwise)."""
@@ -106,6 +106,33 @@ def test_forward_renews_its_reference(gpu, first, then, d, hq, hkv):
         k[min(e, s + 96):e] *= np.float32(then)
     vals["k"] = W.f32_to_bf16_bits(k)
     prob = gpu.DeviceProblem(w, values=vals)
+    prob.poison_outputs()
+    prob.forward()
+    got, ref = prob.results(), oracle_full(w, vals)
+    assert np.isfinite(got["o"]).all()
+    assert e1(got["o"], ref["o"]) <= TOL_O
+    assert (np.abs(got["lse"] - ref["lse"]) <= TOL_LSE * np.maximum(1.0, np.abs(ref["lse"]))).all()
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("chunk", [0, 3, 200])
+@pytest.mark.parametrize("exponent", [112, -112])
+def test_forward_extreme_values_behind_a_low_reference(gpu, exponent, chunk, d):
+    """|V| around 2^112 and 2^-112 and keys that grow behind token 96 of a document, so that later scores
+    exceed the reference by some 20 powers of two.  P of a key is at most 2^8, so that a sum of P V over
+    900 keys of either sign stays below 2^8 * 900^(1/2) * 2^114 < 2^127, and P of a row's largest key at
+    least 2^-12, so that P V stays above 2^-126.  O, an average of V, is finite and as precise as
+    elsewhere.  Small-microbatch kernel (0), cut chains (3) and whole chains (200) of the general one."""
+    from paper_2605_06374_amd import binding
+    w = W.custom("extreme_v", [900, 130, 64, 97, 1], 2, 1, d, seed=d)
+    vals = w.values()
+    k = W.bf16_bits_to_f32(vals["k"])
+    for s, e in zip(w.cu_seqlens[:-1], w.cu_seqlens[1:]):
+        k[s:min(e, s + 96)] *= np.float32(0.02)
+        k[min(e, s + 96):e] *= np.float32(5.0)
+    vals["k"] = W.f32_to_bf16_bits(k)
+    vals["v"] = W.f32_to_bf16_bits(W.bf16_bits_to_f32(vals["v"]) * np.float32(2.0 ** exponent))
+    prob = gpu.DeviceProblem(w, values=vals, flags=binding.flag_chunk_steps(chunk, chunk))
     prob.poison_outputs()
     prob.forward()
     got, ref = prob.results(), oracle_full(w, vals)
