@@ -32,8 +32,9 @@ __device__ __forceinline__ bool derive_short_tile(const PlanArgs& plan, bool pla
   const int B = plan.B, N = plan.N;
   int s = 0, e = 0;
   if (planned) {
-    const uint16_t* ends = kept_ends(plan.hdr);
-    if (lane < B) { s = lane ? ends[lane - 1] : 0; e = ends[lane]; }
+    if (lane < B) e = kept_ends(plan.hdr)[lane];
+    s = __builtin_amdgcn_update_dpp(0, e, 0x138, 0xF, 0xF, true);   // wave_shr:1, 0 into lane 0
+    if (lane >= B) s = 0;
   } else if (lane < B) { s = plan.cu[lane]; e = plan.cu[lane + 1]; }
   if (__any(lane < B && e < s) || lane_value(s, 0) != 0 || lane_value(e, B - 1) != N) return false;
   const int T = (e - s + kShortRows - 1) / kShortRows;
