@@ -172,7 +172,9 @@ typedef struct {
   size_t col_units_offset;
   size_t row_combine_offset;
   size_t col_combine_offset;
-  size_t dsum_offset;         /* fp32 -D = -rowsum(dO * O) [Hq, N], then -LSE / softmax_scale [Hq, N] */
+  size_t dsum_offset;         /* working store of the backward: fp32 -D = -rowsum(dO * O) [Hq, N], then
+                                 -LSE / softmax_scale [Hq, N] (scale * 2^32 for scales below
+                                 2^-120); microbatches that take one launch leave it alone */
   size_t row_partials_offset; /* fp32 partial results of cut row chains */
   size_t col_partials_offset; /* fp32 partial results of cut / grouped column chains */
   size_t dq_accumulator_offset; /* fp32 dQ accumulator [N, Hq, d]; present (non-empty) only with

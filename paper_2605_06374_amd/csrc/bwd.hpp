@@ -106,7 +106,7 @@ bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   // the unit that starts the chain publishes -D and -LSE / scale for the dK/dV kernel
   if (it.step_begin == 0 && row_valid && h == 0) {
     neg_dsum[(size_t)head * N + my_row] = -dsum_row;
-    neg_lse[(size_t)head * N + my_row] = -lse_row / scale;
+    neg_lse[(size_t)head * N + my_row] = -lse_row / folded_scale(scale);
   }
   FragOffsets<D> fo;
   fo.init(lane);
@@ -236,7 +236,7 @@ bwd_prep_kernel(const __bf16* __restrict__ o, const __bf16* __restrict__ d_o,
   if (part == 0 && valid) {
     const int t = (int)(row / Hq), h = (int)(row % Hq);
     neg_dsum[(size_t)h * N + t] = -acc;
-    neg_lse[(size_t)h * N + t] = -lse[(size_t)h * N + t] / scale;
+    neg_lse[(size_t)h * N + t] = -lse[(size_t)h * N + t] / folded_scale(scale);
   }
 }
 
@@ -407,7 +407,7 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   if (unit_idx >= n_units) return;
   const int kvh = head / (Hq / Hkv);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, c = lane & 31;
-  const float cs = scale * kLog2e;
+  const float cs = folded_scale(scale) * kLog2e;
 
   // from the thread index, not from the scalar `wave`: the branches between the two forms of a stage
   // then stay exec-masked, one behind the other, and the accumulators keep their registers; as scalar
@@ -462,6 +462,12 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   const size_t kv_off = ((size_t)min(my_kv, it.doc_end - 1) * Hkv + kvh) * D;
   load_row_frags<D>(k + kv_off, h, kf);
   load_row_frags<D>(v + kv_off, h, vf);
+  if (score_fold(scale) != 1.0f) {
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) kf[kk][e] = (__bf16)((float)kf[kk][e] * score_fold(scale));
+  }
   if (FUSED && !kv_valid) {   // rows past the document end must not enter dQ; elsewhere they are never stored
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) kf[kk] = vf[kk] = __builtin_bit_cast(bf16x8, uint4{0, 0, 0, 0});

@@ -43,6 +43,12 @@ constexpr float kLn2 = 0.6931471805599453f;
 // room; up to a standard deviation of 2 all three are the same).
 constexpr float kRefSumMax = 256.f, kRefRoom = 12.f;
 
+// dK / dV: the matrix instructions of S start from -LSE / scale, which overflows for scales below LSE / 2^128.
+// Below 2^-120 the K fragments of S are therefore multiplied by 2^-32 and the scale that S and -LSE are
+// counted in is 2^32 times larger; what K loses at the bottom of its range is below 2^-86 of a score.
+__device__ __forceinline__ float score_fold(float scale) { return scale < 0x1p-120f ? 0x1p-32f : 1.0f; }
+__device__ __forceinline__ float folded_scale(float scale) { return scale < 0x1p-120f ? scale * 0x1p32f : scale; }
+
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>): a loop whose body may hold
 // scheduling fences (an ordinary loop that holds one is not unrolled).
 template <typename F, int... I>

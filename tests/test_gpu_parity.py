@@ -141,6 +141,25 @@ def test_forward_extreme_values_behind_a_low_reference(gpu, exponent, chunk, d):
     assert (np.abs(got["lse"] - ref["lse"]) <= TOL_LSE * np.maximum(1.0, np.abs(ref["lse"]))).all()
 
 
+@pytest.mark.parametrize("d,hq,hkv", [(128, 2, 2), (128, 4, 2), (64, 2, 1)])
+@pytest.mark.parametrize("scale,magnitude", [(2.0 ** -126, 2.0 ** 60.5), (2.0 ** -121, 2.0 ** 58.5), (2.0 ** -119, 2.0 ** 57.5)])
+@pytest.mark.parametrize("mode", ["small", "cut", "whole", "fused"])
+def test_tiny_softmax_scales(gpu, mode, scale, magnitude, d, hq, hkv):
+    """Scales down to the smallest normal number, with Q and K as large as it takes for ordinary
+    logits: LSE / scale is beyond the range of fp32 there, and P must not vanish from dK and dV.
+    Usual tolerances: the call differs from an ordinary one by factors of Q, K and the scale alone."""
+    from paper_2605_06374_amd import binding
+    w = W.custom("tiny_scale", [700, 130, 64, 97, 1], hq, hkv, d, seed=d + hq)
+    w.__class__ = type("WS", (W.Workload,), {"softmax_scale": property(lambda self: scale)})
+    vals = w.values()
+    for n in ("q", "k"):
+        vals[n] = W.f32_to_bf16_bits(W.bf16_bits_to_f32(vals[n]) * np.float32(magnitude))
+    flags = {"small": 0, "cut": binding.flag_chunk_steps(3, 3), "whole": binding.flag_chunk_steps(200, 200),
+             "fused": binding.flag_chunk_steps(5, 5) | binding.FLAG_FUSED_BWD}[mode]
+    prob = run_all(gpu, w, values=vals, flags=flags)
+    assert_close_full(prob.results(), oracle_full(w, vals), f"scale {scale} {mode}")
+
+
 def test_config1_tiny_full(gpu):
     w = W.config(1)
     prob = run_all(gpu, w)
