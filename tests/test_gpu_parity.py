@@ -537,10 +537,11 @@ def test_self_planned_forward_equals_planned_forward(gpu, lengths, hq, hkv, d):
 @pytest.mark.parametrize("lengths,hq,hkv,d", [([1500, 20, 0, 700, 129, 1], 22, 11, 64),   # 528 (tile, head) pairs: just above one round
                                                ([128 * i for i in range(1, 9)], 16, 4, 128),   # chains of every length, no remainder
                                                ([5982, 1], 32, 32, 64), ([6144], 32, 8, 128),   # exactly three rounds; one tile more: behind a plan launch
-                                               ([1, 31000, 900], 4, 4, 128), ([64] * 63 + [2000], 8, 4, 64)])
+                                               ([1, 31000, 900], 4, 4, 128), ([64] * 63 + [2000], 8, 4, 64),
+                                               ([19] * 40, 32, 32, 128), ([256, 1, 255] * 9, 32, 32, 64)])   # no chunk longer than 4 steps: tile order again
 def test_self_planned_units_longest_first(gpu, lengths, hq, hkv, d, no_split):
-    """Above one round of workgroups the forward workgroups take their own units longest first: every
-    unit is taken once, with the slots of the plan, hence the bits of a forward behind a plan launch
+    """Above one round of workgroups the forward workgroups take their own units longest first (in tile
+    order if all are short): every unit is taken once, with the slots of the plan, hence the bits of a forward behind a plan launch
     (a unit left out leaves the poison, or a partial result of the other run)."""
     from paper_2605_06374_amd import binding
     w = W.custom("longest", lengths, hq, hkv, d, seed=sum(lengths) + hq)
