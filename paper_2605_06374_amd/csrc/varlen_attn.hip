@@ -227,21 +227,29 @@ inline bool self_planned_forward(const varlen_attn_params* p) {
 }
 
 // ... and the smallest microbatches take the kernels of short.hpp, forward and backward apart.  Their
-// time follows the number of 32-row tiles (one workgroup each) and the longest document, which the
-// host does not know: one document of N tokens is the worst case, N / B the usual one.  Measured
-// against the chunked kernels over 260 .. 3000 tokens, 1 .. 32 heads, one document, four, and a
-// log-normal mix (time before / time here): at head size 128 forward 1.87 .. 1.1 up to 14000 rows
-// (tokens x q heads), 0.9 .. 0.6 above 18000; backward 2.9 .. 1.1 up to 12000 rows, 0.95 .. 0.6 above
-// 16000, with grouped queries 2.1 .. 1.1 up to 9000; at head size 64 up to 30000 and 20000.  One document on one
-// head crosses 1 between 1500 and 2000 tokens (2000 and 2500 at head size 64), four documents
-// between 2500 and 3000.
+// time follows the number of 32-row tiles (one workgroup each), hence the bound on rows (tokens x q
+// heads), and the longest document, whose chain one workgroup walks alone.  The host does not know that
+// length, so the bound on tokens is low enough for packs of which one document holds half to all of the
+// tokens; it grows with the heads, because with few of them most of the GPU idles behind that document.
+// Over 3300 such packs of 1000 to 10000 tokens, 2 to 64 documents, 1 to 16 q heads, the chunked kernels
+// take at least 0.86 times as long as these inside the bounds (0.53 to 0.8 times beyond them: 10000
+// tokens, most of them in one document, on one head).  Packs of ordinary documents (log-normal, 360 of
+// them) gain 0.98 to 1.8 forward and 1.02 to 2.9 backward inside, which is why the bounds are not lower.
 inline bool short_path(const varlen_attn_params* p, bool backward) {
-  const bool wide = p->head_dim == 128;
-  const int max_rows = !backward ? (wide ? 14000 : 30000)
-                                 : !wide ? 20000 : p->num_q_heads > p->num_kv_heads ? 9000 : 12000;
-  const long long max_tokens = (wide ? 1536 : 2048) + 384ll * (p->num_docs - 1);
+  const bool wide = p->head_dim == 128, grouped = p->num_q_heads > p->num_kv_heads;
+  const long long heads = p->num_q_heads;
+  long long max_rows, max_tokens;
+  if (!backward) {
+    max_rows = wide ? 13000 : 30000;
+    max_tokens = wide ? std::min(1024 + 1536 * heads, 3840ll) : 2048 + 3072 * heads;
+  } else {
+    max_rows = wide ? (grouped ? 8500 : 10000) : (grouped ? 18000 : 20000);
+    max_tokens = wide ? (grouped ? 768 : 1280) + 512 * heads : 1536 + (grouped ? 384 : 512) * heads;
+  }
+  // few documents: one of them holds most of the tokens
+  max_tokens = std::min(max_tokens, (wide ? 1536 : 2048) + 384ll * (p->num_docs - 1));
   return !(p->flags & VARLEN_ATTN_FLAG_NO_SPLIT) && (p->flags >> 8) == 0 && p->num_docs <= kSelfPlanDocs &&
-         p->total_tokens <= max_tokens && (long long)p->total_tokens * p->num_q_heads <= max_rows;
+         p->total_tokens <= max_tokens && p->total_tokens * heads <= max_rows;
 }
 
 int launch_plan(const varlen_attn_params* p, const int32_t* cu, const Regions& R,

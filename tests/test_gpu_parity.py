@@ -642,6 +642,7 @@ SHORT_EDGES = [([1], 1, 1, 128), ([31, 32, 33], 2, 2, 128), ([95, 1, 96, 97], 1,
                ([127, 128, 129, 130, 0, 2], 4, 4, 128), ([20 + i % 9 for i in range(64)], 2, 2, 128),   # as many documents as it takes
                ([1536], 1, 1, 128), ([1537], 1, 1, 128),                                    # the longest single document, and one token more
                ([2048], 2, 1, 64), ([700, 820], 8, 8, 128), ([300, 825], 8, 2, 128),        # near the row limits
+               ([700, 550], 8, 8, 128), ([300, 762], 8, 2, 128), ([900] + [40] * 40, 1, 1, 128), ([1500] + [100] * 36, 1, 1, 64),
                ([160, 3, 97], 32, 8, 128), ([33, 400], 12, 4, 64)]
 
 
@@ -655,6 +656,29 @@ def test_small_microbatches_both_ways(gpu, lengths, hq, hkv, d, general):
     w = W.custom("short", lengths, hq, hkv, d, seed=sum(lengths) + hq + d)
     prob = run_all(gpu, w, flags=binding.flag_chunk_steps(5, 9) if general else 0)
     assert_close_full(prob.results(), oracle_full(w), label=f"short {lengths[:6]} general={general}")
+
+
+def launched(call):
+    """Names of the library's kernels that `call` launches."""
+    from paper_2605_06374_amd import binding
+    binding.varlen_attn_profile(True)
+    try:
+        call()
+        return set(binding.varlen_attn_profile_read())
+    finally:
+        binding.varlen_attn_profile(False)
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,d,short", [
+    ([100, 900, 40], 2, 2, 128, True), ([500] * 3, 1, 1, 64, True), ([250] * 8, 2, 1, 64, True),
+    # most of the tokens in one document among many: one workgroup would walk its chain alone
+    ([133] * 8 + [5000] + [133] * 7, 2, 2, 128, False), ([11000] + [30] * 29, 1, 1, 128, False),
+    ([20] * 20 + [6500] + [20] * 20, 1, 1, 64, False), ([9] * 30 + [4800], 2, 1, 128, False)])
+def test_long_chains_go_to_the_chunked_kernels(gpu, lengths, hq, hkv, d, short):
+    w = W.custom("route", lengths, hq, hkv, d, seed=sum(lengths))
+    prob = gpu.DeviceProblem(w)
+    assert ("fwd_short_kernel" if short else "fwd_kernel") in launched(prob.forward)
+    assert ("bwd_short_kernel" if short else "bwd_dkv_kernel") in launched(lambda: prob.backward(reuse_plan=True))
 
 
 def test_forward_reuses_a_plan(gpu):
