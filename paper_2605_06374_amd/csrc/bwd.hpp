@@ -462,7 +462,7 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
   const size_t kv_off = ((size_t)min(my_kv, it.doc_end - 1) * Hkv + kvh) * D;
   load_row_frags<D>(k + kv_off, h, kf);
   load_row_frags<D>(v + kv_off, h, vf);
-  if (score_fold(scale) != 1.0f) {
+  if (__builtin_expect(score_fold(scale) != 1.0f, 0)) {   // out of line: jumping over it took 0.3 us
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk)
 #pragma unroll

@@ -239,7 +239,9 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
     int my_bad = 0, my_tiles = 0, my_max = 0;
 #pragma unroll 1
     for (int b = tid; b < a.B; b += kPlanThreads) {
-      const long long l = (long long)cu[b + 1] - cu[b];
+      const int end = cu[b + 1];
+      const long long l = (long long)end - cu[b];
+      if (a.B <= kSelfPlanDocs && a.N <= 0xFFFF) kept_ends(a.hdr)[b] = (uint16_t)end;   // by thread b, which may take it back
       if (l < 0) { my_bad = 1; continue; }
       my_pairs += (unsigned long long)(l * (l + 1) / 2);
       const long long T = (l + kTile - 1) / kTile, S = (l + kStep - 1) / kStep;
@@ -429,8 +431,7 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
   const bool ok = n_units[0] <= a.max_units && n_units[1] <= a.max_units &&
                   n_comb[0] <= a.max_combine && n_comb[1] <= a.max_combine &&
                   n_slots[0] <= a.max_slots[0] && n_slots[1] <= a.max_slots[1];
-  // (the last batch of documents, which is the only one here, still stands in LDS)
-  if (a.B <= kSelfPlanDocs && a.N <= 0xFFFF && tid < kSelfPlanDocs) kept_ends(hdr)[tid] = ok ? (uint16_t)doc_e[tid] : 0;
+  if (!ok && tid < kSelfPlanDocs) kept_ends(hdr)[tid] = 0;
   if (tid == 0) {
     hdr->status = ok ? VARLEN_ATTN_OK : VARLEN_ATTN_PLAN_OVERFLOW;
     if (a.status_copy) *a.status_copy = hdr->status;
