@@ -47,7 +47,8 @@ extern "C" {
  *                             step s holding queries row0 + 64 s .. + 63.
  * A long chain is cut into chunks of nearly equal length so that a short microbatch still
  * fills the GPU; each chunk is one work unit, and the partial results of a cut chain are
- * summed afterwards in a fixed order (deterministic). */
+ * summed afterwards in a fixed order (deterministic).  Small microbatches (a few thousand tokens on few
+ * heads) have the same plan but are computed in 32-row tiles whose chains one workgroup walks. */
 #define VARLEN_ATTN_TILE_ROWS 128
 #define VARLEN_ATTN_STEP_ROWS 64
 
@@ -98,9 +99,12 @@ extern "C" {
                                          reproducible) take those whether it is given or not. */
 #define VARLEN_ATTN_FLAG_PLAN_FIRST 32 /* testing: the plan in a launch of its own in front of the forward
                                          also on small microbatches (by default, with at most 64
-                                         documents and 256 tiles, the forward workgroups work out
-                                         their own units from cu_seqlens and the plan is made beside
-                                         them, inside the forward launch) */
+                                         documents, 256 tiles and 1536 (tile, head) pairs, the
+                                         forward workgroups work out their own units from cu_seqlens
+                                         and the plan is made beside them, inside the forward
+                                         launch) */
+#define VARLEN_ATTN_FLAG_GENERAL 64 /* testing: the chunked kernels of the plan also on microbatches that
+                                         are small enough for the small-microbatch kernels */
 #define VARLEN_ATTN_FLAG_PLAN_LARGE 8 /* testing: plan with the general (16-wave) form of the plan kernel
                                          also where the single-wave form would be taken */
 

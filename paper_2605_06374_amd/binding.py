@@ -31,6 +31,7 @@ FLAG_NO_SPLIT = 2
 FLAG_PLAN_LARGE = 8
 FLAG_FUSED_BWD = 16
 FLAG_PLAN_FIRST = 32
+FLAG_GENERAL = 64
 
 
 def flag_group_heads(n: int) -> int:

@@ -248,7 +248,7 @@ inline bool short_path(const varlen_attn_params* p, bool backward) {
   }
   // few documents: one of them holds most of the tokens
   max_tokens = std::min(max_tokens, (wide ? 1536 : 2048) + 384ll * (p->num_docs - 1));
-  return !(p->flags & VARLEN_ATTN_FLAG_NO_SPLIT) && (p->flags >> 8) == 0 && p->num_docs <= kSelfPlanDocs &&
+  return !(p->flags & (VARLEN_ATTN_FLAG_NO_SPLIT | VARLEN_ATTN_FLAG_GENERAL)) && (p->flags >> 8) == 0 && p->num_docs <= kSelfPlanDocs &&
          p->total_tokens <= max_tokens && p->total_tokens * heads <= max_rows;
 }
 

@@ -23,15 +23,42 @@ def gpu():
     return runner
 
 
+def launched(call):
+    """Names of the library's kernels that `call` launches."""
+    from paper_2605_06374_amd import binding
+    binding.varlen_attn_profile(True)
+    try:
+        call()
+        return set(binding.varlen_attn_profile_read())
+    finally:
+        binding.varlen_attn_profile(False)
+
+
 def run_all(gpu, w, values=None, poison=True, flags=0):
     from paper_2605_06374_amd import binding
     prob = gpu.DeviceProblem(w, values=values, flags=flags)
     if poison:
         prob.poison_outputs()
-    prob.forward()
-    prob.backward(reuse_plan=True)
+
+    def step():
+        prob.forward()
+        prob.backward(reuse_plan=True)
+    names = launched(step)
+    if flags & (binding.FLAG_GENERAL | binding.FLAG_NO_SPLIT) or flags >> 8:
+        assert {"fwd_kernel", "bwd_fused_kernel" if flags & binding.FLAG_FUSED_BWD else "bwd_dkv_kernel"} <= names
+        assert not [n for n in names if "short" in n], names
     assert binding.varlen_attn_check(prob.workspace) == binding.OK
     return prob
+
+
+# most shapes small enough for a test are small enough for the small-microbatch kernels: tests of what the
+# chunked kernels do run a second time on those
+BOTH_ROUTES = pytest.mark.parametrize("general", [False, True])
+
+
+def route(general):
+    from paper_2605_06374_amd import binding
+    return binding.FLAG_GENERAL if general else 0
 
 
 SMALL = [
@@ -57,29 +84,32 @@ SMALL = [
 ]
 
 
+@BOTH_ROUTES
 @pytest.mark.parametrize("lengths,hq,hkv,d", SMALL)
-def test_small_shapes_full_parity(gpu, lengths, hq, hkv, d):
+def test_small_shapes_full_parity(gpu, lengths, hq, hkv, d, general):
     print(f"case lengths={lengths[:8]} hq={hq} hkv={hkv} d={d}", flush=True)
     w = W.custom("small", lengths, hq, hkv, d, seed=sum(lengths) + 13 * hq + d)
-    prob = run_all(gpu, w)
+    prob = run_all(gpu, w, flags=route(general))
     errs = assert_close_full(prob.results(), oracle_full(w), label=str(lengths[:6]))
     print("  errors (E1, row-wise):", {k: (f"{a:.2e}", f"{b:.2e}") for k, (a, b) in errs.items()}, flush=True)
 
 
-def test_non_default_scale_and_std(gpu):
+@BOTH_ROUTES
+def test_non_default_scale_and_std(gpu, general):
     w = W.custom("scaled", [300, 45, 700], 4, 2, 128, std=0.5, seed=5)
     w.__class__ = type("WS", (W.Workload,), {"softmax_scale": property(lambda self: 0.21)})
-    prob = run_all(gpu, w)
+    prob = run_all(gpu, w, flags=route(general))
     assert_close_full(prob.results(), oracle_full(w), "scale 0.21")
 
 
+@BOTH_ROUTES
 @pytest.mark.parametrize("std,d", [(4.0, 128), (3.0, 64), (0.01, 128)])
-def test_extreme_logit_ranges(gpu, std, d):
+def test_extreme_logit_ranges(gpu, std, d, general):
     """Values four times larger give logits with a standard deviation of 16 (nearly one-hot
     rows, the running max rises by far more than the lazy-rescale margin many times over);
     tiny values give nearly uniform rows.  Both across cut chains."""
     w = W.custom("logits", [900, 130, 1500], 2, 1, d, std=std, seed=int(std * 100) + d)
-    prob = run_all(gpu, w)
+    prob = run_all(gpu, w, flags=route(general))
     got = prob.results()
     for name in ("o", "lse", "dq", "dk", "dv"):
         assert np.isfinite(got[name]).all(), name
@@ -92,12 +122,19 @@ def test_extreme_logit_ranges(gpu, std, d):
 
 @pytest.mark.parametrize("d,hq,hkv", [(128, 2, 1), (64, 4, 4)])
 @pytest.mark.parametrize("first,then", [(0.02, 12.0), (12.0, 0.02), (1.0, 40.0)])
-def test_forward_renews_its_reference(gpu, first, then, d, hq, hkv):
+@pytest.mark.parametrize("chunk", ["small", "plan", 3, 200])
+def test_forward_renews_its_reference(gpu, chunk, first, then, d, hq, hkv):
     """The forward keeps the maximum of a chunk's first 32 keys as the reference of its exponentials
     until a row sum exceeds 2^8, and renews it with 12 powers of two of room.  Keys that grow by up to 600 times behind token 96 of each document
     (logits of a few hundred: renewed in some rows, in later sub-steps, in later chunks) and keys
     that shrink (the reference stays far above the scores of a whole chunk): O and LSE within the
-    usual bounds (bf16 rounding of P and O relative to the largest |V|, fp32 otherwise)."""
+    usual bounds (bf16 rounding of P and O relative to the largest |V|, fp32 otherwise).  Chunks as the
+    plan cuts them, short ones (renewed and other references meet in the reduction) and whole chains;
+    the small-microbatch kernel, which takes a maximum per block, on the same values."""
+    from paper_2605_06374_amd import binding
+    flags = {"small": 0, "plan": binding.FLAG_GENERAL}.get(chunk)
+    if flags is None:
+        flags = binding.flag_chunk_steps(chunk, chunk)
     w = W.custom("renew", [900, 130, 64, 97, 1], hq, hkv, d, seed=d + hq)
     vals = w.values()
     k = W.bf16_bits_to_f32(vals["k"])
@@ -105,9 +142,9 @@ def test_forward_renews_its_reference(gpu, first, then, d, hq, hkv):
         k[s:min(e, s + 96)] *= np.float32(first)
         k[min(e, s + 96):e] *= np.float32(then)
     vals["k"] = W.f32_to_bf16_bits(k)
-    prob = gpu.DeviceProblem(w, values=vals)
+    prob = gpu.DeviceProblem(w, values=vals, flags=flags)
     prob.poison_outputs()
-    prob.forward()
+    assert ("fwd_short_kernel" if chunk == "small" else "fwd_kernel") in launched(prob.forward)
     got, ref = prob.results(), oracle_full(w, vals)
     assert np.isfinite(got["o"]).all()
     assert e1(got["o"], ref["o"]) <= TOL_O
@@ -346,12 +383,13 @@ def test_plan_single_long_document_and_gqa(gpu):
         _check_plan(prob, w, False)
 
 
-def test_bad_cu_seqlens_is_reported_and_writes_nothing(gpu):
+@BOTH_ROUTES
+def test_bad_cu_seqlens_is_reported_and_writes_nothing(gpu, general):
     import torch
     from paper_2605_06374_amd import binding
     w = W.custom("bad", [100, 200, 84], 2, 2, 128, seed=3)
     for bad in ([0, 250, 200, 384], [1, 100, 300, 384], [0, 100, 300, 383]):
-        prob = gpu.DeviceProblem(w)
+        prob = gpu.DeviceProblem(w, flags=route(general))
         prob.cu.copy_(torch.tensor(bad, dtype=torch.int32))
         prob.poison_outputs()
         prob.forward()
@@ -381,12 +419,13 @@ def test_first_row_identity(gpu):
             assert np.abs(got["dq"][t, h]).max() <= 1e-5 * w.softmax_scale * np.abs(v64["k"][t]).max() * 10
 
 
-def test_isolation_bit_exact(gpu):
+@BOTH_ROUTES
+def test_isolation_bit_exact(gpu, general):
     """Poisoning every token outside a document (NaN, Inf, huge) leaves that document's
     outputs bit-identical: nothing outside [cu[b], cu[b+1]) is ever read for it."""
     w = W.custom("iso", [300, 130, 1, 700, 64], 4, 2, 128, seed=9)
     vals = w.values()
-    base = run_all(gpu, w).result_bits()
+    base = run_all(gpu, w, flags=route(general)).result_bits()
     cu = w.cu_seqlens
     for b in (0, 1, 2, 3):
         s, e = int(cu[b]), int(cu[b + 1])
@@ -396,7 +435,7 @@ def test_isolation_bit_exact(gpu):
             y[:s] = 0x7FC0 if n != "k" else 0x7F80     # NaN, and +Inf in K
             y[e:] = 0x7FC0 if n != "v" else 0x7E00     # NaN, and huge in V
             poisoned[n] = y
-        got = run_all(gpu, w, values=poisoned).result_bits()
+        got = run_all(gpu, w, values=poisoned, flags=route(general)).result_bits()
         for n in ("o", "dq", "dk", "dv"):
             assert np.array_equal(got[n][s:e], base[n][s:e]), (b, n)
         assert np.array_equal(got["lse"][:, s:e], base["lse"][:, s:e])
@@ -469,17 +508,19 @@ def test_grouped_query_column_units_sweeping_heads(gpu, heads):
         assert_close_full(prob.results(), oracle_full(w), f"gqa sweep {heads} {lengths}")
 
 
-@pytest.mark.parametrize("lengths,hq,hkv,d", SMALL + [([900, 130, 1500, 64, 1], 8, 2, 128)])
-def test_fused_backward_small_shapes(gpu, lengths, hq, hkv, d):
+@BOTH_ROUTES
+@pytest.mark.parametrize("lengths,hq,hkv,d", SMALL + [([900, 130, 1500, 64, 1], 8, 2, 128), ([900, 130, 1500, 64, 1], 4, 4, 64)])
+def test_fused_backward_small_shapes(gpu, lengths, hq, hkv, d, general):
     """The single-kernel backward (dQ by fp32 atomics): same oracle, same tolerances; dV is
     computed by the same arithmetic as in the two-kernel form, hence bit-identical to it (dK is
-    not: D = rowsum(dO * O) is summed by another kernel, in another order)."""
+    not: D = rowsum(dO * O) is summed by another kernel, in another order).  Microbatches that take
+    the small-microbatch kernels do so with the flag as well."""
     from paper_2605_06374_amd import binding
     print(f"fused case lengths={lengths[:8]} hq={hq} hkv={hkv} d={d}", flush=True)
     w = W.custom("fused", lengths, hq, hkv, d, seed=sum(lengths) + 13 * hq + d)
-    prob = run_all(gpu, w, flags=binding.FLAG_FUSED_BWD)
+    prob = run_all(gpu, w, flags=binding.FLAG_FUSED_BWD | route(general))
     assert_close_full(prob.results(), oracle_full(w), label="fused " + str(lengths[:6]))
-    base, got = run_all(gpu, w).result_bits(), prob.result_bits()
+    base, got = run_all(gpu, w, flags=route(general)).result_bits(), prob.result_bits()
     for n in ("o", "lse", "dv"):
         assert np.array_equal(got[n], base[n]), n
 
@@ -507,20 +548,21 @@ def test_bit_reproducible(gpu):
         assert np.array_equal(a[n], b[n]), n
 
 
+@BOTH_ROUTES
 @pytest.mark.parametrize("lengths,hq,hkv,d", [SMALL[3], SMALL[6], SMALL[7], SMALL[10], SMALL[11], SMALL[13],
                                                ([900, 130, 1500, 64, 1, 0, 700], 4, 2, 128),
                                                ([8192], 2, 2, 64), ([3] * 64, 2, 1, 128),
                                                ([16384 + 77], 1, 1, 128),
                                                ([31000, 1, 900], 2, 2, 64),          # 251 tiles: four rounds of 64
                                                ([0, 5, 0, 0, 300, 0] + [1, 130, 64, 0] * 14 + [0, 0], 3, 1, 128)])
-def test_self_planned_forward_equals_planned_forward(gpu, lengths, hq, hkv, d):
+def test_self_planned_forward_equals_planned_forward(gpu, lengths, hq, hkv, d, general):
     """On small microbatches the forward workgroups work out their units themselves while one of
     them writes the plan: same units, same slots, hence the bits of a forward behind a plan
     launch, and the same plan tables (the reduction's items in any order)."""
     from paper_2605_06374_amd import binding
     w = W.custom("self", lengths, hq, hkv, d, seed=sum(lengths) + 7 * hq + d)
-    a = run_all(gpu, w, flags=binding.FLAG_PLAN_FIRST)
-    b = run_all(gpu, w)
+    a = run_all(gpu, w, flags=binding.FLAG_PLAN_FIRST | route(general))
+    b = run_all(gpu, w, flags=route(general))
     abits, bbits = a.result_bits(), b.result_bits()
     for n in abits:
         assert np.array_equal(abits[n], bbits[n]), n
@@ -583,7 +625,8 @@ def _random_shape(rng, kind):
 def test_random_shapes_full_parity(gpu):
     """Sixty seeded random microbatches (six length mixes, twelve head layouts, both head sizes,
     the default and four other modes), each against the oracle in full; in the modes where the
-    forward may plan itself also bit by bit against the forward behind a plan launch."""
+    forward may plan itself also bit by bit against the forward behind a plan launch.  Those that
+    the small-microbatch kernels take run on the chunked ones as well."""
     from paper_2605_06374_amd import binding
     heads = [(1, 1), (2, 1), (2, 2), (4, 4), (4, 2), (8, 2), (8, 8), (6, 3), (3, 3), (16, 2), (5, 1), (12, 4)]
     for case in range(60):
@@ -596,13 +639,15 @@ def test_random_shapes_full_parity(gpu):
         label = f"random case {case}: B={len(lengths)} N={sum(lengths)} hq={hq} hkv={hkv} d={d} flags={flags:#x}"
         print(label, flush=True)
         w = W.custom("random", lengths, hq, hkv, d, seed=case)
-        prob = run_all(gpu, w, flags=flags)
-        assert_close_full(prob.results(), oracle_full(w), label)
-        if not flags & binding.FLAG_PLAN_FIRST:
-            first = run_all(gpu, w, flags=flags | binding.FLAG_PLAN_FIRST).result_bits()
-            got = prob.result_bits()
-            for n in ("o", "lse"):
-                assert np.array_equal(first[n], got[n]), f"{label}: {n}"
+        ref = oracle_full(w)
+        for extra in (0, binding.FLAG_GENERAL):
+            prob = run_all(gpu, w, flags=flags | extra)
+            assert_close_full(prob.results(), ref, f"{label} general={bool(extra)}")
+            if not flags & binding.FLAG_PLAN_FIRST:
+                first = run_all(gpu, w, flags=flags | extra | binding.FLAG_PLAN_FIRST).result_bits()
+                got = prob.result_bits()
+                for n in ("o", "lse"):
+                    assert np.array_equal(first[n], got[n]), f"{label}: {n}"
 
 
 def test_random_larger_shapes_sampled(gpu):
@@ -651,22 +696,11 @@ SHORT_EDGES = [([1], 1, 1, 128), ([31, 32, 33], 2, 2, 128), ([95, 1, 96, 97], 1,
 def test_small_microbatches_both_ways(gpu, lengths, hq, hkv, d, general):
     """Small microbatches go through kernels of their own (32-row tiles whose chain the four waves
     of a workgroup share, dQ and dK / dV in one launch); given chunk lengths send the same
-    microbatches through the general kernels.  Both against the oracle in full."""
+    microbatches through the chunked kernels.  Both against the oracle in full."""
     from paper_2605_06374_amd import binding
     w = W.custom("short", lengths, hq, hkv, d, seed=sum(lengths) + hq + d)
     prob = run_all(gpu, w, flags=binding.flag_chunk_steps(5, 9) if general else 0)
     assert_close_full(prob.results(), oracle_full(w), label=f"short {lengths[:6]} general={general}")
-
-
-def launched(call):
-    """Names of the library's kernels that `call` launches."""
-    from paper_2605_06374_amd import binding
-    binding.varlen_attn_profile(True)
-    try:
-        call()
-        return set(binding.varlen_attn_profile_read())
-    finally:
-        binding.varlen_attn_profile(False)
 
 
 @pytest.mark.parametrize("lengths,hq,hkv,d,short", [
@@ -681,12 +715,13 @@ def test_long_chains_go_to_the_chunked_kernels(gpu, lengths, hq, hkv, d, short):
     assert ("bwd_short_kernel" if short else "bwd_dkv_kernel") in launched(lambda: prob.backward(reuse_plan=True))
 
 
-def test_forward_reuses_a_plan(gpu):
+@BOTH_ROUTES
+def test_forward_reuses_a_plan(gpu, general):
     """One plan for the attention calls of all layers of a micro-batch: a forward that reuses the
     plan of varlen_attn_plan gives the bits of a forward that plans itself."""
     w = W.custom("layers", [700, 40, 1300, 5, 129], 4, 2, 128, seed=31)
-    fresh = run_all(gpu, w).result_bits()
-    prob = gpu.DeviceProblem(w)
+    fresh = run_all(gpu, w, flags=route(general)).result_bits()
+    prob = gpu.DeviceProblem(w, flags=route(general))
     prob.poison_outputs()
     prob.plan()
     prob.forward(reuse_plan=True)
@@ -729,10 +764,11 @@ def test_kept_plan_outlives_cu_seqlens(gpu, planner, lengths, hq, hkv, d):
     assert_close_full(prob.results(), oracle_full(moved, w.values()), "refilled")
 
 
-def test_bwd_plans_itself_without_reuse_flag(gpu):
+@BOTH_ROUTES
+def test_bwd_plans_itself_without_reuse_flag(gpu, general):
     from paper_2605_06374_amd import binding
     w = W.custom("noreuse", [500, 77], 2, 2, 128, seed=21)
-    prob = gpu.DeviceProblem(w)
+    prob = gpu.DeviceProblem(w, flags=route(general))
     prob.poison_outputs()
     prob.forward()
     prob.workspace.zero_()          # wipe the plan: bwd must rebuild it
@@ -749,15 +785,16 @@ def test_cost_follows_sum_of_squares_not_n_squared(gpu):
     assert 3.5 < a / b < 4.0
 
 
-def test_hip_graph_replays_match_eager(gpu):
+@BOTH_ROUTES
+def test_hip_graph_replays_match_eager(gpu, general):
     """fwd + bwd enqueue kernels only (no allocation, no synchronisation, no memset nodes), so
     a caller may capture them in a HIP graph: every replay, with eager work and
     synchronisations between the replays, reproduces the eager results bit for bit."""
     import torch
     w = W.custom("graph", [700, 64, 1, 900, 333], 4, 2, 128, seed=77)
-    eager = run_all(gpu, w)
+    eager = run_all(gpu, w, flags=route(general))
     want = eager.result_bits()
-    prob = gpu.DeviceProblem(w)
+    prob = gpu.DeviceProblem(w, flags=route(general))
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(side):        # warm-up on the capture stream
