@@ -23,10 +23,6 @@ __device__ __forceinline__ void store_frag(float* base, const f32x16 (&acc)[D / 
       *reinterpret_cast<f32x4*>(base + ((((size_t)wave * (D / 32) + db) * 4 + rq) * 64 + lane) * 4) = t;
     }
 }
-template <int D>
-__device__ __forceinline__ f32x4 load_frag4(const float* base, int wave, int lane, int db, int rq) {
-  return *reinterpret_cast<const f32x4*>(base + ((((size_t)wave * (D / 32) + db) * 4 + rq) * 64 + lane) * 4);
-}
 template <int D> constexpr size_t frag_floats() { return (size_t)kTile * D; }
 // forward partial: O fragment, then the reference m[4][64] and row sum l[4][64]
 template <int D> constexpr size_t fwd_partial_floats() { return frag_floats<D>() + 2 * kThreads; }

@@ -13,15 +13,18 @@ namespace {
 // a tile.  Here a workgroup owns 32 rows and its four waves share the chain of 32 x 32 blocks of
 // those rows (wave w takes blocks w, w + 4, ...), so that a chain takes a quarter of its length;
 // the four partial results meet in LDS.  No chain is cut across workgroups: no partial results in
-// memory, no reduction launch.  Every wave stages its blocks for itself, two in flight, without a
+// memory and no reduction launch, except for the q heads of a group in the backward, which store fp32
+// [dK | dV] each and are added up by a second launch.  Every wave stages its blocks for itself, two in flight, without a
 // barrier before the end.  D = rowsum(dO * O) is formed where it is used, so that dQ and dK / dV
 // need no order between them and share one launch.
-// The price is one read of K and V (Q, dO, O) per 32 rows instead of 128 and one workgroup per CU.
+// The price is one read of K and V (Q, dO, O) per 32 rows instead of 128 and the LDS: one workgroup per CU
+// at d = 128 (133 KB forward, 160 KB backward), two at d = 64.
 // 777 tokens, 4 heads of 128, forward 14.5 -> 8.0 us (the plan in workgroup 0 is what is left),
 // backward 29.4 -> 10.5 us; 2048 tokens in 4 documents, 2 heads of 64, forward and backward 37.4 ->
 // 27.9 us.  The rule by which a microbatch comes here is short_path() in varlen_attn.hip.
 // ----------------------------------------------------------------------------------------
 constexpr int kShortRows = 32;
+constexpr float kShortLag = 8.f;   // the forward's running maximum may lag by 2^8 before O is rescaled
 
 // The u-th 32-row tile of a microbatch of at most 64 documents, worked out by a whole wave from the
 // documents that the plan kept or, while the plan is being made beside it (`planned` false), from
@@ -186,7 +189,7 @@ fwd_short_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, con
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = __builtin_fmaxf(mx, s[r]);
     const float m_new = __builtin_fmaxf(m_run, half_max(mx) * cs);
-    if (__any(m_new > m_run + 8.0f)) {   // a reference that lags by up to 2^8 does no harm
+    if (__any(m_new > m_run + kShortLag)) {
       const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
       m_run = m_new;
       l_run *= alpha;

@@ -92,7 +92,9 @@ __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
 }
 
 // The same with the accumulator kept in vector registers whatever the compiler would choose.  The
-// compiler's wait states do not cover its result: see the one place that uses it.
+// compiler's wait states cover neither its operands nor its result: whoever uses it keeps the distance,
+// by mfma_vgpr_settle() (short.hpp) or by two further matrix instructions behind a fence (dK/dV), and
+// tests/test_wait_states.py checks the distances on the compiled code.
 __device__ __forceinline__ void mfma_vgpr(f32x16& c, const bf16x8& a, const bf16x8& b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
