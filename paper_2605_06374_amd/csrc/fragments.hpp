@@ -33,8 +33,9 @@ template <int D> constexpr size_t fwd_partial_floats() { return frag_floats<D>()
 // wave's 32 rows of 128 columns, where 8 stores of whole rows do): step at 8192 tokens 118.3 -> 113.9
 // us (dK/dV 46.6 -> 44.2), 9999 tokens uncut 192.9 -> 185.4 (dK/dV 79.0 -> 73.1), 32768 tokens in
 // documents of ordinary length 460.5 -> 445.9.  A tile [32 rows][D] of bf16, with
-// the 8-byte slots of a row permuted so that neither side meets a bank conflict: 16-byte chunk
-// `chunk` of row r lies at chunk ^ key(r), its halves exchanged in rows 16 .. 31.
+// the 8-byte slots of a row permuted to spread both sides over the banks: 16-byte chunk `chunk` of row
+// r lies at chunk ^ key(r), its halves exchanged in rows 16 .. 31.  (SQ_LDS_BANK_CONFLICT is not zero: 2.4e5
+// clocks over all workgroups of a dK/dV launch at 8192 tokens, under 200 of a wave's 100000.)
 // ----------------------------------------------------------------------------------------
 typedef unsigned u32x2 __attribute__((ext_vector_type(2), may_alias));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4), may_alias));

@@ -218,8 +218,8 @@ inline bool small_plan(const varlen_attn_params* p) {
 // again, so it is worth it up to three rounds of workgroups.  Forward on a plan launch / here, 82
 // microbatches of 3000 to 32000 tokens, 4 to 32 heads: 1.18 .. 1.00 from 800 to 1536 (tile, head)
 // pairs (head size 64 1.19 .. 1.02), 1.05 .. 0.98 from 1700 to 2200.  Longest first as soon as the
-// units may exceed one round: 10063 of 11918 tokens in one document, 8 heads, 768 pairs, took 288 us
-// in tile order and 263 us on a plan launch.
+// units may exceed one round, unless all of them are short: 10063 of 11918 tokens in one document, 8
+// heads, 768 pairs, took 288 us in tile order and 263 us on a plan launch.
 inline bool self_planned_forward(const varlen_attn_params* p) {
   const long long tiles = (long long)p->total_tokens / kTile + p->num_docs;
   return small_plan(p) && !(p->flags & VARLEN_ATTN_FLAG_PLAN_FIRST) && p->num_docs <= kSelfPlanDocs &&
