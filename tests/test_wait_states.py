@@ -112,7 +112,7 @@ CHAIN = """
     ("s_cbranch_scc1 .L1\ns_nop 15\ns_endpgm\n.L1:\nds_write_b128 v20, v[0:3]", 2),
     ("v_mov_b32 v60, 0\n;;#ASMSTART\nv_mfma_f32_32x32x16_bf16 v[64:79], v[60:63], v[44:47], 0\n;;#ASMEND", 1),
     ("v_mov_b32 v60, 0\ns_nop 1\n;;#ASMSTART\nv_mfma_f32_32x32x16_bf16 v[64:79], v[60:63], v[44:47], 0\n;;#ASMEND", 0)])
-def test_checker(tail, count):
+def test_snippets(tail, count):
     bad, _ = violations(CHAIN + tail)
     assert len(bad) == count, bad
 
