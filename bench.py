@@ -206,8 +206,8 @@ def main() -> int:
                                                "bwd_short_group_kernel") * 1e-6) / 1e12, 1)}
         # algorithmic flops per launch: 2*d per (pair, contraction); forward S and PV;
         # dK/dV kernel S, dP, dV, dK; dQ kernel only the dQ contraction is new work
-        # (the single-kernel backward and that of small microbatches: all five)
-        per_pair = {"fwd_kernel": 4, "bwd_dkv_kernel": 8, "bwd_dq_kernel": 2, "bwd_fused_kernel": 10,
+        # (the pooled backward, which launches no dQ kernel, the single-kernel one and that of small microbatches: all five)
+        per_pair = {"fwd_kernel": 4, "bwd_dkv_kernel": 8 if "bwd_dq_kernel" in kernels else 10, "bwd_dq_kernel": 2, "bwd_fused_kernel": 10,
                     "fwd_short_kernel": 4, "bwd_short_kernel": 10}
         dom = max((k for k in kernels if k in per_pair), key=lambda k: kernels[k]["avg_us"])
         alg = per_pair[dom] * w.head_dim * w.n_q_heads * w.pairs

@@ -166,7 +166,8 @@ typedef struct {
                                  unit sweeps one after the other (a divisor of Hq / Hkv; 1: one
                                  unit per q head) */
   int32_t col_class_shift; /* the same for the column units */
-  int32_t reserved[2];
+  int32_t n_dq_units;      /* units of a dQ that has chunks of its own (a library-internal list); 0: the row units */
+  int32_t n_dq_combine;
   int64_t pairs;           /* sum_b l_b (l_b + 1) / 2: (query, key) pairs inside the mask */
 } varlen_attn_plan_header;
 

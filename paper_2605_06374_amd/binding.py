@@ -58,7 +58,7 @@ class PlanHeader(ctypes.Structure):
                 ("col_chunk_steps", ctypes.c_int32), ("n_row_slots", ctypes.c_int32),
                 ("n_col_slots", ctypes.c_int32), ("row_class_shift", ctypes.c_int32),
                 ("col_heads_per_unit", ctypes.c_int32), ("col_class_shift", ctypes.c_int32),
-                ("reserved", ctypes.c_int32 * 2),
+                ("n_dq_units", ctypes.c_int32), ("n_dq_combine", ctypes.c_int32),
                 ("pairs", ctypes.c_int64)]
 
 

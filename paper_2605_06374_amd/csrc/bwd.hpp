@@ -5,6 +5,7 @@
 #include "tiles.hpp"
 #include "staging.hpp"
 #include "fragments.hpp"
+#include "plan.hpp"
 
 namespace {
 
@@ -207,14 +208,17 @@ bwd_dq_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
 }
 
 // ----------------------------------------------------------------------------------------
-// Fused backward (VARLEN_ATTN_FLAG_FUSED_BWD), first kernel: -D = -rowsum(dO * O) and -LSE / scale
-// for every (token, q head) into the workspace, and the fp32 dQ accumulator cleared.  One group of D / 8 lanes per row (16 bytes per lane); HBM-bound.
+// First kernel of the fused backward (VARLEN_ATTN_FLAG_FUSED_BWD) and of the pooled one (bwd_pool.hpp):
+// -D = -rowsum(dO * O) and -LSE / scale for every (token, q head) into the workspace; the fp32 dQ accumulator
+// (fused) or the ticket counters (pooled) cleared.  One group of D / 8 lanes per row (16 bytes per lane); bound by
+// memory (67 MB in 13 us at 32768 tokens, 4 heads of 128; four rows a group took 1 us longer at 8192 tokens).
 // ----------------------------------------------------------------------------------------
-template <int D>
+template <int D, bool FUSED>
 __global__ void __launch_bounds__(kThreads)
 bwd_prep_kernel(const __bf16* __restrict__ o, const __bf16* __restrict__ d_o,
                 const float* __restrict__ lse, float* __restrict__ neg_dsum,
-                float* __restrict__ neg_lse, float* __restrict__ dq_acc, int N, int Hq, float scale) {
+                float* __restrict__ neg_lse, float* __restrict__ dq_acc, int* __restrict__ tickets, int N, int Hq, float scale) {
+  if (!FUSED && blockIdx.x == 0 && threadIdx.x < kTicketCounters) tickets[threadIdx.x] = 0;
   constexpr int kLanesPerRow = D / 8;
   constexpr int kRowsPerBlock = kThreads / kLanesPerRow;
   const long long row = (long long)blockIdx.x * kRowsPerBlock + threadIdx.x / kLanesPerRow;  // t * Hq + h
@@ -227,9 +231,11 @@ bwd_prep_kernel(const __bf16* __restrict__ o, const __bf16* __restrict__ d_o,
     const bf16x8 x = __builtin_bit_cast(bf16x8, a), y = __builtin_bit_cast(bf16x8, b);
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc += (float)x[e] * (float)y[e];
-    f32x4* z = reinterpret_cast<f32x4*>(dq_acc + row * D + 8 * part);
-    z[0] = f32x4{0.f, 0.f, 0.f, 0.f};
-    z[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (FUSED) {
+      f32x4* z = reinterpret_cast<f32x4*>(dq_acc + row * D + 8 * part);
+      z[0] = f32x4{0.f, 0.f, 0.f, 0.f};
+      z[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
   }
 #pragma unroll
   for (int off = kLanesPerRow / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);

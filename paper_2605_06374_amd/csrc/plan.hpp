@@ -41,7 +41,10 @@ constexpr int kNoSplitSteps = 1 << 28;
 // nothing but the plan either: a caller may refill cu_seqlens once the plan is made.  All zero, which
 // is no partition of N tokens, when nothing was planned.
 constexpr int kSelfPlanDocs = 64, kSelfPlanTiles = 256;
-static_assert(sizeof(varlen_attn_plan_header) + 2 * kSelfPlanDocs <= 256, "the unit arrays start at byte 256");
+// ... and behind them the ticket counters of a backward (bwd_pool.hpp).
+constexpr int kTicketsOffset = 192, kTicketCounters = 8;
+static_assert(sizeof(varlen_attn_plan_header) + 2 * kSelfPlanDocs <= kTicketsOffset && kTicketsOffset + 4 * kTicketCounters <= 256,
+              "the unit arrays start at byte 256");
 __device__ __forceinline__ uint16_t* kept_ends(const varlen_attn_plan_header* hdr) {
   return reinterpret_cast<uint16_t*>(const_cast<varlen_attn_plan_header*>(hdr) + 1);
 }
@@ -52,9 +55,10 @@ struct PlanArgs {
   int force_ch[2];  // > 0: chunk length given by the caller (tuning), per direction
   int force_hpu;    // > 0: q heads per column unit given by the caller (a divisor of g)
   varlen_attn_plan_header* hdr;
-  varlen_attn_unit* units[2];
-  varlen_attn_combine_item* comb[2];
-  int max_units, max_combine, max_slots[2], slots_cap;
+  varlen_attn_unit* units[3];            // row units, column units, dQ units
+  varlen_attn_combine_item* comb[3];
+  int max_units, max_combine, max_slots[3], slots_cap;
+  int directions;         // 3: with a list of dQ units of their own chunk length (bwd_pool.hpp)
   bool longest_first;     // order in which the forward's workgroups take their own units (derive_row_unit)
   int32_t* status_copy;   // optional second place for the status word (device), or null
 };
@@ -93,6 +97,14 @@ __device__ __forceinline__ int plan_chunk_steps(int d, unsigned long long steps_
     by_fill = (d + 1) * (((long long)steps_d + room - 1) / room);
   const int ch = (int)max(max((long long)kMinChunkSteps, by_fill), by_units);
   return forced > 0 ? forced : ch;
+}
+
+// Chunk length of a dQ with units of its own: the backward's resident workgroups draw column units and dQ units from one
+// pool, so that a chain is cut only where it would outlast the rest: half of a workgroup's share, a column step
+// counted as two (it takes 1.9 times as long).
+__device__ __forceinline__ int plan_dq_steps(const unsigned long long* steps, int Hq, int row_steps, int forced) {
+  const long long share = (long long)(((steps[0] + 2 * steps[1]) * Hq + kTargetUnits - 1) / kTargetUnits);
+  return forced > 0 ? forced : (int)max((long long)row_steps, share);
 }
 
 // sum over the lanes of a wave (all lanes get it)
@@ -218,20 +230,20 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
   static_assert(2 * kPlanClasses * kPlanWaves == kPlanThreads, "one thread per class counter");
   __shared__ int doc_first_tile[kPlanThreads + 1];  // running tile count of the batch's documents
   __shared__ int doc_s[kPlanThreads], doc_e[kPlanThreads];
-  __shared__ int hist[2][kPlanClasses][kPlanWaves];    // units per (direction, class, wave), then cursors
-  __shared__ int class_total[2][kPlanClasses];
+  __shared__ int hist[3][kPlanClasses][kPlanWaves];    // units per (direction, class, wave), then cursors
+  __shared__ int class_total[3][kPlanClasses];
   __shared__ int wave_sum[kPlanWaves];
   __shared__ unsigned long long pairs, steps[2];
-  __shared__ int n_tiles, bad, max_chain[2];
-  __shared__ int split[2], n_units[2], n_slots[2], n_comb[2];
+  __shared__ int n_tiles, bad, max_chain;
+  __shared__ int split[3], n_units[3], n_slots[3], n_comb[3];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int32_t* cu = a.cu;
   if (tid == 0) {
     bad = (cu[0] != 0) || (cu[a.B] != a.N);
     pairs = steps[0] = steps[1] = 0;
-    n_tiles = 0;
+    n_tiles = max_chain = 0;
   }
-  if (tid < 2) split[tid] = n_units[tid] = n_slots[tid] = n_comb[tid] = max_chain[tid] = 0;
+  if (tid < 3) split[tid] = n_units[tid] = n_slots[tid] = n_comb[tid] = 0;
   __syncthreads();
   // ---- totals over the documents: pairs, steps of both directions, tiles, longest chains
   {
@@ -254,7 +266,7 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
     if (my_pairs) {
       atomicAdd(&pairs, my_pairs); atomicAdd(&steps[0], my_r); atomicAdd(&steps[1], my_c);
       atomicAdd(&n_tiles, my_tiles);
-      atomicMax(&max_chain[0], my_max);   // the longest row and column chains are both ceil(l / 64)
+      atomicMax(&max_chain, my_max);   // the longest row and column chains are both ceil(l / 64)
     }
   }
   __syncthreads();
@@ -269,13 +281,11 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
     }
     return;
   }
-  int ch[2];
+  int ch[3] = {kNoSplitSteps, kNoSplitSteps, kNoSplitSteps};
+  if (!a.no_split) {
 #pragma unroll
-  for (int d = 0; d < 2; ++d) {
-    ch[d] = kNoSplitSteps;
-    if (!a.no_split) {
-      ch[d] = plan_chunk_steps(d, steps[d], n_tiles, a.Hq, a.force_ch[d]);
-    }
+    for (int d = 0; d < 2; ++d) ch[d] = plan_chunk_steps(d, steps[d], n_tiles, a.Hq, a.force_ch[d]);
+    ch[2] = plan_dq_steps(steps, a.Hq, ch[0], a.force_ch[0]);
   }
   // Grouped-query attention: a column unit may sweep several q heads of its group (their dK,
   // dV add up in its registers: fewer and smaller group sums afterwards) as long as enough
@@ -290,20 +300,21 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
         if (a.g % cand == 0 && groups / cand >= kGroupSweepMinUnits) hpu = cand;
     }
   }
-  const int longest = max_chain[0];
+  const int longest = max_chain;
 
   // mode 0: count the units of every cost class (and the chunks of cut chains); mode 1: place.
-  int mode = 0, shift[2] = {0, 0};
+  int mode = 0, shift[3] = {0, 0, 0};
 #pragma unroll 1
   for (;;) {
     if (mode == 0) {
 #pragma unroll
-      for (int d = 0; d < 2; ++d) {
+      for (int d = 0; d < 3; ++d) {
         shift[d] = 0;
         while ((min(ch[d], longest) - 1) >> shift[d] >= kPlanClasses) ++shift[d];
       }
       reinterpret_cast<int*>(hist)[tid] = 0;   // 2 x 32 x waves counters: one per thread
-      if (tid < 2) split[tid] = 0;
+      if (tid < kPlanThreads / 2) reinterpret_cast<int*>(hist[2])[tid] = 0;
+      if (tid < 3) split[tid] = 0;
       __syncthreads();
     }
     int row_slots_before = 0;   // cut row chains' slots so far, in tile order (single-wave form)
@@ -332,7 +343,7 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
       for (int t0 = 0; t0 < batch_tiles; t0 += kPlanThreads) {
         const int t = t0 + tid;
         const bool valid = t < batch_tiles;
-        int ss = 0, ee = 0, row0 = 0, n_d[2] = {0, 0}, nc_d[2] = {0, 0};
+        int ss = 0, ee = 0, row0 = 0, n_d[3] = {0, 0, 0}, nc_d[3] = {0, 0, 0};
         if (valid) {
           // document of tile t: the last one whose first tile is <= t (documents without tiles
           // repeat the value of their successor and are skipped by taking the last)
@@ -348,6 +359,8 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
           n_d[1] = (ee - row0 + kStep - 1) / kStep;
           nc_d[0] = (n_d[0] + ch[0] - 1) / ch[0];
           nc_d[1] = (n_d[1] + ch[1] - 1) / ch[1];
+          n_d[2] = n_d[0];
+          nc_d[2] = (n_d[2] + ch[2] - 1) / ch[2];
         }
         // slots of a cut row chain, numbered in tile order
         int ordered_slot0 = 0;
@@ -359,7 +372,8 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
         }
         if (valid) {
 #pragma unroll
-          for (int d = 0; d < 2; ++d) {
+          for (int d = 0; d < 3; ++d) {
+            if (d == 2 && a.directions < 3) break;
             const int n = n_d[d], nc = nc_d[d], base = n / nc, rem = n % nc;
             // nc - rem chunks of `base` steps, rem chunks of base + 1 (those come first in the chain)
             int* h_lo = &hist[d][(base - 1) >> shift[d]][wave];
@@ -395,17 +409,17 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
     }
     if (mode == 1) break;
     // lengthen the chunks until the cut chains fit their slots
-    const bool fit0 = split[0] <= a.slots_cap, fit1 = split[1] <= a.slots_cap;
-    if (!(fit0 && fit1)) {
+    const bool fit0 = split[0] <= a.slots_cap, fit1 = split[1] <= a.slots_cap, fit2 = split[2] <= a.slots_cap;
+    if (!(fit0 && fit1 && fit2)) {
       __syncthreads();
       if (!fit0) ch[0] *= 2;
       if (!fit1) ch[1] *= 2;
+      if (!fit2) ch[2] *= 2;
       continue;
     }
     // counters -> start positions: classes from the longest down, waves in order inside a class
-    {
-      const int d = tid / (kPlanClasses * kPlanWaves), cls = (tid / kPlanWaves) % kPlanClasses,
-                w = tid % kPlanWaves;
+    auto to_starts = [&](int d, bool active) {
+      const int cls = (tid / kPlanWaves) % kPlanClasses, w = tid % kPlanWaves;
       const int own = hist[d][cls][w];
       int incl = own;   // inclusive sum over the 16 waves of this class (16 adjacent lanes)
 #pragma unroll
@@ -413,24 +427,26 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
         const int o = __shfl_up(incl, off);
         if (w >= off) incl += o;
       }
-      if (w == kPlanWaves - 1) class_total[d][cls] = incl;
+      if (active && w == kPlanWaves - 1) class_total[d][cls] = incl;
       __syncthreads();
       int above = 0;
 #pragma unroll 1
       for (int c2 = cls + 1; c2 < kPlanClasses; ++c2) above += class_total[d][c2];
-      if (cls == 0 && w == kPlanWaves - 1) n_units[d] = above + incl;
+      if (active && cls == 0 && w == kPlanWaves - 1) n_units[d] = above + incl;
       __syncthreads();
-      hist[d][cls][w] = above + incl - own;
+      if (active) hist[d][cls][w] = above + incl - own;
       __syncthreads();
-    }
+    };
+    to_starts(tid / (kPlanClasses * kPlanWaves), true);
+    if (a.directions > 2) to_starts(2, tid < kPlanClasses * kPlanWaves);
     mode = 1;
   }
   // The capacities are worst-case bounds (tiles <= N / 128 + B; a cut chain of n > ch steps
   // takes ceil(n / ch) <= 2 n / ch chunks, and ch was lengthened until those fit), so this
   // cannot fail; if it ever does, it is an error of its own and nothing is planned.
-  const bool ok = n_units[0] <= a.max_units && n_units[1] <= a.max_units &&
-                  n_comb[0] <= a.max_combine && n_comb[1] <= a.max_combine &&
-                  n_slots[0] <= a.max_slots[0] && n_slots[1] <= a.max_slots[1];
+  bool ok = true;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) ok = ok && n_units[d] <= a.max_units && n_comb[d] <= a.max_combine && n_slots[d] <= a.max_slots[d];
   if (!ok && tid < kSelfPlanDocs) kept_ends(hdr)[tid] = 0;
   if (tid == 0) {
     hdr->status = ok ? VARLEN_ATTN_OK : VARLEN_ATTN_PLAN_OVERFLOW;
@@ -446,7 +462,8 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
     hdr->row_class_shift = shift[0];
     hdr->col_heads_per_unit = hpu;
     hdr->col_class_shift = shift[1];
-    for (int i = 0; i < 2; ++i) hdr->reserved[i] = 0;
+    hdr->n_dq_units = ok ? n_units[2] : 0;
+    hdr->n_dq_combine = ok ? n_comb[2] : 0;
     hdr->pairs = (int64_t)pairs;
   }
 }

@@ -29,12 +29,15 @@
 #include "fwd.hpp"
 #include "bwd.hpp"
 #include "short.hpp"
+#include "bwd_pool.hpp"
 
 namespace {
 
 // ----------------------------------------------------------------------------------------
 // Optional per-kernel timing (host-side HIP events only; off by default).
 // ----------------------------------------------------------------------------------------
+// (A launch counts under what it does: the pooled backward's as bwd_dkv_kernel, without a bwd_dq_kernel beside it, and
+// its reduction as bwd_combine_kernel.)
 enum KernelId { kPlan = 0, kFwd, kFwdCombine, kDq, kDkv, kBwdCombine, kPrep, kFusedBwd, kDqFinish, kFwdShort, kBwdShort, kBwdShortGroup, kNumKernels };
 const char* const kKernelNames[kNumKernels] = {
     "plan_kernel", "fwd_kernel", "fwd_combine_kernel", "bwd_dq_kernel", "bwd_dkv_kernel",
@@ -115,6 +118,13 @@ bool params_ok(const varlen_attn_params* p) {
   return true;
 }
 
+// The list of the pooled backward's dQ units lies right in front of the dQ accumulator's offset (the forward, and with it
+// varlen_attn_fwd_static, reaches up to the column partial results only).
+inline size_t dq_list_bytes(const varlen_attn_workspace_layout& L) {
+  return align_up(sizeof(varlen_attn_unit) * L.max_units + sizeof(varlen_attn_combine_item) * L.max_combine, 256);
+}
+inline size_t dq_list_offset(const varlen_attn_workspace_layout& L) { return L.dq_accumulator_offset - dq_list_bytes(L); }
+
 // Capacities depend on the params only.  Slots: enough for kTargetUnits (unit, head) pairs,
 // never more than 8 per tile; with grouped-query attention every column tile takes a slot.
 bool layout_of(const varlen_attn_params* p, varlen_attn_workspace_layout* L, int* slots_cap) {
@@ -141,6 +151,8 @@ bool layout_of(const varlen_attn_params* p, varlen_attn_workspace_layout* L, int
   L->dsum_offset = off; off = align_up(off + 2 * sizeof(float) * (size_t)Hq * p->total_tokens, 256);
   L->row_partials_offset = off; off = align_up(off + fwd_part * Hq * L->max_row_slots, 256);
   L->col_partials_offset = off; off = align_up(off + 2 * frag * Hq * L->max_col_slots, 256);
+  // the pooled backward's dQ units and their reduction list
+  off = align_up(off + dq_list_bytes(*L), 256);
   // fused backward: fp32 dQ accumulator [N, Hq, d]
   L->dq_accumulator_offset = off;
   if (p->flags & VARLEN_ATTN_FLAG_FUSED_BWD)
@@ -168,16 +180,18 @@ int check_common(const varlen_attn_params* p, const void* const* ptrs, int n_ptr
 
 struct Regions {
   varlen_attn_plan_header* hdr;
-  varlen_attn_unit *row_units, *col_units;
-  varlen_attn_combine_item *row_comb, *col_comb;
+  varlen_attn_unit *row_units, *col_units, *dq_units;
+  varlen_attn_combine_item *row_comb, *col_comb, *dq_comb;
   float *dsum, *row_part, *col_part, *dq_acc;
 };
 Regions regions_of(char* ws, const varlen_attn_workspace_layout& L) {
   return Regions{reinterpret_cast<varlen_attn_plan_header*>(ws),
                  reinterpret_cast<varlen_attn_unit*>(ws + L.row_units_offset),
                  reinterpret_cast<varlen_attn_unit*>(ws + L.col_units_offset),
+                 reinterpret_cast<varlen_attn_unit*>(ws + dq_list_offset(L)),
                  reinterpret_cast<varlen_attn_combine_item*>(ws + L.row_combine_offset),
                  reinterpret_cast<varlen_attn_combine_item*>(ws + L.col_combine_offset),
+                 reinterpret_cast<varlen_attn_combine_item*>(ws + dq_list_offset(L) + sizeof(varlen_attn_unit) * L.max_units),
                  reinterpret_cast<float*>(ws + L.dsum_offset),
                  reinterpret_cast<float*>(ws + L.row_partials_offset),
                  reinterpret_cast<float*>(ws + L.col_partials_offset),
@@ -189,6 +203,8 @@ inline long long tile_heads(const varlen_attn_params* p) {
   return ((long long)p->total_tokens / kTile + p->num_docs) * p->num_q_heads;
 }
 
+bool pooled_backward(const varlen_attn_params* p);
+
 PlanArgs plan_args(const varlen_attn_params* p, const int32_t* cu, const Regions& R,
                    const varlen_attn_workspace_layout& L, int slots_cap, int32_t* status_copy) {
   PlanArgs a;
@@ -198,10 +214,11 @@ PlanArgs plan_args(const varlen_attn_params* p, const int32_t* cu, const Regions
   a.force_ch[0] = (p->flags >> 8) & 0xFF;
   a.force_ch[1] = (p->flags >> 16) & 0xFF;
   a.force_hpu = (p->flags >> 24) & 0xF;
-  a.hdr = R.hdr; a.units[0] = R.row_units; a.units[1] = R.col_units;
-  a.comb[0] = R.row_comb; a.comb[1] = R.col_comb;
+  a.hdr = R.hdr; a.units[0] = R.row_units; a.units[1] = R.col_units; a.units[2] = R.dq_units;
+  a.comb[0] = R.row_comb; a.comb[1] = R.col_comb; a.comb[2] = R.dq_comb;
   a.max_units = L.max_units; a.max_combine = L.max_combine;
-  a.max_slots[0] = L.max_row_slots; a.max_slots[1] = L.max_col_slots; a.slots_cap = slots_cap;
+  a.max_slots[0] = a.max_slots[2] = L.max_row_slots; a.max_slots[1] = L.max_col_slots; a.slots_cap = slots_cap;
+  a.directions = pooled_backward(p) ? 3 : 2;
   a.longest_first = tile_heads(p) > kResidentGroups;
   a.status_copy = status_copy;
   return a;
@@ -235,7 +252,7 @@ inline bool self_planned_forward(const varlen_attn_params* p) {
 // take at least 0.86 times as long as these inside the bounds (0.53 to 0.8 times beyond them: 10000
 // tokens, most of them in one document, on one head).  Packs of ordinary documents (log-normal, 360 of
 // them) gain 0.98 to 1.8 forward and 1.02 to 2.9 backward inside, which is why the bounds are not lower.
-inline bool short_path(const varlen_attn_params* p, bool backward) {
+inline bool short_sizes(const varlen_attn_params* p, bool backward) {
   const bool wide = p->head_dim == 128, grouped = p->num_q_heads > p->num_kv_heads;
   const long long heads = p->num_q_heads;
   long long max_rows, max_tokens;
@@ -248,14 +265,30 @@ inline bool short_path(const varlen_attn_params* p, bool backward) {
   }
   // few documents: one of them holds most of the tokens
   max_tokens = std::min(max_tokens, (wide ? 1536 : 2048) + 384ll * (p->num_docs - 1));
-  return !(p->flags & (VARLEN_ATTN_FLAG_NO_SPLIT | VARLEN_ATTN_FLAG_GENERAL)) && (p->flags >> 8) == 0 && p->num_docs <= kSelfPlanDocs &&
-         p->total_tokens <= max_tokens && p->total_tokens * heads <= max_rows;
+  return p->num_docs <= kSelfPlanDocs && p->total_tokens <= max_tokens && p->total_tokens * heads <= max_rows;
+}
+inline bool short_path(const varlen_attn_params* p, bool backward) {
+  return !(p->flags & (VARLEN_ATTN_FLAG_NO_SPLIT | VARLEN_ATTN_FLAG_GENERAL)) && (p->flags >> 8) == 0 && short_sizes(p, backward);
 }
 
-int launch_plan(const varlen_attn_params* p, const int32_t* cu, const Regions& R,
-                const varlen_attn_workspace_layout& L, int slots_cap, hipStream_t stream,
-                int32_t* status_copy = nullptr) {
-  const PlanArgs a = plan_args(p, cu, R, L, slots_cap, status_copy);
+// Backward with heads of 128, beyond the small microbatches: dQ units and column units as one pool (bwd_pool.hpp) or in
+// a kernel each.  The pool gains where chains differ in length and where the matrix pipe is the bound (one tail and
+// one set of prologues instead of two; dQ chains whole); it pays for a pass over dO and O in front of it, which the two kernels
+// do without.  Two kernels / pool over 150 packs of the sizes of perf/cases.py (microbatches of 500 to 40000 tokens, 1 to 32 heads):
+// 1.00 .. 1.38, 1.09 in the mean, with up to 24000 rows (tokens x q heads) or documents of 128 tokens and more on
+// average (400 with more than two q heads a kv head, whose column units all store partial results); 0.91 .. 1.09, 0.97 in the mean,
+// with shorter ones.  (The host does not know the longest document.  Documents of equal length are the pool's
+// worst case inside the rule: 0.95 with 32 of 512 tokens, 4 heads.)  With VARLEN_ATTN_FLAG_NO_SPLIT a document's bits must
+// not depend on what else is in the pack, hence neither may the route: there the heads alone decide.
+inline bool pooled_backward(const varlen_attn_params* p) {
+  if (p->head_dim != 128) return false;
+  const bool many_to_one = p->num_q_heads > 2 * p->num_kv_heads;
+  if (p->flags & VARLEN_ATTN_FLAG_NO_SPLIT) return !many_to_one;
+  const long long rows = (long long)p->total_tokens * p->num_q_heads, mean = p->total_tokens / p->num_docs;
+  return !short_sizes(p, true) && (rows <= 24000 || mean >= (many_to_one ? 400 : 128));
+}
+
+int launch_plan(const varlen_attn_params* p, const PlanArgs& a, hipStream_t stream) {
   ScopedKernelTimer timer(kPlan, stream);
   if (small_plan(p)) plan_kernel<kPlanThreadsSmall><<<1, kPlanThreadsSmall, 0, stream>>>(a);
   else plan_kernel<kPlanThreadsLarge><<<1, kPlanThreadsLarge, 0, stream>>>(a);
@@ -265,6 +298,7 @@ int launch_plan(const varlen_attn_params* p, const int32_t* cu, const Regions& R
 // Workgroups of a reduction launch at most: four per compute unit, which start within 1 us (the
 // dispatcher starts about 1200 workgroups per us; 512, 1024 and 2048 measure the same).
 constexpr int kCombineGroups = 1024;
+constexpr int kPoolGroups = 256;   // one workgroup per compute unit
 
 // self_plan: the forward launch makes the plan itself (no plan launch went before)
 template <int D>
@@ -321,13 +355,44 @@ void launch_bwd(const varlen_attn_params* p, const void* q, const void* k, const
   }
   float* neg_lse = R.dsum + (size_t)Hq * N;
   const bool fused = (p->flags & VARLEN_ATTN_FLAG_FUSED_BWD) != 0;
+  const bool split = !(p->flags & VARLEN_ATTN_FLAG_NO_SPLIT);
+  // A cut chain has at least two chunks and all chunks of cut chains fit the slots, so at most
+  // max_row_slots / 2 tiles are cut in either direction.
+  const int cut_tiles = std::max(1, std::min(L.max_combine, L.max_row_slots / 2));
+  const int col_items = Hq != Hkv ? L.max_combine : cut_tiles;   // grouped-query attention: every tile is summed over its group
+  if constexpr (D == 128) {
+    if (!fused && pooled_backward(p)) {
+      int* const tickets = reinterpret_cast<int*>(reinterpret_cast<char*>(R.hdr) + kTicketsOffset);
+      {
+        ScopedKernelTimer timer(kPrep, stream);
+        constexpr int kRowsPerBlock = kThreads / (D / 8);
+        const long long rows = (long long)N * Hq;
+        bwd_prep_kernel<D, false><<<dim3((unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock)), kThreads, 0, stream>>>(
+            (const __bf16*)o, (const __bf16*)d_o, lse, R.dsum, neg_lse, nullptr, tickets, N, Hq, scale);
+      }
+      {
+        ScopedKernelTimer timer(kDkv, stream);   // dK, dV and dQ
+        bwd_pool_kernel<D><<<dim3(kPoolGroups), kThreads, 0, stream>>>(
+            BwdArgs<D>{(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)d_o, neg_lse, R.dsum, R.hdr, R.col_units,
+                       R.dq_units, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, R.col_part, R.row_part, N, Hq, Hkv, scale, tickets});
+      }
+      if (split || Hq != Hkv) {
+        const int dq_items = split ? cut_tiles : 0;
+        const long long pieces = (long long)col_items * Hkv * (D / 8) + (long long)dq_items * Hq * (D / 16);
+        ScopedKernelTimer timer(kBwdCombine, stream);
+        bwd_pool_combine_kernel<D><<<dim3((unsigned)std::min<long long>(pieces, 2 * kCombineGroups)), kThreads, 0, stream>>>(
+            R.hdr, R.col_comb, col_items, R.col_part, R.dq_comb, dq_items, R.row_part, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, Hq, Hkv, scale);
+      }
+      return;
+    }
+  }
   if (fused) {
     // -D = -rowsum(dO * O), -LSE / scale, and the dQ accumulator cleared
     ScopedKernelTimer timer(kPrep, stream);
     constexpr int kRowsPerBlock = kThreads / (D / 8);
     const long long rows = (long long)N * Hq;
-    bwd_prep_kernel<D><<<dim3((unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock)), kThreads, 0, stream>>>(
-        (const __bf16*)o, (const __bf16*)d_o, lse, R.dsum, neg_lse, R.dq_acc, N, Hq, scale);
+    bwd_prep_kernel<D, true><<<dim3((unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock)), kThreads, 0, stream>>>(
+        (const __bf16*)o, (const __bf16*)d_o, lse, R.dsum, neg_lse, R.dq_acc, nullptr, N, Hq, scale);
   } else {
     // also writes -D = -rowsum(dO * O) and -LSE / scale, which the dK/dV kernel reads
     ScopedKernelTimer timer(kDq, stream);
@@ -336,10 +401,6 @@ void launch_bwd(const varlen_attn_params* p, const void* q, const void* k, const
         lse, R.dsum, neg_lse, R.hdr, R.row_units, (__bf16*)dq, R.row_part, N, Hq, Hkv, scale,
         L.max_units);
   }
-  const bool split = !(p->flags & VARLEN_ATTN_FLAG_NO_SPLIT);
-  // A cut chain has at least two chunks and all chunks of cut chains fit the slots, so at most
-  // max_row_slots / 2 tiles are cut in either direction.
-  const int cut_tiles = std::max(1, std::min(L.max_combine, L.max_row_slots / 2));
   const unsigned unit_blocks = grid_for(L.max_units, Hq);
   if (fused) {
     // one kernel for dQ, dK and dV; dQ is summed in fp32 in the workspace and rounded afterwards
@@ -364,8 +425,6 @@ void launch_bwd(const varlen_attn_params* p, const void* q, const void* k, const
         R.dq_acc, (__bf16*)dq, n8, scale);
   }
   if (split || Hq != Hkv) {
-    // grouped-query attention: every tile's [dK | dV] is summed over the group; else cut tiles only
-    const int col_items = Hq != Hkv ? L.max_combine : cut_tiles;
     const long long pieces = (long long)col_items * Hkv * (D / 8);   // see bwd_combine_kernel
     ScopedKernelTimer timer(kBwdCombine, stream);
     bwd_combine_kernel<D><<<dim3((unsigned)std::min<long long>(pieces, kCombineGroups)), kThreads, 0, stream>>>(
@@ -399,7 +458,7 @@ int varlen_attn_plan(const varlen_attn_params* params, const int32_t* cu_seqlens
   const void* ptrs[] = {cu_seqlens};
   const int rc = check_common(params, ptrs, 1, workspace, workspace_bytes, &L, &cap);
   if (rc != VARLEN_ATTN_OK) return rc;
-  return launch_plan(params, cu_seqlens, regions_of(static_cast<char*>(workspace), L), L, cap,
+  return launch_plan(params, plan_args(params, cu_seqlens, regions_of(static_cast<char*>(workspace), L), L, cap, nullptr),
                      static_cast<hipStream_t>(hip_stream));
 }
 
@@ -418,7 +477,7 @@ int varlen_attn_fwd(const varlen_attn_params* params, const void* q, const void*
   if (!(params->flags & VARLEN_ATTN_FLAG_REUSE_PLAN)) {
     self_plan = self_planned_forward(params);
     if (!self_plan) {
-      rc = launch_plan(params, cu_seqlens, R, L, cap, stream);
+      rc = launch_plan(params, args, stream);
       if (rc != VARLEN_ATTN_OK) return rc;
     }
   }
@@ -449,9 +508,10 @@ int varlen_attn_fwd_static(const varlen_attn_params* params, const void* q, cons
   if (rc != VARLEN_ATTN_OK) return rc;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const Regions R = regions_of(static_cast<char*>(ws), L);
-  const PlanArgs args = plan_args(params, cu_seqlens, R, L, cap, plan_status);
+  PlanArgs args = plan_args(params, cu_seqlens, R, L, cap, plan_status);
+  args.directions = 2;   // no backward follows, and the array ends in front of a third list
   const bool self_plan = self_planned_forward(params);
-  if (!self_plan) rc = launch_plan(params, cu_seqlens, R, L, cap, stream, plan_status);
+  if (!self_plan) rc = launch_plan(params, args, stream);
   if (rc != VARLEN_ATTN_OK) return rc;
   if (params->head_dim == 128) launch_fwd<128>(params, q, k, v, o, lse, R, L, stream, args, self_plan);
   else launch_fwd<64>(params, q, k, v, o, lse, R, L, stream, args, self_plan);
@@ -469,11 +529,11 @@ int varlen_attn_bwd(const varlen_attn_params* params, const void* q, const void*
   if (rc != VARLEN_ATTN_OK) return rc;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const Regions R = regions_of(static_cast<char*>(workspace), L);
+  const PlanArgs args = plan_args(params, cu_seqlens, R, L, cap, nullptr);
   if (!(params->flags & VARLEN_ATTN_FLAG_REUSE_PLAN)) {
-    rc = launch_plan(params, cu_seqlens, R, L, cap, stream);
+    rc = launch_plan(params, args, stream);
     if (rc != VARLEN_ATTN_OK) return rc;
   }
-  const PlanArgs args = plan_args(params, cu_seqlens, R, L, cap, nullptr);
   if (params->head_dim == 128) launch_bwd<128>(params, q, k, v, o, lse, d_o, dq, dk, dv, R, L, stream, args);
   else launch_bwd<64>(params, q, k, v, o, lse, d_o, dq, dk, dv, R, L, stream, args);
   return hipGetLastError() == hipSuccess ? VARLEN_ATTN_OK : VARLEN_ATTN_LAUNCH_FAILED;

@@ -865,3 +865,52 @@ def test_overlap_and_atomic_probes_run(gpu):
     assert float(buf.view(torch.float32)[: 64 * 64 * 128].min()) >= 1.0
     with pytest.raises(RuntimeError):
         binding.varlen_attn_bench_atomic_rate(0, 8, 1 << 20, 1, buf)                # regions do not fit the buffer
+
+
+# ------------------------------------------------------------------ backward as one pool of units
+@pytest.mark.parametrize("chunks", ["plan", "one_step", "sweeps", "uncut"])
+@pytest.mark.parametrize("lengths,hq,hkv", [
+    ([1700], 1, 1), ([1, 127, 128, 129, 0, 63, 64, 65, 1800], 2, 2), ([1200, 700, 31, 33, 600], 3, 1),
+    ([257] * 9, 8, 1), ([640, 320, 961], 16, 4), ([2049, 5], 6, 3), ([129] * 70, 1, 1), ([900, 1600], 12, 4)])
+def test_pooled_backward(gpu, lengths, hq, hkv, chunks):
+    """Heads of 128 beyond the small microbatches: tiles of 1, 127, 128 and 129 rows, units of one stage, every way
+    the heads are dealt to ticket counters (divisors of 8, multiples of 8, neither), several heads a column unit,
+    whole chains; twice on one plan, which draws the units in another order, with the same bits."""
+    from paper_2605_06374_amd import binding
+    flags = {"plan": 0, "one_step": binding.flag_chunk_steps(1, 1),
+             "sweeps": binding.flag_chunk_steps(3, 2) | (binding.flag_group_heads(2) if hq // hkv % 2 == 0 else 0),
+             "uncut": binding.FLAG_NO_SPLIT}[chunks]
+    w = W.custom("pool", lengths, hq, hkv, 128, seed=sum(lengths) + 10 * hq + hkv)
+    prob = run_all(gpu, w, flags=flags)
+    assert_close_full(prob.results(), oracle_full(w), f"pool {lengths[:4]} {hq}/{hkv} {chunks}")
+    bits = prob.result_bits()
+    names = launched(lambda: prob.backward(reuse_plan=True))
+    pooled = chunks != "uncut" or hq <= 2 * hkv
+    assert ("bwd_dq_kernel" not in names) == pooled and ("bwd_prep_kernel" in names) == pooled
+    again = prob.result_bits()
+    for n in ("dq", "dk", "dv"):
+        assert np.array_equal(bits[n], again[n]), n
+
+
+def test_uncut_bits_do_not_depend_on_the_pack(gpu):
+    """VARLEN_ATTN_FLAG_NO_SPLIT: a document alone, among a few and in a large pack of short ones (sizes that
+    take different routes otherwise) has the same bits."""
+    from paper_2605_06374_amd import binding
+    rng = np.random.default_rng(5)
+    for hq, hkv, d in ((2, 2, 128), (8, 2, 128), (2, 2, 64)):
+        doc, bits = None, []
+        for before, after in (([], []), ([300, 40], [77]), ([40] * 150, [500] * 40)):
+            lengths = before + [333] + after
+            w = W.custom("pack", lengths, hq, hkv, d, seed=9)
+            vals = {n: v.copy() for n, v in w.values().items()}
+            at = sum(before)
+            if doc is None:
+                doc = {n: v[at:at + 333].copy() for n, v in vals.items()}
+            for n in vals:
+                vals[n][at:at + 333] = doc[n]
+            prob = run_all(gpu, w, values=vals, flags=binding.FLAG_NO_SPLIT)
+            got = prob.result_bits()
+            bits.append({n: got[n][:, at:at + 333] if n == "lse" else got[n][at:at + 333] for n in got})
+        for other in bits[1:]:
+            for n in bits[0]:
+                assert np.array_equal(bits[0][n], other[n]), (n, hq, hkv, d)
