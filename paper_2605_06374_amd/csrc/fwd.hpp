@@ -44,7 +44,7 @@ fwd_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __b
     decode_block(blockIdx.x - 1, Hq, unit_idx, head);
     if (threadIdx.x < 64) {
       varlen_attn_unit mine;
-      const bool ok = derive_row_unit(plan.cu, plan.B, plan.N, Hq, plan.no_split, plan.force_ch[0],
+      const bool ok = derive_row_unit(plan.cu, plan.B, plan.N, Hq, plan.no_split, plan.rule[0], plan.force_ch[0],
                                       plan.slots_cap, unit_idx, plan.longest_first, threadIdx.x, mine);
       if (threadIdx.x == 0) { own_valid = ok ? 1 : 0; if (ok) own_unit = mine; }
     }

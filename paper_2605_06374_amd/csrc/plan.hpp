@@ -11,11 +11,8 @@ namespace {
 //
 // One workgroup.  For both directions (0: row chains for forward / dQ, 1: column chains for
 // dK / dV) it picks the chunk length, cuts every tile's chain into nearly equal chunks and
-// writes the units.  Chunk length: at least kMinChunkSteps; on a microbatch whose tiles do not
-// fill the GPU by themselves, just long enough that all (unit, head) pairs are resident at
-// once (kResidentGroups workgroups: one round, no second wave of stragglers); otherwise long
-// enough that about kTargetUnits pairs exist; and always such that the partial-result slots
-// fit the workspace.
+// writes the units.  Chunk length: at least kMinChunkSteps, by two lines in the microbatch's steps
+// (ChunkRule), and always such that the partial-result slots fit the workspace.
 //
 // Units are placed longest first by cost class (kPlanClasses classes of equal width over the
 // chunk lengths that occur): the hardware hands workgroups out in index order, so this is
@@ -32,8 +29,7 @@ constexpr int kPlanThreadsSmall = 64;     // one wave: every barrier is free, no
 constexpr int kPlanClasses = 32;
 constexpr int kMinChunkSteps = 4;
 constexpr int kResidentGroups = 512;  // 256 CUs x 2 workgroups (forward, dQ)
-constexpr int kTargetUnits = 512;   // (unit, head) pairs from cut chains to aim for: more cost partial-result traffic
-constexpr long long kGroupSweepMinUnits = 512;  // column workgroups that must remain when units sweep several q heads
+constexpr int kTargetUnits = 512;   // (unit, head) slots that chunk lengths are counted in and that cut chains may take
 constexpr int kNoSplitSteps = 1 << 28;
 
 // Behind the header the plan of at most kSelfPlanDocs documents and 65535 tokens keeps the documents'
@@ -49,7 +45,18 @@ __device__ __forceinline__ uint16_t* kept_ends(const varlen_attn_plan_header* hd
   return reinterpret_cast<uint16_t*>(const_cast<varlen_attn_plan_header*>(hdr) + 1);
 }
 
+// Chunk length of a chain: ceil(slope * x) + base steps, or with slope2 and base2 where that is less (x: steps * Hq, what all
+// heads' chains have together), kMinChunkSteps at least.  The lines are fits to measured times; the host picks
+// them (chunk_rules() in varlen_attn.hip).  With `resident` units of a head that the GPU holds at once, 7/10 to 7/5 of that
+// length, `shortest` at least, where it takes all units into one round.
+struct ChunkRule { float slope, base, slope2, base2; int resident, shortest; };
+// Grouped-query attention: chunks of column units that sweep h q heads are h^-power as long, and h is the largest that leaves
+// min_units + min(units * x, max_units) units and none of more than slope * x + base (step, head) pairs.
+struct SweepRule { float power, min_units, units, max_units, slope, base; };
+
 struct PlanArgs {
+  ChunkRule rule[2];      // row chains, column chains
+  SweepRule sweep;
   const int32_t* cu;
   int B, N, Hq, g, no_split;
   int force_ch[2];  // > 0: chunk length given by the caller (tuning), per direction
@@ -58,7 +65,7 @@ struct PlanArgs {
   varlen_attn_unit* units[3];            // row units, column units, dQ units
   varlen_attn_combine_item* comb[3];
   int max_units, max_combine, max_slots[3], slots_cap;
-  int directions;         // 3: with a list of dQ units of their own chunk length (bwd_pool.hpp)
+  int directions;         // 0: status word only; 1: row units; 2: and column units; 3: and dQ units of their own chunk length
   bool longest_first;     // order in which the forward's workgroups take their own units (derive_row_unit)
   int32_t* status_copy;   // optional second place for the status word (device), or null
 };
@@ -84,19 +91,71 @@ __device__ __forceinline__ int lane_value(int v, int src) {
   return __builtin_amdgcn_readlane(v, __builtin_amdgcn_readfirstlane(src));
 }
 
-// Chunk length of direction d (0: row chains, 1: column chains) from the totals of the microbatch.
-__device__ __forceinline__ int plan_chunk_steps(int d, unsigned long long steps_d, int n_tiles, int Hq,
-                                                int forced) {
-  const long long by_units = (long long)((steps_d * Hq + kTargetUnits - 1) / kTargetUnits);
-  // Units of one head ~ steps / ch + tiles / 2 (a cut chain rarely divides evenly).  If
-  // the tiles leave room, take the shortest chunks that keep every unit resident at once;
-  // dK/dV partials are twice as large and its kernel is insensitive here: twice as long.
-  const long long room = kResidentGroups / Hq - n_tiles / 2;
-  long long by_fill = 0;
-  if (room >= kResidentGroups / Hq / 4 && room > 0)
-    by_fill = (d + 1) * (((long long)steps_d + room - 1) / room);
-  const int ch = (int)max(max((long long)kMinChunkSteps, by_fill), by_units);
-  return forced > 0 ? forced : ch;
+// Chunk length of a direction (ChunkRule).  `tries` > 0 tells that the units are to be resident at once: after each but the
+// last that missed it the length may grow, up to 7/5 of the line's (`line`), and is the line's in the end.  In single
+// precision without contraction: the forward workgroups of a small microbatch, whose steps are few enough to be exact, work it out
+// for themselves and have to agree with the plan.
+__device__ __forceinline__ int plan_chunk_steps(const ChunkRule& r, float steps, int n_tiles, int Hq, int forced, int& line,
+                                                int& tries) {
+#pragma clang fp contract(off)
+  const float x = steps * (float)Hq;
+  line = (int)min(max(min(ceilf(x * r.slope) + r.base, ceilf(x * r.slope2) + r.base2), (float)kMinChunkSteps), (float)kNoSplitSteps);
+  tries = 0;
+  if (forced > 0) return line = forced;
+  if (n_tiles > r.resident || r.resident == 0) return line;
+  // units of one head ~ steps / chunk + tiles / 2 (a cut chain rarely divides evenly)
+  const float room = (float)(2 * r.resident - n_tiles);
+  const int fill = max(max(r.shortest, (7 * line + 9) / 10), (int)ceilf(2.f * steps * __builtin_amdgcn_rcpf(room)));
+  tries = 5 * fill <= 7 * line ? 2 : 0;
+  return tries ? fill : line;
+}
+
+// The next chunk length when there are more chunks than `room` for them: longer in proportion, but by a sixteenth at least
+// (every turn counts all chunks again) and at most twice as long.
+__device__ __forceinline__ int longer_chunk(int ch, int chunks, int room) {
+  const float more = (float)ch * (float)(chunks - room) * __builtin_amdgcn_rcpf((float)room);
+  return ch + min(ch, max(1 + ch / 16, (int)min(more, (float)ch)));
+}
+
+// Chunks of at most `ch` steps over one document's chains, without a look at its tiles: `all` of them, `cut` in chains of more
+// than one.  Chains 1 .. M have 2 t steps (2 t - 1 where `odd`), so every ch chains have one chunk each up to h of them, two
+// up to ch, and 2 more than their predecessors ch before.
+template <typename Int>
+__device__ __forceinline__ void count_chunks(int M, int ch, bool odd, Int& all, Int& cut) {
+  const Int h = (ch + (odd ? 1 : 0)) / 2, q = (unsigned)M / (unsigned)ch, r = (Int)M - q * ch;
+  const Int chunks = ch * q * (q - 1) + q * (2 * (Int)ch - h) + 2 * q * r + r + max((Int)0, r - h);
+  all += chunks;
+  cut += chunks - min((Int)M, h);
+}
+// rows of a document of T tiles and S steps: T - 1 chains of 2 t steps and one of S
+template <typename Int>
+__device__ __forceinline__ void count_row_chunks(int T, int S, int ch, Int& all, Int& cut) {
+  if (T <= 0) return;
+  count_chunks<Int>(T - 1, ch, false, all, cut);
+  const int last = (int)(((unsigned)S + (unsigned)ch - 1) / (unsigned)ch);
+  all += last;
+  cut += last > 1 ? last : 0;
+}
+// columns: T chains of S, S - 2, ... steps
+template <typename Int>
+__device__ __forceinline__ void count_col_chunks(int T, int S, int ch, Int& all, Int& cut) {
+  if (T > 0) count_chunks<Int>(T, ch, S & 1, all, cut);
+}
+
+// Another turn with a longer chunk?  `cut` chunks of cut chains have `slots`, `all` units one round of `resident`.
+__device__ __forceinline__ bool next_chunk(int& ch, int line, int& tries, float steps, int cut, int slots, int all, int resident) {
+#pragma clang fp contract(off)
+  if (tries && all > resident) {
+    // what is not in proportion to 1 / ch (chains that do not divide evenly) stays
+    const float stays = (float)all - steps * __builtin_amdgcn_rcpf((float)ch), room = (float)resident - stays;
+    const float longer = room > 0.f ? ceilf(min(steps * __builtin_amdgcn_rcpf(room), 1e6f)) + 1.f : 1e6f;
+    if (--tries && longer * 5.f <= (float)(7 * line)) ch = max(ch + 1, (int)longer);
+    else { tries = 0; ch = line; }
+    return true;
+  }
+  if (cut <= slots) return false;
+  ch = longer_chunk(ch, cut, slots);
+  return true;
 }
 
 // Chunk length of a dQ with units of its own: the backward's resident workgroups draw column units and dQ units from one
@@ -107,8 +166,18 @@ __device__ __forceinline__ int plan_dq_steps(const unsigned long long* steps, in
   return forced > 0 ? forced : (int)max((long long)row_steps, share);
 }
 
-// sum over the lanes of a wave (all lanes get it)
+// sum, maximum and 64-bit sum over the lanes of a wave (all lanes get it)
 __device__ __forceinline__ int wave_total(int v) { return lane_value(wave_inclusive_sum(v), 63); }
+__device__ __forceinline__ int wave_max(int v) {
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) v = max(v, __shfl_xor(v, off));
+  return v;
+}
+__device__ __forceinline__ unsigned long long wave_total_wide(unsigned long long v) {
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) v += __shfl_xor(v, off);
+  return v;
+}
 
 // ----------------------------------------------------------------------------------------
 // The u-th row unit of a microbatch of at most 64 documents and 256 tiles, in the order
@@ -119,7 +188,7 @@ __device__ __forceinline__ int wave_total(int v) { return lane_value(wave_inclus
 // plan reports it) or u is past the last unit.
 // ----------------------------------------------------------------------------------------
 __device__ __forceinline__ bool derive_row_unit(const int32_t* __restrict__ cu, int B, int N, int Hq,
-                                                int no_split, int forced, int slots_cap, int u,
+                                                int no_split, const ChunkRule& rule, int forced, int slots_cap, int u,
                                                 bool longest_first, int lane, varlen_attn_unit& out) {
   int s = 0, e = 0;
   if (lane < B) { s = cu[lane]; e = cu[lane + 1]; }
@@ -130,7 +199,9 @@ __device__ __forceinline__ bool derive_row_unit(const int32_t* __restrict__ cu, 
   const int t_incl = wave_inclusive_sum(T);   // tiles up to and including this document
   const int n_tiles = lane_value(t_incl, 63);
   const int steps = wave_total(T * (T - 1) + S);
-  int ch = no_split ? kNoSplitSteps : plan_chunk_steps(0, (unsigned long long)steps, n_tiles, Hq, forced);
+  int ch = kNoSplitSteps, line = 0;
+  int tries = 0;
+  if (!no_split) ch = plan_chunk_steps(rule, (float)steps, n_tiles, Hq, forced, line, tries);
   constexpr int kRounds = kSelfPlanTiles / 64;
   static_assert(kRounds == 4, "chain lengths of four tiles a lane");
   int ds[kRounds], de[kRounds], row0[kRounds], n[kRounds], nc[kRounds];
@@ -153,18 +224,16 @@ __device__ __forceinline__ bool derive_row_unit(const int32_t* __restrict__ cu, 
       n[r] = t < n_tiles ? (min(row0[r] + kTile, de[r]) - 1 - ds[r]) / kStep + 1 : 0;
     }
   }
-  // chunks per tile; the chunk length doubles until the chunks of cut chains fit their slots
+  // the chunk length grows until the chunks of cut chains fit their slots
 #pragma unroll 1
   for (;;) {
-    int cut = 0;
-#pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-      nc[r] = n[r] ? (n[r] + ch - 1) / ch : 0;
-      cut += nc[r] > 1 ? nc[r] : 0;
-    }
-    if (no_split || wave_total(cut) <= slots_cap) break;
-    ch *= 2;
+    int cut = 0, all = 0;
+    if (!no_split) count_row_chunks<int>(T, S, ch, all, cut);
+    if (no_split) break;
+    if (!next_chunk(ch, line, tries, (float)steps, wave_total(cut), slots_cap, tries ? wave_total(all) : 0, rule.resident)) break;
   }
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) nc[r] = n[r] ? (n[r] + ch - 1) / ch : 0;
   // Longest first: the units of tiles with chunks longer than x come before all others, F(x) of them.
   // The smallest x with F(x) <= u, found bit by bit, is the length of the unit asked for; among the
   // tiles of that length it is number u - F(x) in tile order.  One sum over the wave per bit of the
@@ -234,16 +303,23 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
   __shared__ int class_total[3][kPlanClasses];
   __shared__ int wave_sum[kPlanWaves];
   __shared__ unsigned long long pairs, steps[2];
-  __shared__ int n_tiles, bad, max_chain;
-  __shared__ int split[3], n_units[3], n_slots[3], n_comb[3];
+  __shared__ int n_tiles, bad, max_chain, chunks[4];
+  __shared__ int n_units[3], n_slots[3], n_comb[3];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int32_t* cu = a.cu;
+  // the documents of the first batch stay in registers: every other pass starts without a trip to memory
+  const int first_s = tid < a.B ? cu[tid] : 0, first_e = tid < a.B ? cu[tid + 1] : 0;
+  const int cu_first = cu[0], cu_last = cu[a.B];
+  auto document = [&](int b, int& s, int& e) {   // b = tid + a multiple of kPlanThreads
+    s = first_s; e = first_e;
+    if (b >= kPlanThreads) { s = b < a.B ? cu[b] : 0; e = b < a.B ? cu[b + 1] : 0; }
+  };
   if (tid == 0) {
-    bad = (cu[0] != 0) || (cu[a.B] != a.N);
+    bad = cu_first != 0 || cu_last != a.N;
     pairs = steps[0] = steps[1] = 0;
     n_tiles = max_chain = 0;
   }
-  if (tid < 3) split[tid] = n_units[tid] = n_slots[tid] = n_comb[tid] = 0;
+  if (tid < 3) n_units[tid] = n_slots[tid] = n_comb[tid] = 0;
   __syncthreads();
   // ---- totals over the documents: pairs, steps of both directions, tiles, longest chains
   {
@@ -251,8 +327,9 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
     int my_bad = 0, my_tiles = 0, my_max = 0;
 #pragma unroll 1
     for (int b = tid; b < a.B; b += kPlanThreads) {
-      const int end = cu[b + 1];
-      const long long l = (long long)end - cu[b];
+      int begin, end;
+      document(b, begin, end);
+      const long long l = (long long)end - begin;
       if (a.B <= kSelfPlanDocs && a.N <= 0xFFFF) kept_ends(a.hdr)[b] = (uint16_t)end;   // by thread b, which may take it back
       if (l < 0) { my_bad = 1; continue; }
       my_pairs += (unsigned long long)(l * (l + 1) / 2);
@@ -263,46 +340,108 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
       my_max = max(my_max, (int)S);
     }
     if (my_bad) bad = 1;
-    if (my_pairs) {
-      atomicAdd(&pairs, my_pairs); atomicAdd(&steps[0], my_r); atomicAdd(&steps[1], my_c);
-      atomicAdd(&n_tiles, my_tiles);
-      atomicMax(&max_chain, my_max);   // the longest row and column chains are both ceil(l / 64)
+    // one lane of a wave adds for all: same-address atomics of single lanes would run one by one
+    if (64 * wave < a.B) {
+      const int tiles = wave_total(my_tiles);
+      my_max = wave_max(my_max);
+      if (kOrdered) {   // at most 32768 tokens: 32 bits hold every sum
+        my_pairs = (unsigned)wave_total((int)my_pairs); my_r = (unsigned)wave_total((int)my_r); my_c = (unsigned)wave_total((int)my_c);
+      } else {
+        my_pairs = wave_total_wide(my_pairs); my_r = wave_total_wide(my_r); my_c = wave_total_wide(my_c);
+      }
+      if (lane == 0 && tiles) {
+        atomicAdd(&pairs, my_pairs); atomicAdd(&steps[0], my_r); atomicAdd(&steps[1], my_c);
+        atomicAdd(&n_tiles, tiles);
+        atomicMax(&max_chain, my_max);   // the longest row and column chains are both ceil(l / 64)
+      }
     }
   }
   __syncthreads();
   varlen_attn_plan_header* hdr = a.hdr;
-  if (bad) {
+  if (bad || a.directions == 0) {
     if (tid < (int)(sizeof(varlen_attn_plan_header) / 4)) reinterpret_cast<int32_t*>(hdr)[tid] = 0;
-    if (tid < kSelfPlanDocs) kept_ends(hdr)[tid] = 0;
+    if (bad && tid < kSelfPlanDocs) kept_ends(hdr)[tid] = 0;
     __syncthreads();
     if (tid == 0) {
-      hdr->status = VARLEN_ATTN_BAD_CU_SEQLENS;
-      if (a.status_copy) *a.status_copy = VARLEN_ATTN_BAD_CU_SEQLENS;
+      const int32_t status = bad ? VARLEN_ATTN_BAD_CU_SEQLENS : VARLEN_ATTN_OK;
+      hdr->status = status;
+      if (a.status_copy) *a.status_copy = status;
     }
     return;
   }
-  int ch[3] = {kNoSplitSteps, kNoSplitSteps, kNoSplitSteps};
+  int ch[3] = {kNoSplitSteps, kNoSplitSteps, kNoSplitSteps}, line[3] = {0, 0, 0};
+  int tries[3] = {0, 0, 0};
   if (!a.no_split) {
 #pragma unroll
-    for (int d = 0; d < 2; ++d) ch[d] = plan_chunk_steps(d, steps[d], n_tiles, a.Hq, a.force_ch[d]);
+    for (int d = 0; d < 2; ++d) ch[d] = plan_chunk_steps(a.rule[d], (float)steps[d], n_tiles, a.Hq, a.force_ch[d], line[d], tries[d]);
     ch[2] = plan_dq_steps(steps, a.Hq, ch[0], a.force_ch[0]);
   }
-  // Grouped-query attention: a column unit may sweep several q heads of its group (their dK,
-  // dV add up in its registers: fewer and smaller group sums afterwards) as long as enough
-  // workgroups remain.  Units of one head ~ steps / ch + tiles / 2.
+  // Grouped-query attention: a column unit may sweep several q heads of its group (their dK, dV add up in its
+  // registers: fewer and smaller group sums afterwards, none for a tile whose units sweep the whole group) as long as
+  // enough units remain and the longest does not outlast the rest.
   int hpu = 1;
   if (a.g > 1) {
     if (a.force_hpu > 0 && a.g % a.force_hpu == 0) {
       hpu = a.force_hpu;
     } else if (!a.no_split) {   // unsplit plans must not depend on the rest of the microbatch
-      const long long groups = ((long long)steps[1] / ch[1] + n_tiles / 2) * a.Hq;
-      for (int cand = 2; cand <= a.g; ++cand)
-        if (a.g % cand == 0 && groups / cand >= kGroupSweepMinUnits) hpu = cand;
+      const int whole = ch[1];
+      const float col_steps = (float)steps[1], tiles = (float)n_tiles;
+      const float x = col_steps * (float)a.Hq, longest_unit = a.sweep.slope * x + a.sweep.base;
+      const float min_units = a.sweep.min_units + min(a.sweep.units * x, a.sweep.max_units);
+#pragma unroll 1
+      for (int cand = 2; cand <= a.g; ++cand) {
+        if (a.g % cand) continue;
+        const float shorter = (float)whole * __builtin_amdgcn_exp2f(-a.sweep.power * __builtin_amdgcn_logf((float)cand));
+        const int c = a.force_ch[1] > 0 ? whole : max(kMinChunkSteps, (int)ceilf(shorter));
+        // units of one head ~ steps / chunk + tiles / 2 (a cut chain rarely divides evenly)
+        const float units = max(tiles, col_steps * __builtin_amdgcn_rcpf((float)c) + 0.5f * tiles) * (float)(a.Hq / cand);
+        if (units >= min_units && (float)min(max_chain, c) * (float)cand <= longest_unit) { hpu = cand; ch[1] = c; }
+      }
     }
   }
   const int longest = max_chain;
 
-  // mode 0: count the units of every cost class (and the chunks of cut chains); mode 1: place.
+  // lengthen the chunks until the chunks of cut chains fit their slots
+  if (!a.no_split) {
+#pragma unroll 1
+    for (;;) {
+      if (tid < 4) chunks[tid] = 0;
+      __syncthreads();
+      auto count = [&](auto zero) {
+        decltype(zero) all[3] = {0, 0, 0}, cut[3] = {0, 0, 0};
+#pragma unroll 1
+        for (int b = tid; b < a.B; b += kPlanThreads) {
+          int s, e;
+          document(b, s, e);
+          const int T = (e - s + kTile - 1) / kTile, S = (e - s + kStep - 1) / kStep;
+          count_row_chunks(T, S, ch[0], all[0], cut[0]);
+          if (a.directions > 1) count_col_chunks(T, S, ch[1], all[1], cut[1]);
+          if (a.directions > 2) count_row_chunks(T, S, ch[2], all[2], cut[2]);
+        }
+        // past the slots it is enough to know how far, up to twice as many
+        auto add = [&](int i, decltype(zero) v) {
+          const int sum = wave_total((int)min(v, (decltype(zero))(1 << 20)));
+          if (lane == 0 && sum) atomicAdd(&chunks[i], sum);
+        };
+        if (64 * wave < a.B) {
+#pragma unroll
+          for (int d = 0; d < 3; ++d) add(d, cut[d]);
+          add(3, all[0]);
+        }
+      };
+      if (kOrdered || a.N <= (1 << 20)) count((int)0);   // no sum reaches 2^31
+      else count((long long)0);
+      __syncthreads();
+      bool again = false;
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+        if (next_chunk(ch[d], line[d], tries[d], (float)steps[0], chunks[d], a.slots_cap, chunks[3], a.rule[0].resident)) again = true;
+      if (!again) break;
+      __syncthreads();
+    }
+  }
+
+  // mode 0: count the units of every cost class; mode 1: place.
   int mode = 0, shift[3] = {0, 0, 0};
 #pragma unroll 1
   for (;;) {
@@ -314,7 +453,6 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
       }
       reinterpret_cast<int*>(hist)[tid] = 0;   // 2 x 32 x waves counters: one per thread
       if (tid < kPlanThreads / 2) reinterpret_cast<int*>(hist[2])[tid] = 0;
-      if (tid < 3) split[tid] = 0;
       __syncthreads();
     }
     int row_slots_before = 0;   // cut row chains' slots so far, in tile order (single-wave form)
@@ -322,9 +460,8 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
     for (int b0 = 0; b0 < a.B; b0 += kPlanThreads) {
       // ---- this batch's documents: running tile count (exclusive) by a workgroup-wide scan
       {
-        const int b = b0 + tid;
-        int s = 0, e = 0;
-        if (b < a.B) { s = cu[b]; e = cu[b + 1]; }
+        int s, e;
+        document(b0 + tid, s, e);
         const int T = (e - s + kTile - 1) / kTile;
         const int incl = wave_inclusive_sum(T);
         if (lane == 63) wave_sum[wave] = incl;
@@ -373,7 +510,7 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
         if (valid) {
 #pragma unroll
           for (int d = 0; d < 3; ++d) {
-            if (d == 2 && a.directions < 3) break;
+            if (d >= a.directions) break;
             const int n = n_d[d], nc = nc_d[d], base = n / nc, rem = n % nc;
             // nc - rem chunks of `base` steps, rem chunks of base + 1 (those come first in the chain)
             int* h_lo = &hist[d][(base - 1) >> shift[d]][wave];
@@ -381,7 +518,6 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
             if (mode == 0) {
               atomicAdd(h_lo, nc - rem);
               if (rem) atomicAdd(h_hi, rem);
-              if (nc > 1) atomicAdd(&split[d], nc);
             } else {
               int slot0 = -1;
               if (nc > 1 || (d == 1 && a.g > hpu)) {
@@ -408,17 +544,9 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
       __syncthreads();   // the batch arrays are rewritten by the next batch
     }
     if (mode == 1) break;
-    // lengthen the chunks until the cut chains fit their slots
-    const bool fit0 = split[0] <= a.slots_cap, fit1 = split[1] <= a.slots_cap, fit2 = split[2] <= a.slots_cap;
-    if (!(fit0 && fit1 && fit2)) {
-      __syncthreads();
-      if (!fit0) ch[0] *= 2;
-      if (!fit1) ch[1] *= 2;
-      if (!fit2) ch[2] *= 2;
-      continue;
-    }
     // counters -> start positions: classes from the longest down, waves in order inside a class
-    auto to_starts = [&](int d, bool active) {
+    // (`lo`, `hi`: directions of lanes 0 .. 31 and 32 .. 63 where all classes are summed up)
+    auto to_starts = [&](int d, int lo, int hi, bool active) {
       const int cls = (tid / kPlanWaves) % kPlanClasses, w = tid % kPlanWaves;
       const int own = hist[d][cls][w];
       int incl = own;   // inclusive sum over the 16 waves of this class (16 adjacent lanes)
@@ -429,16 +557,17 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
       }
       if (active && w == kPlanWaves - 1) class_total[d][cls] = incl;
       __syncthreads();
-      int above = 0;
-#pragma unroll 1
-      for (int c2 = cls + 1; c2 < kPlanClasses; ++c2) above += class_total[d][c2];
+      const int total = class_total[lane < 32 ? lo : hi][kPlanClasses - 1 - (lane & 31)];   // longest class first
+      int longer = wave_inclusive_sum(total);
+      const int first_half = lane_value(longer, 31);
+      longer -= total + (lane < 32 ? 0 : first_half);
+      const int above = __shfl(longer, kPlanClasses - 1 - cls + (d == lo ? 0 : 32));
       if (active && cls == 0 && w == kPlanWaves - 1) n_units[d] = above + incl;
-      __syncthreads();
       if (active) hist[d][cls][w] = above + incl - own;
       __syncthreads();
     };
-    to_starts(tid / (kPlanClasses * kPlanWaves), true);
-    if (a.directions > 2) to_starts(2, tid < kPlanClasses * kPlanWaves);
+    to_starts(tid / (kPlanClasses * kPlanWaves), 0, 1, true);
+    if (a.directions > 2) to_starts(2, 2, 2, tid < kPlanClasses * kPlanWaves);
     mode = 1;
   }
   // The capacities are worst-case bounds (tiles <= N / 128 + B; a cut chain of n > ch steps

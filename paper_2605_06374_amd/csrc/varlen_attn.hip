@@ -205,6 +205,32 @@ inline long long tile_heads(const varlen_attn_params* p) {
 
 bool pooled_backward(const varlen_attn_params* p);
 
+// Chunk lengths (plan.hpp).  Short chunks balance, long ones spare prologues and partial results; where the best length lies
+// was measured by forcing it (230 microbatches of 1 K to 65 K tokens, 5 to 25 lengths each), and the two lines are fits to
+// those times, one pair for each kernel.  Against one round of resident workgroups, or else 512 units, on the same microbatches
+// (geometric means; slowest in brackets): forward 1.048 times as fast at heads of 128 (0.97), 1.049 at 64 (0.96); dQ at 64 1.031;
+// the backward with column chunks so chosen 1.072 at 128 in the pool (0.96), 1.040 at 64 (0.97).  With grouped queries, chunk
+// length and heads a unit together (130 microbatches, all combinations): 1.073 in the pool (0.98), 1.148 in two kernels at
+// 128, 1.078 at 64 (0.99).  The best length of each single microbatch would add 1 to 3 %.
+// A forward whose units just miss one round loses up to half: 19038 tokens in 14 documents, one head of 64, 38.0 us with 508
+// units and 69.9 with 552, hence the exact count.  A unit that sweeps a group of 8 and outlasts the rest is what the line for the
+// longest unit is there for: 20406 tokens, 8 q heads on one kv head, 1.54 times the best without it.
+void chunk_rules(const varlen_attn_params* p, PlanArgs* a) {
+  const bool grouped = p->num_q_heads > p->num_kv_heads, pooled = pooled_backward(p);
+  const int resident = kResidentGroups / p->num_q_heads;
+  constexpr float kSlot = 1.f / kTargetUnits;   // slopes: against what falls to one of kTargetUnits (unit, head) slots
+  if (p->head_dim == 64) {
+    a->rule[0] = ChunkRule{0.875f * kSlot, 3, 0.875f * kSlot, 3, resident, kMinChunkSteps};
+    a->rule[1] = grouped ? ChunkRule{1.15f * kSlot, 2, kSlot, 18, 0, 0} : ChunkRule{1.15f * kSlot, 3, kSlot, 11, 0, 0};
+    a->sweep = SweepRule{0.75f, 512, 0, 0, kSlot, 32};   // two workgroups share a compute unit: more units are wanted
+    return;
+  }
+  a->rule[0] = ChunkRule{1.3125f * kSlot, 3, kSlot, 19, resident, kMinChunkSteps + 1};
+  a->rule[1] = !pooled ? ChunkRule{2.5f * kSlot, 2, kSlot, 18, 0, 0}
+               : grouped ? ChunkRule{2.5f * kSlot, 2, 1.6f * kSlot, 26, 0, 0} : ChunkRule{3 * kSlot, 3, 1.6f * kSlot, 27, 0, 0};
+  a->sweep = pooled ? SweepRule{0.75f, 128, 3 * kSlot, 200, 2.5f * kSlot, 32} : SweepRule{1, 160, 0, 0, 2 * kSlot, 8};
+}
+
 PlanArgs plan_args(const varlen_attn_params* p, const int32_t* cu, const Regions& R,
                    const varlen_attn_workspace_layout& L, int slots_cap, int32_t* status_copy) {
   PlanArgs a;
@@ -220,6 +246,7 @@ PlanArgs plan_args(const varlen_attn_params* p, const int32_t* cu, const Regions
   a.max_slots[0] = a.max_slots[2] = L.max_row_slots; a.max_slots[1] = L.max_col_slots; a.slots_cap = slots_cap;
   a.directions = pooled_backward(p) ? 3 : 2;
   a.longest_first = tile_heads(p) > kResidentGroups;
+  chunk_rules(p, &a);
   a.status_copy = status_copy;
   return a;
 }
@@ -509,7 +536,9 @@ int varlen_attn_fwd_static(const varlen_attn_params* params, const void* q, cons
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const Regions R = regions_of(static_cast<char*>(ws), L);
   PlanArgs args = plan_args(params, cu_seqlens, R, L, cap, plan_status);
-  args.directions = 2;   // no backward follows, and the array ends in front of a third list
+  // No backward follows (and the array ends in front of a third list).  The short kernels take their tiles from the documents: only
+  // the status word is wanted (889 tokens in one document, 16 q heads of 64: 8.5 us, 9.4 with a plan that nobody reads).
+  args.directions = short_path(params, false) ? 0 : 1;
   const bool self_plan = self_planned_forward(params);
   if (!self_plan) rc = launch_plan(params, args, stream);
   if (rc != VARLEN_ATTN_OK) return rc;

@@ -914,3 +914,38 @@ def test_uncut_bits_do_not_depend_on_the_pack(gpu):
         for other in bits[1:]:
             for n in bits[0]:
                 assert np.array_equal(bits[0][n], other[n]), (n, hq, hkv, d)
+
+
+# ------------------------------------------------------------------ chunk lengths
+@pytest.mark.parametrize("lengths,hq,hkv,d", [
+    ([6912], 4, 4, 128),                               # one chain set, one round of workgroups within reach
+    ([13000, 2222], 2, 1, 128), ([19038 - 13 * 80] + [80] * 13, 1, 1, 64),   # a length that has to grow to get there
+    ([4000] * 4, 4, 4, 128),                           # more tiles than one round: the slots bind
+    ([63, 64, 65, 127, 128, 129, 0, 1] * 8, 8, 8, 128), ([1] * 64, 6, 3, 64),
+    ([9000, 300, 31], 8, 1, 128), ([700] * 13, 16, 4, 64), ([2500, 700], 12, 4, 64), ([300] * 200, 2, 1, 64)])
+def test_chunk_lengths_keep_their_bounds(gpu, lengths, hq, hkv, d):
+    """Both planners choose the same chunk lengths; every tile's chain is cut into as many chunks as its length
+    asks for, all cut chains fit their slots, and a forward that works its units out has the plan's bits."""
+    from paper_2605_06374_amd import binding
+    w = W.custom("chunks", lengths, hq, hkv, d, seed=len(lengths) + hq)
+    seen = []
+    for flags in (0, binding.FLAG_PLAN_LARGE):
+        prob = gpu.DeviceProblem(w, flags=flags)
+        prob.plan()
+        plan = _check_plan(prob, w, False)
+        hdr, L = plan["header"], plan["layout"]
+        for units, ch in ((plan["row_units"], hdr.row_chunk_steps), (plan["col_units"], hdr.col_chunk_steps)):
+            assert ch >= 4 and int(units[:, 6].max()) <= ch
+            chain = {}
+            for r0, _, e, _, _, _, cost, _ in units.tolist():
+                n, k = chain.get((r0, e), (0, 0))
+                chain[(r0, e)] = (n + cost, k + 1)
+            assert all(k == -(-n // ch) for n, k in chain.values())
+            assert sum(k for _, k in chain.values() if k > 1) <= L.max_row_slots
+        seen.append((hdr.row_chunk_steps, hdr.col_chunk_steps, hdr.col_heads_per_unit, len(plan["row_units"]), len(plan["col_units"])))
+    assert seen[0] == seen[1]
+    general = binding.FLAG_GENERAL
+    a = run_all(gpu, w, flags=general).result_bits()
+    b = run_all(gpu, w, flags=general | binding.FLAG_PLAN_FIRST).result_bits()
+    for n in ("o", "lse"):
+        assert np.array_equal(a[n], b[n]), n
