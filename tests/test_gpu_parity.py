@@ -871,7 +871,7 @@ def test_overlap_and_atomic_probes_run(gpu):
 @pytest.mark.parametrize("chunks", ["plan", "one_step", "sweeps", "uncut"])
 @pytest.mark.parametrize("lengths,hq,hkv", [
     ([1700], 1, 1), ([1, 127, 128, 129, 0, 63, 64, 65, 1800], 2, 2), ([1200, 700, 31, 33, 600], 3, 1),
-    ([257] * 9, 8, 1), ([640, 320, 961], 16, 4), ([2049, 5], 6, 3), ([129] * 70, 1, 1), ([900, 1600], 12, 4)])
+    ([257] * 9, 8, 1), ([640, 320, 961], 16, 4), ([2049, 5], 6, 3), ([129] * 70, 1, 1), ([900, 1600], 12, 4), ([150, 1, 260] * 12, 16, 4)])
 def test_pooled_backward(gpu, lengths, hq, hkv, chunks):
     """Heads of 128 beyond the small microbatches: tiles of 1, 127, 128 and 129 rows, units of one stage, every way
     the heads are dealt to ticket counters (divisors of 8, multiples of 8, neither), several heads a column unit,
