@@ -24,7 +24,7 @@ namespace {
 // the same-address atomics of a wave stay inside the wave, and two sweeps over the tiles
 // (count, then place) that run the same code.
 // ----------------------------------------------------------------------------------------
-constexpr int kPlanThreadsLarge = 1024;   // general form
+constexpr int kPlanThreadsLarge = 1024;   // general form (also built for 256 and 512: launch_plan)
 constexpr int kPlanThreadsSmall = 64;     // one wave: every barrier is free, nothing is shared between waves
 constexpr int kPlanClasses = 32;
 constexpr int kMinChunkSteps = 4;
@@ -549,7 +549,7 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
     auto to_starts = [&](int d, int lo, int hi, bool active) {
       const int cls = (tid / kPlanWaves) % kPlanClasses, w = tid % kPlanWaves;
       const int own = hist[d][cls][w];
-      int incl = own;   // inclusive sum over the 16 waves of this class (16 adjacent lanes)
+      int incl = own;   // inclusive sum over the waves of this class (adjacent lanes)
 #pragma unroll
       for (int off = 1; off < kPlanWaves; off <<= 1) {
         const int o = __shfl_up(incl, off);

@@ -922,7 +922,8 @@ def test_uncut_bits_do_not_depend_on_the_pack(gpu):
     ([13000, 2222], 2, 1, 128), ([19038 - 13 * 80] + [80] * 13, 1, 1, 64),   # a length that has to grow to get there
     ([4000] * 4, 4, 4, 128),                           # more tiles than one round: the slots bind
     ([63, 64, 65, 127, 128, 129, 0, 1] * 8, 8, 8, 128), ([1] * 64, 6, 3, 64),
-    ([9000, 300, 31], 8, 1, 128), ([700] * 13, 16, 4, 64), ([2500, 700], 12, 4, 64), ([300] * 200, 2, 1, 64)])
+    ([9000, 300, 31], 8, 1, 128), ([700] * 13, 16, 4, 64), ([2500, 700], 12, 4, 64), ([300] * 200, 2, 1, 64),
+    ([40, 0] * 129, 2, 2, 128), ([1] * 320, 2, 2, 64), ([1, 200] * 200, 1, 1, 64), ([2] * 768, 1, 1, 128), ([2, 1] * 385, 1, 1, 64)])   # sizes of the plan kernel
 def test_chunk_lengths_keep_their_bounds(gpu, lengths, hq, hkv, d):
     """Both planners choose the same chunk lengths; every tile's chain is cut into as many chunks as its length
     asks for, all cut chains fit their slots, and a forward that works its units out has the plan's bits."""
