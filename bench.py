@@ -305,7 +305,7 @@ def main() -> int:
         "config": {"workload": w.name, "tokens": w.n_tokens, "docs": len(w.lengths),
                    "q_heads": w.n_q_heads, "kv_heads": w.n_kv_heads, "head_dim": w.head_dim,
                    "pairs": w.pairs, "flops_per_step": flops, "buffer_sets": len(probs),
-                   "step": "plan + fwd + bwd", "backward": "single kernel" if args.fused_bwd else "two kernels"},
+                   "step": "plan + fwd + bwd", "backward": "single kernel" if args.fused_bwd else "split, deterministic"},
         "frac_of_bf16_peak": round(tflops / PEAK_BF16_TFLOPS, 4),
         "algorithmic_GBps": round(w.algorithmic_bytes / sec_per_step / 1e9, 1),
         "roofline": roofline,
