@@ -160,10 +160,12 @@ __device__ __forceinline__ bool next_chunk(int& ch, int line, int& tries, float 
 
 // Chunk length of a dQ with units of its own: the backward's resident workgroups draw column units and dQ units from one
 // pool, so that a chain is cut only where it would outlast the rest: half of a workgroup's share, a column step
-// counted as two (it takes 1.9 times as long).
-__device__ __forceinline__ int plan_dq_steps(const unsigned long long* steps, int Hq, int row_steps, int forced) {
-  const long long share = (long long)(((steps[0] + 2 * steps[1]) * Hq + kTargetUnits - 1) / kTargetUnits);
-  return forced > 0 ? forced : (int)max((long long)row_steps, share);
+// counted as two (it takes 1.9 times as long).  From about 77 million tokens in one document the share is beyond 31 bits; it
+// has the bound of a ChunkRule's lines (a chunk length below 1 would divide by zero where chains are cut).
+__host__ __device__ __forceinline__ int plan_dq_steps(const unsigned long long* steps, int Hq, int row_steps, int forced) {
+  if (forced > 0) return forced;
+  const unsigned long long share = ((steps[0] + 2 * steps[1]) * Hq + kTargetUnits - 1) / kTargetUnits;
+  return share >= (unsigned long long)kNoSplitSteps ? kNoSplitSteps : (int)share > row_steps ? (int)share : row_steps;
 }
 
 // sum, maximum and 64-bit sum over the lanes of a wave (all lanes get it)

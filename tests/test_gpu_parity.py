@@ -950,3 +950,21 @@ def test_chunk_lengths_keep_their_bounds(gpu, lengths, hq, hkv, d):
     b = run_all(gpu, w, flags=general | binding.FLAG_PLAN_FIRST).result_bits()
     for n in ("o", "lse"):
         assert np.array_equal(a[n], b[n]), n
+
+
+def test_plan_of_a_document_of_67_million_tokens(gpu):
+    """The largest chains by far: no chunk length may wrap around, in any of the three lists (the plan alone; the
+    arithmetic itself is checked on the host in test_plan_arithmetic.py)."""
+    import ctypes
+    import torch
+    from paper_2605_06374_amd import binding
+    tokens = 1 << 26
+    params = binding.make_params(tokens, 1, 2, 2, 128, 0.1)
+    workspace = torch.empty(binding.varlen_attn_workspace_bytes(params), dtype=torch.uint8, device="cuda:0")
+    cu = torch.tensor([0, tokens], dtype=torch.int32, device="cuda:0")
+    binding.check(binding.varlen_attn_plan(params, cu, workspace))
+    assert binding.varlen_attn_check(workspace) == binding.OK
+    hdr = binding.PlanHeader.from_buffer_copy(workspace[:ctypes.sizeof(binding.PlanHeader)].cpu().numpy().tobytes())
+    tiles = tokens // 128
+    assert hdr.n_row_units == hdr.n_col_units == hdr.n_dq_units == tiles and hdr.n_dq_combine == 0
+    assert hdr.row_chunk_steps >= 2 * tiles and hdr.pairs == tokens * (tokens + 1) // 2

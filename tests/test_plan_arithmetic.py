@@ -1,0 +1,52 @@
+"""The plan's arithmetic that needs no GPU, compiled for the host: the same functions, out of the same header."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2605_06374_amd import build
+
+HARNESS = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "plan.hpp"
+int main(int argc, char** argv) {   // steps of rows, of columns, q heads, length of the row chunks, forced length
+  for (int i = 1; i + 4 < argc; i += 5) {
+    const unsigned long long steps[2] = {strtoull(argv[i], nullptr, 10), strtoull(argv[i + 1], nullptr, 10)};
+    printf("%d\n", plan_dq_steps(steps, atoi(argv[i + 2]), atoi(argv[i + 3]), atoi(argv[i + 4])));
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def dq_steps(tmp_path_factory):
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("needs the HIP compiler")
+    where = tmp_path_factory.mktemp("plan")
+    src, exe = where / "harness.hip", where / "harness"
+    src.write_text(HARNESS)
+    subprocess.run([build.HIPCC, "--cuda-host-only", "-O1", "-std=c++17", "-I" + os.path.join(build.ROOT, "include"),
+                    "-I" + os.path.dirname(build.SRC), "-o", str(exe), str(src)], check=True, capture_output=True)
+
+    def call(cases):
+        out = subprocess.run([str(exe)] + [str(x) for c in cases for x in c], check=True, capture_output=True, text=True)
+        return [int(x) for x in out.stdout.split()]
+    return call
+
+
+def test_dq_chunk_length_stays_in_range(dq_steps):
+    """One document of N tokens has T = N / 128 tiles, T (T + 1) steps in rows and in columns.  From about 77 million tokens
+    on one head the share of a workgroup (3 T^2 Hq / 512 steps) is beyond 31 bits: it is an upper bound on a chunk,
+    so that any length beyond the longest chain means the same, and none may be negative."""
+    cases = []
+    for tokens in (1 << 10, 1 << 14, 1 << 20, 1 << 24, 1 << 25, 77_000_000, 1 << 26, 1 << 28, (1 << 31) - 128):
+        t = tokens // 128
+        for heads in (1, 2, 8, 48):
+            for row in (4, 1 << 20, 1 << 28):
+                cases.append((t * (t + 1), t * (t + 1), heads, row, 0))
+    for case, got in zip(cases, dq_steps(cases)):
+        rows, cols, heads, row, _ = case
+        want = max(row, -(-(rows + 2 * cols) * heads // 512))
+        assert got == min(want, 1 << 28), (case, got)
+    assert dq_steps([(1 << 60, 1 << 60, 2, 9, 7)]) == [7]
