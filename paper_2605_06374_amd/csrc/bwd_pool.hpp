@@ -247,16 +247,20 @@ struct DqUnit {
     });
     wait_vm<0>();
     __syncthreads();
+    // A wave's only masked stage holds the diagonal, of an even wave in its first block: the second, above it, is left out, not
+    // multiplied by zeros, so that an infinity or NaN in K or V reaches dQ of the 31 rows in front of its token at most, as in
+    // bwd_dq_kernel.  (By the matrix instruction: with the whole phase left out packs of short documents take 1 % longer, and
+    // with a stage of one block as a third form longer chains up to 2 %.)
     static_for<2 * DB>([&](auto j_c) {
       constexpr int j = decltype(j_c)::value;
-      acc[j % DB] = mfma(tk1[j / DB][j % DB], dsb1[j / DB], acc[j % DB]);
+      if (!MASKED || (wave & 1)) acc[j % DB] = mfma(tk1[j / DB][j % DB], dsb1[j / DB], acc[j % DB]);
       ka[j] = lds_read_frag(smem + (1 - ST) * kStage, fo.row_frag[j]);
       va[j] = lds_read_frag(smem + (3 - ST) * kStage, fo.row_frag[j]);
       __builtin_amdgcn_sched_barrier(0);
     });
   };
-  // steps that hold a key for this wave: all but the last ones of the diagonal
-  const int my_steps = wave_active ? min(n_steps, (wave_last_row - kv_first) / kStep + 1) : 0;
+  // steps that hold a key for this wave: all but the last ones of the diagonal (none where the chunk begins behind its rows)
+  const int my_steps = wave_active ? min(n_steps, (wave_last_row - kv_first + kStep) / kStep) : 0;
   int st = 0;
   if (n_steps == 1) tickets.step(0);
   auto to_next = [&]() __attribute__((always_inline)) {   // the last step requests its own stage again (nobody reads it)

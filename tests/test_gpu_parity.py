@@ -892,6 +892,34 @@ def test_pooled_backward(gpu, lengths, hq, hkv, chunks):
         assert np.array_equal(bits[n], again[n]), n
 
 
+@pytest.mark.parametrize("name,lengths,hq,hkv,d", [("pool", [1500, 700], 2, 2, 128), ("pool", [1990, 31], 4, 2, 128),
+                                                   ("two", [1500, 700], 2, 2, 64), ("small", [700, 300], 2, 2, 128)])
+@pytest.mark.parametrize("chunks", ["plan", "one_step", "uncut"])
+def test_reach_of_non_finite_keys_inside_a_document(gpu, chunks, name, lengths, hq, hkv, d):
+    """An infinity in K or a NaN in V at token j of a document: O and dQ of the rows in front of the block of 32 tokens
+    that holds j stay bit for bit what they are without it, however the chains are cut (a masked element multiplied by
+    zero instead of left out would carry it further up)."""
+    from paper_2605_06374_amd import binding
+    flags = {"plan": 0, "one_step": binding.flag_chunk_steps(1, 1), "uncut": binding.FLAG_NO_SPLIT}[chunks]
+    w = W.custom("reach", lengths, hq, hkv, d, seed=sum(lengths) + hq + d)
+    prob = gpu.DeviceProblem(w, flags=flags)
+    names = launched(lambda: (prob.forward(), prob.backward(reuse_plan=True)))
+    if name == "pool":
+        assert "bwd_prep_kernel" in names and "bwd_dq_kernel" not in names
+    want = prob.result_bits()
+    vals = w.values()
+    for j in (33, 64 + 63, 128 + 95, 256 + 127, 512 + 32, lengths[0] - 1):
+        for tensor, value in (("k", 0x7F80), ("v", 0x7FC0)):
+            bad = dict(vals)
+            bad[tensor] = vals[tensor].copy()
+            bad[tensor][j] = value
+            got = run_all(gpu, w, values=bad, flags=flags).result_bits()
+            keep = np.ones(sum(lengths), dtype=bool)
+            keep[j // 32 * 32:lengths[0]] = False
+            for n in ("o", "dq"):
+                assert np.array_equal(got[n][keep], want[n][keep]), (n, j, tensor)
+
+
 def test_uncut_bits_do_not_depend_on_the_pack(gpu):
     """VARLEN_ATTN_FLAG_NO_SPLIT: a document alone, among a few and in a large pack of short ones (sizes that
     take different routes otherwise) has the same bits."""
