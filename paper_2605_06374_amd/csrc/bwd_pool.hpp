@@ -104,7 +104,7 @@ struct BwdArgs {
   const __bf16 *q, *k, *v, *d_o;
   const float *neg_lse, *neg_dsum;
   const varlen_attn_plan_header* hdr;
-  const varlen_attn_unit *col_units, *dq_units;
+  const varlen_attn_unit *col_units, *dq_units, *row_units;
   __bf16 *dq, *dk, *dv;
   float *col_partials, *row_partials;
   int N, Hq, Hkv;
@@ -551,7 +551,11 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_pool_kernel(BwdArgs<D> a) {
   __shared__ __attribute__((aligned(1024))) char smem[BwdLds<D>::kBytes];
   __shared__ __attribute__((aligned(1024))) char out_tiles[4 * RowTile<D>::kBytes];
   __shared__ int ticket;
-  const int hpu = a.hdr->col_heads_per_unit, n_col = a.hdr->n_col_units, n_dq = a.hdr->n_dq_units;
+  const int hpu = a.hdr->col_heads_per_unit, n_col = a.hdr->n_col_units;
+  // a plan that was made for two kernels has no dQ units of its own: the row units
+  const bool own_dq = a.hdr->n_dq_units > 0;
+  const int n_dq = own_dq ? a.hdr->n_dq_units : a.hdr->n_row_units;
+  const varlen_attn_unit* const dq_units = own_dq ? a.dq_units : a.row_units;
   if (n_col == 0) return;   // nothing planned
   TicketGroup g;
   g.init(blockIdx.x, gridDim.x, a.Hq, hpu, n_col, n_dq);
@@ -587,7 +591,7 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_pool_kernel(BwdArgs<D> a) {
     }
     if (t >= g.total) return;
   }
-  row.open(a, load_unit(a.dq_units, unit), head, smem);
+  row.open(a, load_unit(dq_units, unit), head, smem);
   f32x16 acc[D / 32];
 #pragma unroll 1
   for (;;) {
@@ -598,7 +602,7 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_pool_kernel(BwdArgs<D> a) {
     t = g.members + tickets.take();
     if (t < g.total) {
       g.decode(t, unit, head);
-      row.open(a, load_unit(a.dq_units, unit), head, smem);
+      row.open(a, load_unit(dq_units, unit), head, smem);
     }
     store_dq<D>(a, done, done_head, tile, acc);
     if (t >= g.total) break;

@@ -408,7 +408,7 @@ void launch_bwd(const varlen_attn_params* p, const void* q, const void* k, const
         ScopedKernelTimer timer(kDkv, stream);   // dK, dV and dQ
         bwd_pool_kernel<D><<<dim3(kPoolGroups), kThreads, 0, stream>>>(
             BwdArgs<D>{(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)d_o, neg_lse, R.dsum, R.hdr, R.col_units,
-                       R.dq_units, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, R.col_part, R.row_part, N, Hq, Hkv, scale, tickets});
+                       R.dq_units, R.row_units, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, R.col_part, R.row_part, N, Hq, Hkv, scale, tickets});
       }
       if (split || Hq != Hkv) {
         const int dq_items = split ? cut_tiles : 0;

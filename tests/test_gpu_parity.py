@@ -920,6 +920,22 @@ def test_reach_of_non_finite_keys_inside_a_document(gpu, chunks, name, lengths, 
                 assert np.array_equal(got[n][keep], want[n][keep]), (n, j, tensor)
 
 
+@pytest.mark.parametrize("lengths,hq,hkv,uncut_plan", [([1500, 700, 40], 8, 2, True), ([40] * 100, 8, 8, False)])
+def test_pooled_backward_on_a_plan_without_dq_units(gpu, lengths, hq, hkv, uncut_plan):
+    """A plan made for the two kernels (n_dq_units = 0: the row units) under a backward that goes to the pool, because
+    one of them was called with VARLEN_ATTN_FLAG_NO_SPLIT and the other without; no chain is cut in either."""
+    from paper_2605_06374_amd import binding
+    w = W.custom("mixed", lengths, hq, hkv, 128, seed=sum(lengths))
+    prob = gpu.DeviceProblem(w, flags=binding.FLAG_NO_SPLIT if uncut_plan else 0)
+    prob.poison_outputs()
+    prob.forward()
+    hdr = prob.read_plan()["header"]
+    assert hdr.n_dq_units == 0 and hdr.n_row_combine == 0
+    prob.params.flags ^= binding.FLAG_NO_SPLIT
+    assert "bwd_dq_kernel" not in launched(lambda: prob.backward(reuse_plan=True))
+    assert_close_full(prob.results(), oracle_full(w), f"mixed {lengths[:3]} {hq}/{hkv}")
+
+
 def test_uncut_bits_do_not_depend_on_the_pack(gpu):
     """VARLEN_ATTN_FLAG_NO_SPLIT: a document alone, among a few and in a large pack of short ones (sizes that
     take different routes otherwise) has the same bits."""
