@@ -142,6 +142,11 @@ __device__ __forceinline__ void count_col_chunks(int T, int S, int ch, Int& all,
   if (T > 0) count_chunks<Int>(T, ch, S & 1, all, cut);
 }
 
+// At most `room` chunks of `ch` steps, without a count?  A chain of n steps has fewer than n / ch + 1.
+__device__ __forceinline__ bool surely_fits(float steps, int n_tiles, int ch, int room) {
+  return steps * __builtin_amdgcn_rcpf((float)ch) + 0.01f <= (float)(room - n_tiles);
+}
+
 // Another turn with a longer chunk?  `cut` chunks of cut chains have `slots`, `all` units one round of `resident`.
 __device__ __forceinline__ bool next_chunk(int& ch, int line, int& tries, float steps, int cut, int slots, int all, int resident) {
 #pragma clang fp contract(off)
@@ -170,10 +175,14 @@ __host__ __device__ __forceinline__ int plan_dq_steps(const unsigned long long* 
 
 // sum, maximum and 64-bit sum over the lanes of a wave (all lanes get it)
 __device__ __forceinline__ int wave_total(int v) { return lane_value(wave_inclusive_sum(v), 63); }
-__device__ __forceinline__ int wave_max(int v) {
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) v = max(v, __shfl_xor(v, off));
-  return v;
+__device__ __forceinline__ int wave_max(int v) {   // v >= 0
+  v = max(v, dpp_or_zero<0x111, 0xF>(v));
+  v = max(v, dpp_or_zero<0x112, 0xF>(v));
+  v = max(v, dpp_or_zero<0x114, 0xF>(v));
+  v = max(v, dpp_or_zero<0x118, 0xF>(v));
+  v = max(v, dpp_or_zero<0x142, 0xA>(v));
+  v = max(v, dpp_or_zero<0x143, 0xC>(v));
+  return lane_value(v, 63);
 }
 __device__ __forceinline__ unsigned long long wave_total_wide(unsigned long long v) {
 #pragma unroll
@@ -403,8 +412,10 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
   }
   const int longest = max_chain;
 
-  // lengthen the chunks until the chunks of cut chains fit their slots
-  if (!a.no_split) {
+  // lengthen the chunks until the chunks of cut chains fit their slots; on most small microbatches they do as they are
+  bool fits = surely_fits((float)steps[0], n_tiles, ch[0], tries[0] ? min(a.slots_cap, a.rule[0].resident) : a.slots_cap);
+  if (a.directions > 1) fits = fits && surely_fits((float)steps[1], n_tiles, ch[1], a.slots_cap);   // (a dQ chunk is a row chunk or longer)
+  if (!a.no_split && !fits) {
 #pragma unroll 1
     for (;;) {
       if (tid < 4) chunks[tid] = 0;
