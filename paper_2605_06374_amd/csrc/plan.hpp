@@ -236,12 +236,12 @@ __device__ __forceinline__ bool derive_row_unit(const int32_t* __restrict__ cu, 
     }
   }
   // the chunk length grows until the chunks of cut chains fit their slots
+  bool again = !no_split && !surely_fits((float)steps, n_tiles, ch, tries ? min(slots_cap, rule.resident) : slots_cap);
 #pragma unroll 1
-  for (;;) {
+  while (again) {
     int cut = 0, all = 0;
-    if (!no_split) count_row_chunks<int>(T, S, ch, all, cut);
-    if (no_split) break;
-    if (!next_chunk(ch, line, tries, (float)steps, wave_total(cut), slots_cap, tries ? wave_total(all) : 0, rule.resident)) break;
+    count_row_chunks<int>(T, S, ch, all, cut);
+    again = next_chunk(ch, line, tries, (float)steps, wave_total(cut), slots_cap, tries ? wave_total(all) : 0, rule.resident);
   }
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) nc[r] = n[r] ? (n[r] + ch - 1) / ch : 0;
