@@ -301,13 +301,17 @@ inline bool short_path(const varlen_attn_params* p, bool backward) {
 // Backward with heads of 128, beyond the small microbatches: dQ units and column units as one pool (bwd_pool.hpp) or in
 // a kernel each.  The pool gains where chains differ in length and where the matrix pipe is the bound (one tail and
 // one set of prologues instead of two; dQ chains whole); it pays for a pass over dO and O in front of it, which the two kernels
-// do without.  Two kernels / pool over 150 packs (500 to 40000 tokens, 1 to 32 heads): 1.00 .. 1.38, 1.09 in the mean, with up to
-// 24000 rows (tokens x q heads) or documents of 128 tokens and more on average; 0.91 .. 1.09, 0.97 in the mean, with shorter ones.
-// With more than two q heads a kv head, documents of 128 to 400 tokens on average: 1.04 .. 1.72, 1.14 in the mean (45 packs), up to
-// 160000 rows; above, where the two kernels have column units enough that sweep whole groups, 0.85 .. 1.16 (13 packs).
-// (The host does not know the longest document.  Documents of equal length are the pool's
-// worst case inside the rule: 0.95 with 32 of 512 tokens, 4 heads.)  With VARLEN_ATTN_FLAG_NO_SPLIT a document's bits must
-// not depend on what else is in the pack, hence neither may the route: there the heads alone decide.
+// do without.  Two kernels / pool:
+//   documents of 128 tokens and more on average, or up to 24000 rows (tokens x q heads): 1.00 .. 1.38, 1.09 in the mean (150 packs
+//   of 500 to 40000 tokens, 1 to 32 heads); of these only shorter documents, measured again: 0.92 .. 1.63, 1.21 in the mean (63 packs);
+//   shorter ones, more rows: 0.91 .. 1.09, 0.97 in the mean;
+//   more than two q heads a kv head, documents of 128 to 400 tokens on average: 1.04 .. 1.72, 1.14 in the mean (45 packs), up to
+//   160000 rows; above, where the two kernels have column units enough that sweep whole groups, 0.85 .. 1.16 (13 packs).
+// (The host does not know the longest document.  Documents of equal length are the pool's worst case inside the rule: 0.95 with
+// 32 of 512 tokens, 4 heads; of up to 127 tokens 0.90 .. 1.38, 1.07 in the mean of 20 packs, where all chains are 1 or 2 steps.)
+// With VARLEN_ATTN_FLAG_NO_SPLIT a document's bits must not depend on what else is in the pack, hence neither may the route: there
+// the heads alone decide.  With at most two q heads a kv head, 160 uncut packs: 0.98 .. 2.04, 1.52 in the mean, up to 24000 rows, 0.93 .. 1.86,
+// 1.28 in the mean, up to 80000, and 0.87 .. 1.25, 0.98 in the mean, above.
 inline bool pooled_backward(const varlen_attn_params* p) {
   if (p->head_dim != 128) return false;
   const bool many_to_one = p->num_q_heads > 2 * p->num_kv_heads;
