@@ -1012,3 +1012,152 @@ def test_plan_of_a_document_of_67_million_tokens(gpu):
     tiles = tokens // 128
     assert hdr.n_row_units == hdr.n_col_units == hdr.n_dq_units == tiles and hdr.n_dq_combine == 0
     assert hdr.row_chunk_steps >= 2 * tiles and hdr.pairs == tokens * (tokens + 1) // 2
+
+
+# ------------------------------------------------------------------ what holds on every route holds in the pool
+POOL_SIZES = [([1500, 700, 64, 97, 1], 2, 2), ([1500, 700, 64, 97, 1], 4, 2), ([700, 1500, 131, 33], 4, 1)]   # beyond the small microbatches
+
+
+def run_pooled(gpu, w, values=None, flags=0):
+    """run_all, and the backward went to the pool."""
+    prob = run_all(gpu, w, values=values, flags=flags)
+    names = launched(lambda: prob.backward(reuse_plan=True))
+    assert "bwd_prep_kernel" in names and "bwd_dq_kernel" not in names and "bwd_short_kernel" not in names, names
+    return prob
+
+
+@pytest.mark.parametrize("lengths,hq,hkv", POOL_SIZES)
+@pytest.mark.parametrize("scale,magnitude", [(2.0 ** -126, 2.0 ** 60.5), (2.0 ** -121, 2.0 ** 58.5), (2.0 ** -119, 2.0 ** 57.5)])
+@pytest.mark.parametrize("mode", ["plan", "cut", "whole"])
+def test_pool_tiny_softmax_scales(gpu, mode, scale, magnitude, lengths, hq, hkv):
+    """test_tiny_softmax_scales in the pool, both sweeps of which fold the scale into Q or K below 2^-120."""
+    from paper_2605_06374_amd import binding
+    w = W.custom("tiny_scale", lengths, hq, hkv, 128, seed=hq)
+    w.__class__ = type("WS", (W.Workload,), {"softmax_scale": property(lambda self: scale)})
+    vals = w.values()
+    for n in ("q", "k"):
+        vals[n] = W.f32_to_bf16_bits(W.bf16_bits_to_f32(vals[n]) * np.float32(magnitude))
+    flags = {"plan": 0, "cut": binding.flag_chunk_steps(3, 3), "whole": binding.flag_chunk_steps(200, 200)}[mode]
+    prob = run_pooled(gpu, w, values=vals, flags=flags)
+    assert_close_full(prob.results(), oracle_full(w, vals), f"pool, scale {scale} {mode}")
+
+
+@pytest.mark.parametrize("lengths,hq,hkv", POOL_SIZES)
+def test_pool_scales_and_values(gpu, lengths, hq, hkv):
+    """Another scale, values four times larger (logits with a standard deviation of 16) and tiny ones; the row-wise bound as in
+    test_extreme_logit_ranges."""
+    for std, scale, widen in ((0.5, 0.21, 1.0), (4.0, None, 4.0), (0.01, None, 4.0)):
+        w = W.custom("values", lengths, hq, hkv, 128, std=std, seed=17)
+        if scale:
+            w.__class__ = type("WS", (W.Workload,), {"softmax_scale": property(lambda self: 0.21)})
+        assert_close_full(run_pooled(gpu, w).results(), oracle_full(w), f"pool, std {std}", row_tol_scale=widen)
+
+
+@pytest.mark.parametrize("lengths,hq,hkv", POOL_SIZES)
+def test_pool_writes_nothing_on_bad_cu_seqlens(gpu, lengths, hq, hkv):
+    import torch
+    from paper_2605_06374_amd import binding
+    w = W.custom("bad", lengths, hq, hkv, 128, seed=3)
+    cu = w.cu_seqlens.tolist()
+    for bad in ([0, cu[2], cu[1]] + cu[3:], [1] + cu[1:], cu[:-1] + [cu[-1] - 1]):
+        prob = gpu.DeviceProblem(w)
+        prob.cu.copy_(torch.tensor(bad, dtype=torch.int32))
+        prob.poison_outputs()
+        prob.forward()
+        names = launched(prob.backward)
+        assert "bwd_prep_kernel" in names and "bwd_dq_kernel" not in names
+        assert binding.varlen_attn_check(prob.workspace) == binding.BAD_CU_SEQLENS
+        bits = prob.result_bits()
+        for n in ("o", "dq", "dk", "dv"):
+            assert (bits[n] == 0x7FC0).all(), n
+
+
+@pytest.mark.parametrize("lengths,hq,hkv", POOL_SIZES)
+def test_pool_isolation_bit_exact(gpu, lengths, hq, hkv):
+    """test_isolation_bit_exact in the pool: NaN, Inf and huge values in every other document leave a document's bits alone (rows
+    and statistics past its end are clamped to its last row)."""
+    w = W.custom("iso", lengths, hq, hkv, 128, seed=9)
+    vals = w.values()
+    base = run_pooled(gpu, w).result_bits()
+    cu = w.cu_seqlens
+    for b in range(len(lengths)):
+        s, e = int(cu[b]), int(cu[b + 1])
+        poisoned = {}
+        for n, x in vals.items():
+            y = x.copy()
+            y[:s] = 0x7FC0 if n != "k" else 0x7F80
+            y[e:] = 0x7FC0 if n != "v" else 0x7E00
+            poisoned[n] = y
+        got = run_pooled(gpu, w, values=poisoned).result_bits()
+        for n in ("o", "dq", "dk", "dv"):
+            assert np.array_equal(got[n][s:e], base[n][s:e]), (b, n)
+
+
+@pytest.mark.parametrize("lengths,hq,hkv", POOL_SIZES)
+def test_pool_under_graph_replay(gpu, lengths, hq, hkv):
+    """Forward and pooled backward in a HIP graph: every replay finds its ticket counters cleared, also over a workspace that holds
+    anything, and with two backward passes in the graph; eager work between the replays."""
+    import torch
+    w = W.custom("graph", lengths, hq, hkv, 128, seed=77)
+    want = run_pooled(gpu, w).result_bits()
+    prob = gpu.DeviceProblem(w)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        prob.forward()
+        prob.backward(reuse_plan=True)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        prob.forward()
+        prob.backward(reuse_plan=True)
+        prob.backward(reuse_plan=True)
+    for replay in range(4):
+        prob.poison_outputs()
+        prob.workspace.fill_(255 * (replay & 1))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = prob.result_bits()
+        for n in want:
+            assert np.array_equal(got[n], want[n]), (replay, n)
+        prob.poison_outputs()
+        prob.forward()                         # eager work between the replays, through the same counters
+        prob.backward(reuse_plan=True)
+        eager = prob.result_bits()
+        for n in want:
+            assert np.array_equal(eager[n], want[n]), (replay, n)
+
+
+@pytest.mark.parametrize("lengths,hq,hkv", POOL_SIZES)
+def test_pool_backward_plans_itself(gpu, lengths, hq, hkv):
+    w = W.custom("noreuse", lengths, hq, hkv, 128, seed=21)
+    prob = gpu.DeviceProblem(w)
+    prob.poison_outputs()
+    prob.forward()
+    prob.workspace.zero_()          # wipe the plan: the backward must make it again, all three lists
+    names = launched(lambda: prob.backward(reuse_plan=False))
+    assert "plan_kernel" in names and "bwd_prep_kernel" in names and "bwd_dq_kernel" not in names
+    assert_close_full(prob.results(), oracle_full(w), "pool, noreuse")
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,heads,chunks,general", [
+    ([250] * 100, 8, 1, 0, 0, False),              # what the plan takes by itself: above 160000 rows, 128 to 399 tokens a document
+    ([1500, 130, 400], 4, 1, 2, 0, True), ([1500, 130, 400], 4, 1, 4, 0, True),
+    ([1500, 130, 400], 4, 1, 4, 3, False), ([1500, 500, 125], 4, 1, 2, 3, False), ([900, 64, 1, 33], 8, 2, 4, 2, False)])
+def test_two_kernels_sweeping_heads(gpu, lengths, hq, hkv, heads, chunks, general):
+    """bwd_dkv_kernel and bwd_combine_kernel at head size 128 with several q heads a column unit: whole groups and parts of
+    them, chains of several steps, whole and cut."""
+    from paper_2605_06374_amd import binding
+    flags = (binding.flag_group_heads(heads) if heads else 0) | (binding.flag_chunk_steps(chunks, chunks) if chunks else 0) | route(general)
+    w = W.custom("sweeps", lengths, hq, hkv, 128, seed=sum(lengths) + heads)
+    prob = run_all(gpu, w, flags=flags)
+    plan = _check_plan(prob, w, False)
+    hdr = plan["header"]
+    assert hdr.col_heads_per_unit == heads if heads else hdr.col_heads_per_unit > 1
+    assert int(plan["col_units"][:, 6].max()) > 1
+    if chunks or hdr.col_heads_per_unit < hq // hkv:
+        assert hdr.n_col_combine > 0
+    assert "bwd_dq_kernel" in launched(lambda: prob.backward(reuse_plan=True))
+    assert_close_full(prob.results(), oracle_full(w), f"two kernels {heads} {lengths[:3]}")
