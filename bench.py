@@ -25,7 +25,7 @@ PEAK_HBM_GBS = 8000.0
 CALIBRATION_COPY_BYTES = 256 << 20   # --calibrate-copy: bench_copy_kernel reads and writes this much
 
 ATTENTION_SOURCES = ("varlen_attn.hip", "tiles.hpp", "staging.hpp", "fragments.hpp", "plan.hpp",
-                     "fwd.hpp", "bwd.hpp", "short.hpp")
+                     "fwd.hpp", "bwd.hpp", "bwd_pool.hpp", "short.hpp")
 
 
 def csrc_digest() -> str:

@@ -189,3 +189,21 @@ def test_product_and_oracle_do_not_reach_into_each_other():
     first = bench.index("from oracle import")
     assert bench.index("if not args.no_cpu_baseline") < first          # only inside the baseline leg
     assert bench.count("from oracle import") + bench.count("import oracle") == 1
+
+
+def test_measured_traffic_is_keyed_by_every_kernel_source():
+    """bench.py reports measured traffic only for the sources it was measured on: its list of them is what the translation
+    unit includes."""
+    import sys
+    sys.path.insert(0, ROOT)
+    import bench
+    csrc = os.path.join(ROOT, "paper_2605_06374_amd", "csrc")
+    found, todo = set(), ["varlen_attn.hip"]
+    while todo:
+        name = todo.pop()
+        if name in found:
+            continue
+        found.add(name)
+        todo += [n for n in re.findall(r'#include "([\w.]+)"', open(os.path.join(csrc, name)).read())
+                 if os.path.exists(os.path.join(csrc, n))]
+    assert found == set(bench.ATTENTION_SOURCES)
