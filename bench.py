@@ -83,7 +83,7 @@ def main() -> int:
                          "micro-batches per iteration of Table 3; prints one JSON line, then exits")
     ap.add_argument("--fused-bwd", action="store_true",
                     help="run the backward as the single-kernel variant (dQ accumulated with fp32 "
-                         "atomic adds) instead of the default two-kernel form")
+                         "atomic adds) instead of the default, reproducible one")
     ap.add_argument("--overlap-probe", action="store_true",
                     help="time matrix and vector instruction streams alone, side by side on one SIMD "
                          "(two waves) and interleaved in one wave; prints one JSON line, then exits")
@@ -202,12 +202,12 @@ def main() -> int:
         split_tflops = {
             "fwd": round(4 * pair_flops / (us("plan_kernel", "fwd_kernel", "fwd_combine_kernel", "fwd_short_kernel") * 1e-6) / 1e12, 1),
             "bwd": round(10 * pair_flops / (us("bwd_dq_kernel", "bwd_dkv_kernel", "bwd_combine_kernel", "bwd_prep_kernel",
-                                               "bwd_fused_kernel", "bwd_dq_finish_kernel", "bwd_short_kernel",
+                                               "bwd_pool_kernel", "bwd_pool_combine_kernel", "bwd_fused_kernel", "bwd_dq_finish_kernel", "bwd_short_kernel",
                                                "bwd_short_group_kernel") * 1e-6) / 1e12, 1)}
         # algorithmic flops per launch: 2*d per (pair, contraction); forward S and PV;
         # dK/dV kernel S, dP, dV, dK; dQ kernel only the dQ contraction is new work
-        # (the pooled backward, which launches no dQ kernel, the single-kernel one and that of small microbatches: all five)
-        per_pair = {"fwd_kernel": 4, "bwd_dkv_kernel": 8 if "bwd_dq_kernel" in kernels else 10, "bwd_dq_kernel": 2, "bwd_fused_kernel": 10,
+        # (the pooled backward, the single-kernel one and that of small microbatches: all five)
+        per_pair = {"fwd_kernel": 4, "bwd_dkv_kernel": 8, "bwd_dq_kernel": 2, "bwd_pool_kernel": 10, "bwd_fused_kernel": 10,
                     "fwd_short_kernel": 4, "bwd_short_kernel": 10}
         dom = max((k for k in kernels if k in per_pair), key=lambda k: kernels[k]["avg_us"])
         alg = per_pair[dom] * w.head_dim * w.n_q_heads * w.pairs

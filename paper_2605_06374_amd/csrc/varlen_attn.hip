@@ -9,7 +9,8 @@
 //
 // Sources: tiles.hpp (types, MFMA, LDS tile addressing and the register conventions),
 // staging.hpp (direct-to-LDS loads), plan.hpp, fragments.hpp (partial-result layout), fwd.hpp,
-// bwd.hpp, short.hpp (small microbatches in one launch each way); this file holds the profiler, the host side and the C ABI.
+// bwd.hpp, bwd_pool.hpp (the backward as one pool of units), short.hpp (small microbatches in one launch each way); this file
+// holds the profiler, the host side and the C ABI.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -36,13 +37,14 @@ namespace {
 // ----------------------------------------------------------------------------------------
 // Optional per-kernel timing (host-side HIP events only; off by default).
 // ----------------------------------------------------------------------------------------
-// (A launch counts under what it does: the pooled backward's as bwd_dkv_kernel, without a bwd_dq_kernel beside it, and
-// its reduction as bwd_combine_kernel.)
-enum KernelId { kPlan = 0, kFwd, kFwdCombine, kDq, kDkv, kBwdCombine, kPrep, kFusedBwd, kDqFinish, kFwdShort, kBwdShort, kBwdShortGroup, kNumKernels };
+enum KernelId {
+  kPlan = 0, kFwd, kFwdCombine, kDq, kDkv, kBwdCombine, kPrep, kBwdPool, kBwdPoolCombine, kFusedBwd, kDqFinish, kFwdShort, kBwdShort,
+  kBwdShortGroup, kNumKernels
+};
 const char* const kKernelNames[kNumKernels] = {
     "plan_kernel", "fwd_kernel", "fwd_combine_kernel", "bwd_dq_kernel", "bwd_dkv_kernel",
-    "bwd_combine_kernel", "bwd_prep_kernel", "bwd_fused_kernel", "bwd_dq_finish_kernel",
-    "fwd_short_kernel", "bwd_short_kernel", "bwd_short_group_kernel"};
+    "bwd_combine_kernel", "bwd_prep_kernel", "bwd_pool_kernel", "bwd_pool_combine_kernel", "bwd_fused_kernel",
+    "bwd_dq_finish_kernel", "fwd_short_kernel", "bwd_short_kernel", "bwd_short_group_kernel"};
 struct Profiler {
   std::mutex mu;
   bool enabled = false;
@@ -409,7 +411,7 @@ void launch_bwd(const varlen_attn_params* p, const void* q, const void* k, const
             (const __bf16*)o, (const __bf16*)d_o, lse, R.dsum, neg_lse, nullptr, tickets, N, Hq, scale);
       }
       {
-        ScopedKernelTimer timer(kDkv, stream);   // dK, dV and dQ
+        ScopedKernelTimer timer(kBwdPool, stream);   // dK, dV and dQ
         bwd_pool_kernel<D><<<dim3(kPoolGroups), kThreads, 0, stream>>>(
             BwdArgs<D>{(const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (const __bf16*)d_o, neg_lse, R.dsum, R.hdr, R.col_units,
                        R.dq_units, R.row_units, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, R.col_part, R.row_part, N, Hq, Hkv, scale, tickets});
@@ -417,7 +419,7 @@ void launch_bwd(const varlen_attn_params* p, const void* q, const void* k, const
       if (split || Hq != Hkv) {
         const int dq_items = split ? cut_tiles : 0;
         const long long pieces = (long long)col_items * Hkv * (D / 8) + (long long)dq_items * Hq * (D / 16);
-        ScopedKernelTimer timer(kBwdCombine, stream);
+        ScopedKernelTimer timer(kBwdPoolCombine, stream);
         bwd_pool_combine_kernel<D><<<dim3((unsigned)std::min<long long>(pieces, 2 * kCombineGroups)), kThreads, 0, stream>>>(
             R.hdr, R.col_comb, col_items, R.col_part, R.dq_comb, dq_items, R.row_part, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, Hq, Hkv, scale);
       }

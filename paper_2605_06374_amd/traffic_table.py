@@ -21,8 +21,7 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 KERNELS = ("plan_kernel", "fwd_combine_kernel", "fwd_kernel", "bwd_dkv_kernel", "bwd_dq_kernel",
-           "bwd_combine_kernel", "bwd_prep_kernel", "bench_copy_kernel")
-POOLED = {"bwd_pool_kernel": "bwd_dkv_kernel", "bwd_pool_combine_kernel": "bwd_combine_kernel"}   # timed under these names
+           "bwd_combine_kernel", "bwd_prep_kernel", "bwd_pool_kernel", "bwd_pool_combine_kernel", "bench_copy_kernel")
 
 
 def counter_means(directory: str, counter: str) -> dict:
@@ -34,9 +33,9 @@ def counter_means(directory: str, counter: str) -> dict:
         for r in csv.DictReader(open(f)):
             if r["Counter_Name"] != counter:
                 continue
-            m = re.search("|".join((*POOLED, *KERNELS)), r["Kernel_Name"])
+            m = re.search("|".join(KERNELS), r["Kernel_Name"])
             if m:
-                acc[POOLED.get(m.group(0), m.group(0))].append(float(r["Counter_Value"]))
+                acc[m.group(0)].append(float(r["Counter_Value"]))
     return {k: sum(v) / len(v) for k, v in acc.items()}
 
 

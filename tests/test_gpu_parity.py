@@ -45,7 +45,8 @@ def run_all(gpu, w, values=None, poison=True, flags=0):
         prob.backward(reuse_plan=True)
     names = launched(step)
     if flags & (binding.FLAG_GENERAL | binding.FLAG_NO_SPLIT) or flags >> 8:
-        assert {"fwd_kernel", "bwd_fused_kernel" if flags & binding.FLAG_FUSED_BWD else "bwd_dkv_kernel"} <= names
+        assert "fwd_kernel" in names
+        assert names & ({"bwd_fused_kernel"} if flags & binding.FLAG_FUSED_BWD else {"bwd_dkv_kernel", "bwd_pool_kernel"}), names
         assert not [n for n in names if "short" in n], names
     assert binding.varlen_attn_check(prob.workspace) == binding.OK
     return prob
@@ -712,7 +713,8 @@ def test_long_chains_go_to_the_chunked_kernels(gpu, lengths, hq, hkv, d, short):
     w = W.custom("route", lengths, hq, hkv, d, seed=sum(lengths))
     prob = gpu.DeviceProblem(w)
     assert ("fwd_short_kernel" if short else "fwd_kernel") in launched(prob.forward)
-    assert ("bwd_short_kernel" if short else "bwd_dkv_kernel") in launched(lambda: prob.backward(reuse_plan=True))
+    names = launched(lambda: prob.backward(reuse_plan=True))
+    assert ("bwd_short_kernel" in names) == short and (short or names & {"bwd_dkv_kernel", "bwd_pool_kernel"}), names
 
 
 @BOTH_ROUTES
@@ -886,7 +888,7 @@ def test_pooled_backward(gpu, lengths, hq, hkv, chunks):
     bits = prob.result_bits()
     names = launched(lambda: prob.backward(reuse_plan=True))
     pooled = chunks != "uncut" or hq <= 2 * hkv
-    assert ("bwd_dq_kernel" not in names) == pooled and ("bwd_prep_kernel" in names) == pooled
+    assert ("bwd_pool_kernel" in names) == pooled and ("bwd_dq_kernel" in names) != pooled
     again = prob.result_bits()
     for n in ("dq", "dk", "dv"):
         assert np.array_equal(bits[n], again[n]), n
@@ -905,7 +907,7 @@ def test_reach_of_non_finite_keys_inside_a_document(gpu, chunks, name, lengths, 
     prob = gpu.DeviceProblem(w, flags=flags)
     names = launched(lambda: (prob.forward(), prob.backward(reuse_plan=True)))
     if name == "pool":
-        assert "bwd_prep_kernel" in names and "bwd_dq_kernel" not in names
+        assert "bwd_pool_kernel" in names
     want = prob.result_bits()
     vals = w.values()
     for j in (33, 64 + 63, 128 + 95, 256 + 127, 512 + 32, lengths[0] - 1):
@@ -932,7 +934,7 @@ def test_pooled_backward_on_a_plan_without_dq_units(gpu, lengths, hq, hkv, uncut
     hdr = prob.read_plan()["header"]
     assert hdr.n_dq_units == 0 and hdr.n_row_combine == 0
     prob.params.flags ^= binding.FLAG_NO_SPLIT
-    assert "bwd_dq_kernel" not in launched(lambda: prob.backward(reuse_plan=True))
+    assert "bwd_pool_kernel" in launched(lambda: prob.backward(reuse_plan=True))
     assert_close_full(prob.results(), oracle_full(w), f"mixed {lengths[:3]} {hq}/{hkv}")
 
 
@@ -1022,7 +1024,7 @@ def run_pooled(gpu, w, values=None, flags=0):
     """run_all, and the backward went to the pool."""
     prob = run_all(gpu, w, values=values, flags=flags)
     names = launched(lambda: prob.backward(reuse_plan=True))
-    assert "bwd_prep_kernel" in names and "bwd_dq_kernel" not in names and "bwd_short_kernel" not in names, names
+    assert "bwd_pool_kernel" in names, names
     return prob
 
 
@@ -1064,8 +1066,7 @@ def test_pool_writes_nothing_on_bad_cu_seqlens(gpu, lengths, hq, hkv):
         prob.cu.copy_(torch.tensor(bad, dtype=torch.int32))
         prob.poison_outputs()
         prob.forward()
-        names = launched(prob.backward)
-        assert "bwd_prep_kernel" in names and "bwd_dq_kernel" not in names
+        assert "bwd_pool_kernel" in launched(prob.backward)
         assert binding.varlen_attn_check(prob.workspace) == binding.BAD_CU_SEQLENS
         bits = prob.result_bits()
         for n in ("o", "dq", "dk", "dv"):
@@ -1138,7 +1139,7 @@ def test_pool_backward_plans_itself(gpu, lengths, hq, hkv):
     prob.forward()
     prob.workspace.zero_()          # wipe the plan: the backward must make it again, all three lists
     names = launched(lambda: prob.backward(reuse_plan=False))
-    assert "plan_kernel" in names and "bwd_prep_kernel" in names and "bwd_dq_kernel" not in names
+    assert {"plan_kernel", "bwd_pool_kernel"} <= names
     assert_close_full(prob.results(), oracle_full(w), "pool, noreuse")
 
 
