@@ -86,8 +86,8 @@ extern "C" {
 
 #define VARLEN_ATTN_FLAG_FUSED_BWD 16 /* bwd: one kernel for dQ, dK and dV, so that S and dP are
                                          computed once for the whole backward (5 contractions per
-                                         (query, key) pair instead of the 7 of the two-kernel
-                                         form).  dQ is summed with floating-point atomics into an
+                                         (query, key) pair instead of the 7 of the default
+                                         forms).  dQ is summed with floating-point atomics into an
                                          fp32 array in the workspace and rounded afterwards: its
                                          bits are NOT reproducible from run to run (dK, dV stay
                                          reproducible).  The flag enlarges the workspace by
@@ -183,7 +183,9 @@ typedef struct {
   size_t row_partials_offset; /* fp32 partial results of cut row chains */
   size_t col_partials_offset; /* fp32 partial results of cut / grouped column chains */
   size_t dq_accumulator_offset; /* fp32 dQ accumulator [N, Hq, d]; present (non-empty) only with
-                                   VARLEN_ATTN_FLAG_FUSED_BWD */
+                                   VARLEN_ATTN_FLAG_FUSED_BWD.  The last bytes in front of it belong to the plan
+                                   (the dQ units of n_dq_units and their reductions): a plan is kept by leaving the
+                                   workspace alone, not by copying the regions named here */
   size_t total_bytes;
   int32_t max_units;          /* capacity of each unit array */
   int32_t max_combine;        /* capacity of each combine array */
