@@ -414,8 +414,9 @@ __device__ __forceinline__ void plan_body(const PlanArgs& a) {
   }
   const int longest = max_chain;
 
-  // lengthen the chunks until the chunks of cut chains fit their slots; on most small microbatches they do as they are
-  bool fits = surely_fits((float)steps[0], n_tiles, ch[0], tries[0] ? min(a.slots_cap, a.rule[0].resident) : a.slots_cap);
+  // lengthen the chunks until the chunks of cut chains fit their slots; on most microbatches that one wave plans they do as they
+  // are (beyond, asking costs 0.1 to 0.3 us and seldom helps)
+  bool fits = kOrdered && surely_fits((float)steps[0], n_tiles, ch[0], tries[0] ? min(a.slots_cap, a.rule[0].resident) : a.slots_cap);
   if (a.directions > 1) fits = fits && surely_fits((float)steps[1], n_tiles, ch[1], a.slots_cap);   // (a dQ chunk is a row chunk or longer)
   if (!a.no_split && !fits) {
 #pragma unroll 1
