@@ -18,8 +18,9 @@ namespace {
 // results are reproducible.  The price is D: both kinds need it, so it comes from a pass in front (bwd_prep_kernel).
 //
 // What bounds it: at 512 registers one wave per SIMD issues everything, and on large microbatches the clock, which the
-// power limit takes from 2.4 to 1.8 - 2.1 GHz on real operands.  Both sweeps are therefore pipelined by hand: the streamed
-// rows come in stages of 64, two blocks of 32 of which
+// power limit takes down to 1.7 - 2.0 GHz on real operands (2.2 on zeros; cycles of a die over the launch's duration).  The matrix
+// pipe is busy in 0.33 of these cycles at 8192 tokens in 9 documents, 0.50 at 32768 in 35 and 0.62 at 32768 in 11.  Both sweeps
+// are therefore pipelined by hand: the streamed rows come in stages of 64, two blocks of 32 of which
 //   M1(0) + R1 | V(0) with M1(1) + T0 | M2(0) with V(1) + T1 | wait, barrier | M2(1) + R0 of the next stage
 // (R: row fragments and statistics from LDS, T: transposed fragments, M1: S and dP, V: P and dS on the vector ALU, M2: the
 // sums).  The barrier lies in front of M2(1), whose operands are in registers by then, so that the first reads of the next

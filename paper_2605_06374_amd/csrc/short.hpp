@@ -19,7 +19,7 @@ namespace {
 // need no order between them and share one launch.
 // The price is one read of K and V (Q, dO, O) per 32 rows instead of 128 and the LDS: one workgroup per CU
 // at d = 128 (133 KB forward, 160 KB backward), two at d = 64.
-// 777 tokens, 4 heads of 128, forward 14.5 -> 8.0 us (the plan in workgroup 0 is what is left),
+// 777 tokens, 4 heads of 128, forward 14.5 -> 7.9 us (with the plan in workgroup 0 or its status word alone),
 // backward 29.4 -> 10.5 us; 2048 tokens in 4 documents, 2 heads of 64, forward and backward 37.4 ->
 // 27.9 us.  The rule by which a microbatch comes here is short_path() in varlen_attn.hip.
 // ----------------------------------------------------------------------------------------
