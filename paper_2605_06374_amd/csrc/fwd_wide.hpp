@@ -221,6 +221,8 @@ fwd_wide_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
       if constexpr (NEXT && NB == 0) {
         if constexpr (kk == 0) mfma_vgpr_agpr_first(nxt[0], kf[kk], qf[0][kk]);
         else mfma_vgpr_agpr(nxt[0], kf[kk], qf[0][kk]);
+      } else {
+        asm volatile("s_nop 0");   // (a load to LDS takes m0 one wait state behind its write at the earliest; elsewhere the matrix instruction is that)
       }
       if constexpr (NEXT && kk < KK / 2) kf[kk + KK / 2] = fo.row_frag(kt, kk + KK / 2);
       upper(std::integral_constant<int, 2 * kk>{});

@@ -152,3 +152,39 @@ def test_inline_exponentials_keep_their_distance(tmp_path):
     bad, seen = transcendental_violations(out.read_text())
     assert seen >= 64
     assert not bad, "\n".join(bad[:20])
+
+
+def load_violations(text):
+    """Loads whose scalar operands are too fresh, none of which the compiler sees inside inline assembly: a load to LDS takes its destination from
+    m0 one wait state behind a scalar write of it at the earliest, and an address in scalar registers five behind the vector instruction that wrote them."""
+    scalars = lambda text: {r for lo, hi, one in re.findall(r"\bs(?:\[(\d+):(\d+)\]|(\d+)\b)", text)
+                            for r in (range(int(lo), int(hi) + 1) if lo else [int(one)])}
+    code, labels = parse(text)
+    bad, seen = [], 0
+    for i, (op, args, _) in enumerate(code):
+        if op.startswith("s_") and args and args[0] == "m0":
+            seen += 1
+            bad += [f"{op} {', '.join(args)} right in front of {code[j][0]}" for j, _ in within(code, labels, i, 1)
+                    if "_lds_" in code[j][0] and code[j][0].startswith(("global_", "buffer_", "scratch_"))]
+        elif op.startswith("v_") and args and scalars(args[0]):
+            bad += [f"{op} {', '.join(args)} {gone} wait states before {code[j][0]} {', '.join(code[j][1])}"
+                    for j, gone in within(code, labels, i, 5)
+                    if code[j][0].startswith(("global_", "buffer_", "scratch_", "flat_")) and any(scalars(a) & scalars(args[0]) for a in code[j][1])]
+    return bad, seen
+
+
+@pytest.mark.parametrize("between,count", [("", 1), ("s_nop 0\n", 0), ("s_add_u32 s0, s0, s1\n", 0), ("s_branch .L1\n.L1:\n", 0),
+                                           ("v_readfirstlane_b32 s5, v9\ns_nop 3\n", 1), ("v_readfirstlane_b32 s5, v9\ns_nop 4\n", 0)])
+def test_load_snippets(between, count):
+    planted = "s_add_u32 m0, s2, 64\n" + between + ";;#ASMSTART\nglobal_load_lds_dwordx4 v1, s[4:5] offset:64\n;;#ASMEND\n"
+    assert len(load_violations(planted)[0]) == count
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs the HIP compiler")
+def test_inline_loads_keep_their_distances(tmp_path):
+    out = tmp_path / "varlen_attn.s"
+    flags = [f for f in build.FLAGS if f != "-shared"]
+    subprocess.run([build.HIPCC] + flags + ["--cuda-device-only", "-S", "-o", str(out), build.SRC], check=True, capture_output=True)
+    bad, seen = load_violations(out.read_text())
+    assert seen >= 100
+    assert not bad, "\n".join(bad[:20])
