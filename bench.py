@@ -200,14 +200,14 @@ def main() -> int:
         pair_flops = w.head_dim * w.n_q_heads * w.pairs
         # forward alone (with its plan) and backward alone, by the same FLOP convention
         split_tflops = {
-            "fwd": round(4 * pair_flops / (us("plan_kernel", "fwd_kernel", "fwd_combine_kernel", "fwd_short_kernel") * 1e-6) / 1e12, 1),
+            "fwd": round(4 * pair_flops / (us("plan_kernel", "fwd_kernel", "fwd_wide_kernel", "fwd_combine_kernel", "fwd_short_kernel") * 1e-6) / 1e12, 1),
             "bwd": round(10 * pair_flops / (us("bwd_dq_kernel", "bwd_dkv_kernel", "bwd_combine_kernel", "bwd_prep_kernel",
                                                "bwd_pool_kernel", "bwd_pool_combine_kernel", "bwd_fused_kernel", "bwd_dq_finish_kernel", "bwd_short_kernel",
                                                "bwd_short_group_kernel") * 1e-6) / 1e12, 1)}
         # algorithmic flops per launch: 2*d per (pair, contraction); forward S and PV;
         # dK/dV kernel S, dP, dV, dK; dQ kernel only the dQ contraction is new work
         # (the pooled backward, the single-kernel one and that of small microbatches: all five)
-        per_pair = {"fwd_kernel": 4, "bwd_dkv_kernel": 8, "bwd_dq_kernel": 2, "bwd_pool_kernel": 10, "bwd_fused_kernel": 10,
+        per_pair = {"fwd_kernel": 4, "fwd_wide_kernel": 4, "bwd_dkv_kernel": 8, "bwd_dq_kernel": 2, "bwd_pool_kernel": 10, "bwd_fused_kernel": 10,
                     "fwd_short_kernel": 4, "bwd_short_kernel": 10}
         dom = max((k for k in kernels if k in per_pair), key=lambda k: kernels[k]["avg_us"])
         alg = per_pair[dom] * w.head_dim * w.n_q_heads * w.pairs

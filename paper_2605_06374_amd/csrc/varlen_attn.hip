@@ -8,9 +8,10 @@
 // visited, so the work follows sum l_i^2, not N^2.
 //
 // Sources: tiles.hpp (types, MFMA, LDS tile addressing and the register conventions),
-// staging.hpp (direct-to-LDS loads), plan.hpp, fragments.hpp (partial-result layout), fwd.hpp,
-// bwd.hpp, bwd_pool.hpp (the backward as one pool of units), short.hpp (small microbatches in one launch each way); this file
-// holds the profiler, the host side and the C ABI.
+// staging.hpp (direct-to-LDS loads), panels.hpp (what the kernels with one wave a SIMD share), plan.hpp,
+// fragments.hpp (partial-result layout), fwd.hpp, fwd_wide.hpp (waves of 64 rows), bwd.hpp, bwd_pool.hpp (the
+// backward as one pool of units), short.hpp (small microbatches in one launch each way); this file holds the
+// profiler, the host side and the C ABI.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -40,12 +41,13 @@ namespace {
 // ----------------------------------------------------------------------------------------
 enum KernelId {
   kPlan = 0, kFwd, kFwdCombine, kDq, kDkv, kBwdCombine, kPrep, kBwdPool, kBwdPoolCombine, kFusedBwd, kDqFinish, kFwdShort, kBwdShort,
-  kBwdShortGroup, kNumKernels
+  kBwdShortGroup, kFwdWide, kNumKernels
 };
 const char* const kKernelNames[kNumKernels] = {
     "plan_kernel", "fwd_kernel", "fwd_combine_kernel", "bwd_dq_kernel", "bwd_dkv_kernel",
     "bwd_combine_kernel", "bwd_prep_kernel", "bwd_pool_kernel", "bwd_pool_combine_kernel", "bwd_fused_kernel",
-    "bwd_dq_finish_kernel", "fwd_short_kernel", "bwd_short_kernel", "bwd_short_group_kernel"};
+    "bwd_dq_finish_kernel", "fwd_short_kernel", "bwd_short_kernel", "bwd_short_group_kernel",
+    "fwd_wide_kernel"};
 struct Profiler {
   std::mutex mu;
   bool enabled = false;
@@ -384,9 +386,10 @@ void launch_fwd(const varlen_attn_params* p, const void* q, const void* k, const
         (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, (__bf16*)o, lse, Hq, Hkv, p->softmax_scale, plan_block, args);
     return;
   }
-  {
-    ScopedKernelTimer timer(kFwd, stream);
-    if (wide_forward(p)) {
+  const bool wide = D == 128 && wide_forward(p);
+  if constexpr (D == 128) {
+    if (wide) {
+      ScopedKernelTimer timer(kFwdWide, stream);
       if (self_plan)
         fwd_wide_kernel<true><<<dim3(grid_for(L.max_units, Hq) + 1), 128, 0, stream>>>(
             (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, R.hdr, R.row_units, (__bf16*)o, lse,
@@ -395,7 +398,11 @@ void launch_fwd(const varlen_attn_params* p, const void* q, const void* k, const
         fwd_wide_kernel<false><<<dim3(grid_for(L.max_units, Hq)), 128, 0, stream>>>(
             (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, R.hdr, R.row_units, (__bf16*)o, lse,
             R.row_part, N, Hq, Hkv, p->softmax_scale, L.max_units, PlanArgs{});
-    } else if (self_plan)
+    }
+  }
+  if (!wide) {
+    ScopedKernelTimer timer(kFwd, stream);
+    if (self_plan)
       fwd_kernel<D, true><<<dim3(grid_for(L.max_units, Hq) + 1), kThreads, 0, stream>>>(
           (const __bf16*)q, (const __bf16*)k, (const __bf16*)v, R.hdr, R.row_units, (__bf16*)o, lse,
           R.row_part, N, Hq, Hkv, p->softmax_scale, L.max_units, args);
