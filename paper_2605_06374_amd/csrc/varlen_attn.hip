@@ -230,8 +230,8 @@ void chunk_rules(const varlen_attn_params* p, PlanArgs* a) {
   } else {
     // One wave a SIMD gains less from more units than fit one round: from 26 steps a slot on its chunks are 8 steps shorter than those of
     // waves of 32 rows (200 packs of ragged documents 1.005 times as fast as with their line).  Below, the same line: one of 1.1 x + 4 cut
-    // documents of equal length just short of their end (9 of 1394 tokens, 6 q heads: 51.5 / 57.9 us).
-    a->rule[0] = ChunkRule{1.3125f * kSlot, 3, kSlot, wide_forward(p) ? 11 : 19, resident, kMinChunkSteps + 1};
+    // documents of equal length just short of their end (8 of 1451 tokens and 946 more, 6 q heads: 50.3 / 57.6 us).
+    a->rule[0] = ChunkRule{1.3125f * kSlot, 3, kSlot, wide_forward(p) ? 11.f : 19.f, resident, kMinChunkSteps + 1};
   }
   if (pooled) {
     // ungrouped heads of 64: a quarter longer than at 128 takes 0.99 of the time (17 packs, 0.8 to 1.6 times the length)
