@@ -346,14 +346,22 @@ inline bool pooled_backward(const varlen_attn_params* p) {
   return !short_sizes(p, true) && (rows <= 24000 || mean >= (many_to_one && rows > 160000 ? 400 : 128));
 }
 
-// Forward with heads of 128 in waves of 64 rows (fwd_wide.hpp) from 60000 rows and 700 tokens a document on average on.  Waves of 32 rows / of 64, on
-// buffers that no cache holds: 0.998 .. 1.14, 1.08 in the mean of 45 packs by this rule; 12000 to 60000 rows 0.91 .. 1.09, 1.02 in the mean of 33 (8192
-// tokens in 9 documents, 4 heads: forward 30.8 / 32.0 us; where the data stay in the cache between passes 31.9 / 30.6), because nothing covers a unit's
-// first loads here; documents of 50 to 700 tokens on average 0.93 .. 1.04, 0.98 in the mean (70 packs).  With VARLEN_ATTN_FLAG_NO_SPLIT a document's bits
-// must not depend on the rest of the pack: 32 rows (0.93 .. 1.05 in 16 uncut packs).
+// Forward with heads of 128 in waves of 64 rows (fwd_wide.hpp): nothing covers a unit's first loads there, so chains have to be
+// long, the more so where a workgroup slot sees many of them one after the other.  The host knows the mean length only, and packs
+// of documents of one length have the shortest chains for it.  Waves of 32 rows / of 64, on buffers that no cache holds and on
+// resident ones (geometric mean of the two), 760 packs of 60000 to 400000 rows, half of them of equal or nearly equal documents:
+//   inside the rule 0.98 .. 1.12, 1.05 in the mean, up to 40000 tokens, and 0.96 .. 1.13, 1.06, above (one pack below: 98147 tokens in
+//   85 equal documents, 4 heads, 229 / 255 us);
+//   60000 to 90000 rows, 700 to 2000 tokens on average 0.91 .. 1.08, 1.00 and 1.02 in the mean;
+//   90000 to 180000, 700 to 850: 0.96 .. 1.05, 1.00 and 1.02;  above, 700 to 1100: 0.90 .. 1.08, 0.97 and 1.03 (94317 tokens
+//   in 109 equal documents, 4 heads, 175 / 196 us).
+// Fewer rows: 0.91 .. 1.09, 1.02 in the mean of 33 (8192 tokens in 9 documents, 4 heads: 30.8 / 32.0 us; where the data stay in the
+// cache between passes 31.9 / 30.6); documents of 50 to 700 tokens 0.93 .. 1.04, 0.98 in the mean of 70.  With
+// VARLEN_ATTN_FLAG_NO_SPLIT a document's bits must not depend on the rest of the pack: 32 rows (0.93 .. 1.05 in 16 uncut packs).
 inline bool wide_forward(const varlen_attn_params* p) {
-  return p->head_dim == 128 && !(p->flags & VARLEN_ATTN_FLAG_NO_SPLIT) && (long long)p->total_tokens * p->num_q_heads >= 60000 &&
-         p->total_tokens / p->num_docs >= 700;
+  const long long rows = (long long)p->total_tokens * p->num_q_heads, mean = p->total_tokens / p->num_docs;
+  if (p->head_dim != 128 || (p->flags & VARLEN_ATTN_FLAG_NO_SPLIT) || rows < 60000) return false;
+  return mean >= (rows < 90000 ? 2000 : rows < 180000 ? 850 : 1100);
 }
 
 int launch_plan(const varlen_attn_params* p, const PlanArgs& a, hipStream_t stream) {
