@@ -166,20 +166,12 @@ fwd_wide_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
     if constexpr (i < 16 && (i >> 3) >= first) exponential(s[i >> 3], i >> 3, base + (i & 7));
     if constexpr (p >= 0 && (p >> 3) >= first) add_up(s[p >> 3], p >> 3, base + (p & 7), out[p >> 3]);
   };
-  // rare: scores of block b anew, from memory (the K tile may be landing on already), against a new reference
-  auto renew = [&](f32x16& s, int b, int kv0, bool triangle) __attribute__((always_inline)) {
-    const __bf16* row = k + ((size_t)min(kv0 + c, it.doc_end - 1) * Hkv + kvh) * D + 8 * h;
-    f32x16 x = f32x16(0.f);
-    static_for<KK>([&](auto i_c) __attribute__((always_inline)) {
-      constexpr int i = decltype(i_c)::value;
-      x = mfma(__builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(row + 16 * i)), qf[b][i], x);
-      fence();
-    });
-    if (triangle) mask(x);
-    const float m_new = __builtin_fmaxf(m[b], row_max(x) + kRefRoom);
+  // O, the row sum and this substep's as of a new reference
+  auto rescale = [&](int b, float m_new) __attribute__((always_inline)) {
     const float alpha = __builtin_amdgcn_exp2f(m[b] - m_new);
     m[b] = m_new;
     l[b] *= alpha;
+    psum[b] *= alpha;
 #pragma unroll
     for (int i = 0; i < DB; ++i) {
 #pragma unroll
@@ -187,11 +179,40 @@ fwd_wide_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
       asm volatile("" : "+a"(acc[b][i]));
       fence();
     }
+  };
+  // Rare: block b against a new reference.  Its scores are gone by now and the probabilities at hand are scaled, which gives a row's largest the same
+  // 2^-12 exactly.  To form the scores again from memory (the K tile may be landing on already) stops both waves for the time of a load, and is
+  // done for sums beyond 2^100, whose scaling would leave the range, and NaN.  Forward at 32768 tokens in 35 documents, 16384 (8 q heads on
+  // one) and 32768 in 11, scores with a standard deviation of 9, from memory each time 153.6, 191.6 and 472 us, scaled 126.0, 166.3 and 437;
+  // with a standard deviation of 1 114.1, 148.9 and 402, scaled 113.3, 148.8 and 402.
+  auto renew = [&](f32x16& s, int b, int kv0, bool triangle) __attribute__((always_inline)) {
+    if (__builtin_expect(__any(!(psum[b] <= 0x1p100f)), 0)) {
+      const __bf16* row = k + ((size_t)min(kv0 + c, it.doc_end - 1) * Hkv + kvh) * D + 8 * h;
+      f32x16 x = f32x16(0.f);
+      static_for<KK>([&](auto i_c) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_c)::value;
+        x = mfma(__builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(row + 16 * i)), qf[b][i], x);
+        fence();
+      });
+      if (triangle) mask(x);
+      rescale(b, __builtin_fmaxf(m[b], row_max(x) + kRefRoom));
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      exponential(x, b, r);
-      add_up(x, b, r, r < 8 ? pb0[b] : pb1[b]);
+      for (int r = 0; r < 16; ++r) {
+        exponential(x, b, r);
+        add_up(x, b, r, r < 8 ? pb0[b] : pb1[b]);
+      }
+      return;
     }
+    float top = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) top = __builtin_fmaxf(top, s[r]);
+    const float m_old = m[b], m_new = __builtin_fmaxf(m_old, m_old + (__builtin_amdgcn_logf(half_max(top)) + kRefRoom));
+    const float alpha = __builtin_amdgcn_exp2f(m_old - m_new);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] *= alpha;
+    pb0[b] = pack8(s, 0);
+    pb1[b] = pack8(s, 8);
+    rescale(b, m_new);
   };
   int t = 0;
   // Substep x = 32 HALF .. of step t: S of the next substep beside the upper half of x's exponentials, then O += P V of x beside the lower half
