@@ -329,18 +329,20 @@ inline bool short_path(const varlen_attn_params* p, bool backward) {
 // the heads alone decide.  With at most two q heads a kv head, 160 uncut packs: 0.98 .. 2.04, 1.52 in the mean, up to 24000 rows, 0.93 .. 1.86,
 // 1.28 in the mean, up to 80000, and 0.87 .. 1.25, 0.98 in the mean, above.
 // Heads of 64: the two kernels run two waves a SIMD, which hide each other's vector work (as long as the matrix instructions there) once there
-// are units enough for both; below that the pool's one launch, whole dQ chains and single tail win.  Two kernels / pool, 370 packs of 15000 to
-// 180000 rows: one q head a kv head up to 45000 rows 0.92 .. 1.36, 1.15 in the mean, above and up to 62000 with documents of 700 tokens and more
-// on average 1.01 .. 1.10, of fewer 0.84 .. 1.05; beyond 0.59 .. 1.03; two q heads a kv head up to 90000 rows 1.03 .. 1.21, beyond
-// 0.72 .. 1.12; more up to 110000 rows 0.99 .. 1.27 (0.93 from 75000 on with fewer than 250 tokens a document), beyond 0.74 .. 1.01.  Shorter documents (on average below 128 tokens, 90 with grouped
-// queries): 0.68 .. 1.21.
+// are units enough for both; below that the pool's one launch, whole dQ chains and single tail win.  Two kernels / pool, on buffers that no
+// cache holds and on resident ones (geometric mean of the two), 860 packs of 10000 to 190000 rows:
+//   one q head a kv head, inside the rule 0.98 .. 1.29, 1.09 in the mean; on to 62000 rows with 700 tokens a document and more 0.96 .. 1.11,
+//   1.02, with fewer 0.83 .. 1.06, 0.98; above 0.73 .. 1.08, 0.89; below 128 tokens 0.76 .. 1.22, 0.92;
+//   two q heads a kv head, inside 0.95 .. 1.23, 1.09; more rows 0.76 .. 1.13, 0.94;
+//   more, inside 0.95 .. 1.22, 1.06; shorter documents on to 110000 rows 0.89 .. 1.24, 1.10 (slowest with 8 q heads on one kv head);
+//   more rows 0.90 .. 1.24, 1.02.
 inline bool pooled_backward(const varlen_attn_params* p) {
   const bool many_to_one = p->num_q_heads > 2 * p->num_kv_heads;
   if (p->flags & VARLEN_ATTN_FLAG_NO_SPLIT) return p->head_dim == 128 && !many_to_one;
   const long long rows = (long long)p->total_tokens * p->num_q_heads, mean = p->total_tokens / p->num_docs;
   if (p->head_dim == 64) {
     const bool grouped = p->num_q_heads > p->num_kv_heads;
-    const long long max_rows = many_to_one ? (mean >= 250 ? 110000 : 75000) : grouped ? 90000 : mean >= 700 ? 62000 : 45000;
+    const long long max_rows = many_to_one ? (mean >= 250 ? 110000 : 75000) : grouped ? 90000 : mean >= 250 ? 50000 : 38000;
     return !short_sizes(p, true) && rows <= max_rows && mean >= (grouped ? 90 : 128);
   }
   return !short_sizes(p, true) && (rows <= 24000 || mean >= (many_to_one && rows > 160000 ? 400 : 128));
