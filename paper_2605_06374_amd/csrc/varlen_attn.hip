@@ -234,7 +234,9 @@ void chunk_rules(const varlen_attn_params* p, PlanArgs* a) {
     a->rule[0] = ChunkRule{1.3125f * kSlot, 3, kSlot, wide_forward(p) ? 11.f : 19.f, resident, kMinChunkSteps + 1};
   }
   if (pooled) {
-    // ungrouped heads of 64: a quarter longer than at 128 takes 0.99 of the time (17 packs, 0.8 to 1.6 times the length)
+    // Heads of 64 go by the lines of 128 where queries are grouped (57 packs with more than two q heads a kv head, 33 with two; 0.6, 0.8, 1.25 and 1.6
+    // times the length: 0.96, 0.98, 0.94, 0.86 and 0.95, 0.98, 0.99, 0.93 times as fast; half or twice the heads a unit: 0.95 and 0.55, 0.90
+    // and 0.99; the best of each pack 1.014 and 1.010), by a longer one where they are not (50 packs, the same lengths: 0.96, 0.99, 0.96, 0.91; best 1.005).
     a->rule[1] = grouped ? ChunkRule{2.5f * kSlot, 2, 1.6f * kSlot, 26, 0, 0}
                  : p->head_dim == 64 ? ChunkRule{3.75f * kSlot, 3, 2 * kSlot, 33, 0, 0} : ChunkRule{3 * kSlot, 3, 1.6f * kSlot, 27, 0, 0};
     a->sweep = SweepRule{0.75f, 128, 3 * kSlot, 200, 2.5f * kSlot, 32};
