@@ -525,13 +525,17 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
         acc[b] = mfma(lds_read_tr8(tile + lo + cc * 16 * kStep * 2, tile + hi + cc * 16 * kStep * 2), kb, acc[b]);
       }
     }
-    float* col = dq_acc_h + 32 * db + c;
+    // (the 32 offsets are formed here every time: kept across the stages they are spilled, one load from scratch memory in front of each atomic)
+    size_t stride = (size_t)Hq * D;
+    asm volatile("" : "+s"(stride));
+    const int row0 = q0 + 32 * qb0 + 4 * h;
+    float* const first = dq_acc_h + 32 * db + c + row0 * stride;
 #pragma unroll
     for (int b = 0; b < kBlocks; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int row = q0 + 32 * (qb0 + b) + 8 * (r / 4) + 4 * h + r % 4;
-        if (row < it.doc_end) unsafeAtomicAdd(col + (size_t)row * Hq * D, acc[b][r]);
+        const int i = 32 * b + 8 * (r / 4) + r % 4;
+        if (row0 + i < it.doc_end) unsafeAtomicAdd(first + i * stride, acc[b][r]);
       }
   };
 
