@@ -345,8 +345,9 @@ __device__ __forceinline__ void dq_tile_combine(int block, const varlen_attn_pla
 // an LDS tile [128 keys][64 queries]; one stage later wave w multiplies it with columns
 // 32w .. 32w+31 of the unit's K tile (kept in LDS for this) and adds the 64 x 32 block of
 // dQ = dS K into a fp32 accumulator in the workspace with floating-point atomics: the order of
-// those additions is not fixed, so dQ is not bit-reproducible in this mode.  HALVES: dV is summed over the lower and over the upper 32
-// queries of the stages apart and then together, as the pool does (bwd_pool.hpp), so that it has the bits of the backward without the flag.
+// those additions is not fixed, so dQ is not bit-reproducible in this mode.  HALVES (heads of 128): dV is summed
+// over the lower and over the upper 32 queries of the stages apart and then together, as the pool does (bwd_pool.hpp), so that it
+// has the bits of the backward without the flag.
 // ----------------------------------------------------------------------------------------
 template <int D, bool FUSED, bool HALVES = false>
 __global__ void __launch_bounds__(kThreads, D == 64 && !FUSED ? 2 : 1)

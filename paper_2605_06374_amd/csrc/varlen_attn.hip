@@ -343,6 +343,7 @@ inline bool pooled_backward(const varlen_attn_params* p) {
   if (p->flags & VARLEN_ATTN_FLAG_NO_SPLIT) return p->head_dim == 128 && !many_to_one;
   const long long rows = (long long)p->total_tokens * p->num_q_heads, mean = p->total_tokens / p->num_docs;
   if (p->head_dim == 64) {
+    if (p->flags & VARLEN_ATTN_FLAG_FUSED_BWD) return false;   // its chunks and heads a unit are those of the two kernels
     const bool grouped = p->num_q_heads > p->num_kv_heads;
     const long long max_rows = many_to_one ? (mean >= 250 ? 110000 : 75000) : grouped ? 90000 : mean >= 250 ? 50000 : 38000;
     return !short_sizes(p, true) && rows <= max_rows && mean >= (grouped ? 90 : 128);
@@ -509,8 +510,12 @@ void launch_bwd(const varlen_attn_params* p, const void* q, const void* k, const
           R.col_units, (__bf16*)dk, (__bf16*)dv, R.col_part, N, Hq, Hkv, scale, L.max_units,
           (int)unit_blocks, R.row_comb, L.max_combine, R.row_part, (__bf16*)dq, R.dq_acc);
     };
-    if (pooled_backward(p)) launch(bwd_dkv_kernel<D, true, true>);
-    else launch(bwd_dkv_kernel<D, true>);
+    bool halves = false;
+    if constexpr (D == 128) {
+      halves = pooled_backward(p);
+      if (halves) launch(bwd_dkv_kernel<D, true, true>);
+    }
+    if (!halves) launch(bwd_dkv_kernel<D, true>);
   } else {
     // behind its units: one workgroup per (cut tile, q head) that sums the dQ partials
     const unsigned dq_blocks = split ? (unsigned)cut_tiles * Hq : 0u;
