@@ -25,9 +25,10 @@ namespace {
 // columns 1.61 / 1.43 us, dQ 1.23 / 1.12; 32768 tokens in 11 documents 1.80 / 1.65, 1.33 / 1.25.  The matrix instructions alone (no
 // vector work, LDS reads or loads) take 1.18, 0.89, 1.36 and 0.99.  The price is paid between two sweeps: the halves of a stage meet in LDS, which the
 // next unit's rows are landing in as well (LDS writes run at 77 bytes a clock, reads at 170): a column unit's results take 3.3 us
-// there instead of 1.8, which short documents pay for (backward of 64 packs of 256 to 30000 tokens 0.93 .. 1.10 times as fast
-// as with 32 rows a wave, 1.02 in the mean; slowest documents of 32 tokens).  Whole steps: 8192 tokens 108.9 -> 106.1 us, 7001 80.8 -> 77.5, 16384 with 8 q heads
-// on one kv head 626 -> 601, 32768 in 35 documents 426 -> 409, in 11 1683 -> 1604, 131072 in one 32.3 -> 30.6 ms.
+// there instead of 1.8, which short documents pay for: backward of 56 packs of documents of 60 to 180 tokens 0.94 to 1.19, 1.00 in the mean,
+// times as fast as with 32 rows a wave (up to 32 tokens are spared it: lower_half_only(); 22 packs 1.00 to 1.30).  Whole steps: 8192 tokens
+// 108.9 -> 106.1 us, 7001 80.8 -> 77.5, 16384 with 8 q heads on one kv head 626 -> 601, 32768 in 35 documents 426 -> 409, in 11
+// 1683 -> 1604, 131072 in one 32.3 -> 30.6 ms.
 //
 // Both sweeps are pipelined by hand; vector work and LDS reads ride on matrix instructions, the next stage's loads on those of S:
 //   columns  S(0, 1) | dP(0, 1) with P | dV(0, 1) with P, dS | dK(0, 1) with dS | wait, barrier | the last of dK with the next stage's first reads
@@ -226,6 +227,12 @@ __device__ __forceinline__ void add(f32x4 (&x)[D / 8], const float (&mine)[D / 3
 
 // Has this wave a row of the unit's tile?
 __device__ __forceinline__ bool has_rows(const varlen_attn_unit& it, int wave) { return it.row0 + 64 * (wave & 1) < it.doc_end; }
+// The streamed rows of a unit end in the lower half of its only stage: what wave 0 has is the result, and no halves meet.  Two branches a unit of
+// other tiles.  32 rows a wave / meeting always / so, backward, resident buffers: 1250 documents of 32 tokens 56.8 / 60.2 / 51.9 us, 489 of
+// 8 to 100, 8 heads, 162.9 / 176.1 / 158.8; documents of 60 to 200 tokens 0.987 .. 1.005 of the speed without it, 32768 tokens in 35 1.005.
+__device__ __forceinline__ bool lower_half_only(const varlen_attn_unit& it, bool columns) {
+  return it.doc_end - (columns ? it.row0 : it.doc_start) <= kStep / 2;
+}
 // Block of 32 rows of the unit's tile that this wave stores
 __device__ __forceinline__ int own_block(int wave) { return 2 * (wave & 1) + (wave >> 1); }
 
@@ -234,6 +241,21 @@ __device__ __forceinline__ void store_partial(float* partial, int wave, int lane
   float* const p = partial + ((size_t)own_block(wave) * (D / 8) * 64 + lane) * 4;
 #pragma unroll
   for (int i = 0; i < D / 8; ++i) *reinterpret_cast<f32x4*>(p + i * 256) = x[i];
+}
+
+// ... of wave 0, whose sums are the results
+template <int D>
+__device__ __forceinline__ void store_partial(float* partial, const float (&x)[D / 32][16], int lane) {
+  float* const p = partial + lane * 4;
+#pragma unroll
+  for (int i = 0; i < D / 8; ++i)
+    *reinterpret_cast<f32x4*>(p + i * 256) = f32x4{x[i / 4][4 * (i % 4)], x[i / 4][4 * (i % 4) + 1], x[i / 4][4 * (i % 4) + 2], x[i / 4][4 * (i % 4) + 3]};
+}
+template <int D>
+__device__ __forceinline__ void pack(uint2 (&w)[D / 8], const float (&x)[D / 32][16], float mul) {
+#pragma unroll
+  for (int i = 0; i < D / 8; ++i)
+    w[i] = pack4(x[i / 4][4 * (i % 4)] * mul, x[i / 4][4 * (i % 4) + 1] * mul, x[i / 4][4 * (i % 4) + 2] * mul, x[i / 4][4 * (i % 4) + 3] * mul);
 }
 
 // bf16 rows by way of LDS, 64 columns at a time in runs of 128 bytes; buffer stores, which leave out what lies behind the last row
@@ -555,6 +577,16 @@ struct DqUnit {
 // behind give(acc[1])
 template <int D>
 __device__ __forceinline__ void store_dq(const BwdArgs<D>& a, const varlen_attn_unit& it, int head, char* smem, int wave, const f32x16 (&acc)[2][D / 32]) {
+  if (__builtin_expect(lower_half_only(it, false), 0)) {   // (one step: not cut)
+    if (wave == 0) {
+      uint2 w[D / 8];
+      float mine[D / 32][16];
+      static_for<D / 32>([&](auto db) __attribute__((always_inline)) { acc_values<db>(acc[0][db], mine[db]); });
+      pack<D>(w, mine, a.scale);
+      store_bf16<D>(smem, wave, fresh_lane(), it, w, a.dq, a.Hq, head);
+    }
+    return;
+  }
   if (!has_rows(it, wave)) {
     skip_take();
     return;
@@ -840,6 +872,27 @@ template <int D>
 __device__ __forceinline__ void store_dkv(const BwdArgs<D>& a, const varlen_attn_unit& it, int head, int kvh, char* smem, int wave,
                                           const f32x16 (&dkacc)[2][D / 32], const f32x16 (&dvacc)[2][D / 32]) {
   constexpr int DB = D / 32;
+  if (__builtin_expect(lower_half_only(it, true), 0)) {
+    if (wave == 0) {
+      const int lane = fresh_lane();
+      uint2 w[D / 8];
+      float mine[DB][16];
+      static_for<DB>([&](auto db) __attribute__((always_inline)) { acc_values<db>(dkacc[0][db], mine[db]); });
+      if (it.slot >= 0) {
+        float* const partial = a.col_partials + ((size_t)it.slot * a.Hq + head) * 2 * frag_floats<D>();
+        store_partial<D>(partial, mine, lane);
+        static_for<DB>([&](auto db) __attribute__((always_inline)) { acc_values<2 * DB + db>(dvacc[0][db], mine[db]); });
+        store_partial<D>(partial + frag_floats<D>(), mine, lane);
+      } else {
+        pack<D>(w, mine, a.scale);
+        store_bf16<D>(smem, wave, lane, it, w, a.dk, a.Hkv, kvh);
+        static_for<DB>([&](auto db) __attribute__((always_inline)) { acc_values<2 * DB + db>(dvacc[0][db], mine[db]); });
+        pack<D>(w, mine, 1.f);
+        store_bf16<D>(smem, wave, lane, it, w, a.dv, a.Hkv, kvh);
+      }
+    }
+    return;
+  }
   if (!has_rows(it, wave)) {
     skip_take();
     skip_take();
@@ -916,8 +969,9 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_pool_kernel(BwdArgs<D>) {
       const varlen_attn_unit done = col.it;
       const int done_head = col.head, done_kvh = col.kvh;
       t = g.members + tickets.take();
-      follows = has_rows(done, wave);
-      give<D, D / 32>(smem, wave, follows, dkacc[1]);
+      const bool meet = !lower_half_only(done, true);
+      follows = has_rows(done, wave) && (meet || wave == 0);
+      give<D, D / 32>(smem, wave, follows && meet, dkacc[1]);
       g.decode(t, unit, head);
       const BwdArgs<D> b = fresh();
       if (t < g.n_col) col.open(b, load_unit(b.col_units, unit), head, group(head), hpu, smem, wave, tickets);
@@ -937,8 +991,9 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_pool_kernel(BwdArgs<D>) {
     const varlen_attn_unit done = row.it;
     const int done_head = row.head;
     t = g.members + tickets.take();
-    follows = has_rows(done, wave);
-    give<D, D / 32>(smem, wave, follows, acc[1]);
+    const bool meet = !lower_half_only(done, false);
+    follows = has_rows(done, wave) && (meet || wave == 0);
+    give<D, D / 32>(smem, wave, follows && meet, acc[1]);
     const BwdArgs<D> b = fresh();
     if (t < g.total) {
       g.decode(t, unit, head);
