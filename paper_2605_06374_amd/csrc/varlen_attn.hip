@@ -331,13 +331,15 @@ inline bool short_path(const varlen_attn_params* p, bool backward) {
 // the heads alone decide.  With at most two q heads a kv head, 160 uncut packs: 0.98 .. 2.04, 1.52 in the mean, up to 24000 rows, 0.93 .. 1.86,
 // 1.28 in the mean, up to 80000, and 0.87 .. 1.25, 0.98 in the mean, above.
 // Heads of 64: the two kernels run two waves a SIMD, which hide each other's vector work (as long as the matrix instructions there) once there
-// are units enough for both; below that the pool's one launch, whole dQ chains and single tail win.  Two kernels / pool, on buffers that no
-// cache holds and on resident ones (geometric mean of the two), 860 packs of 10000 to 190000 rows:
-//   one q head a kv head, inside the rule 0.98 .. 1.29, 1.09 in the mean; on to 62000 rows with 700 tokens a document and more 0.96 .. 1.11,
-//   1.02, with fewer 0.83 .. 1.06, 0.98; above 0.73 .. 1.08, 0.89; below 128 tokens 0.76 .. 1.22, 0.92;
-//   two q heads a kv head, inside 0.95 .. 1.23, 1.09; more rows 0.76 .. 1.13, 0.94;
-//   more, inside 0.95 .. 1.22, 1.06; shorter documents on to 110000 rows 0.89 .. 1.24, 1.10 (slowest with 8 q heads on one kv head);
-//   more rows 0.90 .. 1.24, 1.02.
+// are units enough for both; below that the pool's one launch, whole dQ chains and single tail win.  Units cost the pool more, and their
+// number goes with (document, q head) pairs, since each has a tile that it does not fill; documents of one length just above a
+// multiple of 128 have the most for their rows, and chains that do not differ.  Two kernels / pool, on buffers that no cache holds and
+// on resident ones (geometric mean of the two), 860 packs of 10000 to 112000 rows, half of them of equal or nearly equal documents, of 90 to
+// 2500 tokens on average:
+//   one q head a kv head, inside the rule 0.99 .. 1.42, 1.15 in the mean;  up to 50000 rows in more than 110 pairs 0.73 .. 1.21, 0.94 (216
+//   documents of 130 tokens: 20.7 / 27.3 us);  more rows (other packs, most of them ragged) 0.73 .. 1.11, 0.93;
+//   two q heads a kv head, inside 0.93 .. 1.29, 1.14;  more than 450 pairs 0.73 .. 1.18, 1.00;  more rows (other packs) 0.76 .. 1.13, 0.94;
+//   more, inside 0.95 .. 1.26, 1.08;  more rows with 8 q heads on one kv head 0.84 .. 1.12, 1.00.
 inline bool pooled_backward(const varlen_attn_params* p) {
   const bool many_to_one = p->num_q_heads > 2 * p->num_kv_heads;
   if (p->flags & VARLEN_ATTN_FLAG_NO_SPLIT) return p->head_dim == 128 && !many_to_one;
@@ -345,7 +347,8 @@ inline bool pooled_backward(const varlen_attn_params* p) {
   if (p->head_dim == 64) {
     if (p->flags & VARLEN_ATTN_FLAG_FUSED_BWD) return false;   // its chunks and heads a unit are those of the two kernels
     const bool grouped = p->num_q_heads > p->num_kv_heads;
-    const long long max_rows = many_to_one ? (mean >= 250 ? 110000 : 75000) : grouped ? 90000 : mean >= 250 ? 50000 : 38000;
+    const long long max_rows = many_to_one ? (mean < 250 ? 75000 : p->num_q_heads > 4 * p->num_kv_heads ? 80000 : 110000) : grouped ? 90000 : 50000;
+    if (!many_to_one && (long long)p->num_docs * p->num_q_heads > (grouped ? 450 : 110)) return false;
     return !short_sizes(p, true) && rows <= max_rows && mean >= (grouped ? 90 : 128);
   }
   return !short_sizes(p, true) && (rows <= 24000 || mean >= (many_to_one && rows > 160000 ? 400 : 128));
