@@ -526,7 +526,8 @@ bwd_dkv_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k,
         acc[b] = mfma(lds_read_tr8(tile + lo + cc * 16 * kStep * 2, tile + hi + cc * 16 * kStep * 2), kb, acc[b]);
       }
     }
-    // (the 32 offsets are formed here every time: kept across the stages they are spilled, one load from scratch memory in front of each atomic)
+    // (the 32 offsets are formed here every time: kept across the stages they are spilled, one load from scratch memory in
+    // front of each atomic)
     size_t stride = (size_t)Hq * D;
     asm volatile("" : "+s"(stride));
     const int row0 = q0 + 32 * qb0 + 4 * h;

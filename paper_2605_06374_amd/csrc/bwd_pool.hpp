@@ -11,40 +11,43 @@
 namespace {
 
 // ----------------------------------------------------------------------------------------
-// Backward (the rule: pooled_backward() in varlen_attn.hip; figures without a head size are for 128).  One workgroup per compute unit stays and draws
-// units, column units (dK, dV) first, then units of dQ, longest first within each: the short dQ units fill what
-// the column units leave idle, where a kernel each has a tail, a burst of first loads and a launch of its own.  dQ has
-// units of its own (plan.hpp): in the pool a chain needs no cut until it would outlast the rest, which leaves a
-// quarter of the partial results at 8192 tokens.  Nothing depends on the order in which units are drawn, so that the
-// results are reproducible.  The price is D: both kinds need it, so it comes from a pass in front (bwd_prep_kernel).
+// Backward (the rule: pooled_backward() in varlen_attn.hip; figures without a head size are for 128).  One workgroup per
+// compute unit stays and draws units, column units (dK, dV) first, then units of dQ, longest first within each: the short dQ
+// units fill what the column units leave idle, where a kernel each has a tail, a burst of first loads and a launch of its own.
+// dQ has units of its own (plan.hpp): in the pool a chain needs no cut until it would outlast the rest, which leaves a quarter
+// of the partial results at 8192 tokens.  Nothing depends on the order in which units are drawn, so that the results are
+// reproducible.  The price is D: both kinds need it, so it comes from a pass in front (bwd_prep_kernel).
 //
-// What bounds it: at 512 registers one wave per SIMD issues everything, and on large microbatches the clock, which the
-// power limit takes down to 1.7 - 2.0 GHz on real operands (2.2 on zeros).  A wave owns 64 of a unit's 128 rows against half of
-// the 64 streamed rows of every stage, so that a fragment from LDS feeds two matrix instructions; with 32 rows a wave against all of the stage
-// the LDS was busy for 0.9 of the matrix pipe's time.  A stage of 64 rows, one wave's 32 rows before / now, 8192 tokens in 9 documents:
-// columns 1.61 / 1.43 us, dQ 1.23 / 1.12; 32768 tokens in 11 documents 1.80 / 1.65, 1.33 / 1.25.  The matrix instructions alone (no
-// vector work, LDS reads or loads) take 1.18, 0.89, 1.36 and 0.99.  The price is paid between two sweeps: the halves of a stage meet in LDS, which the
-// next unit's rows are landing in as well (LDS writes run at 77 bytes a clock, reads at 170): a column unit's results take 3.3 us
-// there instead of 1.8, which short documents pay for: backward of 56 packs of documents of 60 to 180 tokens 0.94 to 1.19, 1.00 in the mean,
-// times as fast as with 32 rows a wave (up to 32 tokens are spared it: lower_half_only(); 22 packs 1.00 to 1.30).  Whole steps: 8192 tokens
-// 108.9 -> 106.1 us, 7001 80.8 -> 77.5, 16384 with 8 q heads on one kv head 626 -> 601, 32768 in 35 documents 426 -> 409, in 11
-// 1683 -> 1604, 131072 in one 32.3 -> 30.6 ms.
+// What bounds it: at 512 registers one wave per SIMD issues everything, and on large microbatches the clock, which the power
+// limit takes down to 1.7 - 2.0 GHz on real operands (2.2 on zeros).  A wave owns 64 of a unit's 128 rows against half of the
+// 64 streamed rows of every stage, so that a fragment from LDS feeds two matrix instructions; with 32 rows a wave against all
+// of the stage the LDS was busy for 0.9 of the matrix pipe's time.  A stage of 64 rows, one wave's 32 rows before / now, 8192
+// tokens in 9 documents: columns 1.61 / 1.43 us, dQ 1.23 / 1.12; 32768 tokens in 11 documents 1.80 / 1.65, 1.33 / 1.25.  The
+// matrix instructions alone (no vector work, LDS reads or loads) take 1.18, 0.89, 1.36 and 0.99.  The price is paid between two
+// sweeps: the halves of a stage meet in LDS, which the next unit's rows are landing in as well (LDS writes run at 77 bytes a
+// clock, reads at 170): a column unit's results take 3.3 us there instead of 1.8, which short documents pay for: backward of 56
+// packs of documents of 60 to 180 tokens 0.94 to 1.19, 1.00 in the mean, times as fast as with 32 rows a wave (up to 32 tokens
+// are spared it: lower_half_only(); 22 packs 1.00 to 1.30).  Whole steps: 8192 tokens 108.9 -> 106.1 us, 7001 80.8 -> 77.5,
+// 16384 with 8 q heads on one kv head 626 -> 601, 32768 in 35 documents 426 -> 409, in 11 1683 -> 1604, 131072 in one 32.3 ->
+// 30.6 ms.
 //
 // Both sweeps are pipelined by hand; vector work and LDS reads ride on matrix instructions, the next stage's loads on those of S:
-//   columns  S(0, 1) | dP(0, 1) with P | dV(0, 1) with P, dS | dK(0, 1) with dS | wait, barrier | the last of dK with the next stage's first reads
-//   dQ       S(0) | S(1) with P(0) | dP(0) with P(0), P(1) | dP(1) with P(1), dS(0) | dQ(0) with dS(1) | wait, barrier | dQ(1) with the next reads
-// (0, 1: the wave's two blocks of 32 stationary rows).  The operands of what follows a barrier are in registers by then, so that no wave meets an
-// empty matrix pipe behind it.  The sums of a column unit take all 256 accumulation registers and its stationary fragments half of
-// the vector registers; dQ's sums and stationary fragments share the accumulation registers.
-// Measured and left out: row units first, which publish D themselves, with a wait in front of the column units (loads
-// past the L2 and 250 increments of one counter: 44 instead of 23 us at 4096 tokens); the next unit's stationary
-// tiles through LDS while the last stages run (its bookkeeping costs each of those stages as much as the
-// loads would); stages unrolled in pairs (a third more code, no faster); output rows stored from registers, 32 bytes of a row at a time (a step at
-// 32768 tokens in 35 documents 409 -> 420 us).
+//   columns  S(0, 1) | dP(0, 1) with P | dV(0, 1) with P, dS | dK(0, 1) with dS | wait, barrier |
+//            the last of dK with the next stage's first reads
+//   dQ       S(0) | S(1) with P(0) | dP(0) with P(0), P(1) | dP(1) with P(1), dS(0) | dQ(0) with dS(1) |
+//            wait, barrier | dQ(1) with the next reads
+// (0, 1: the wave's two blocks of 32 stationary rows).  The operands of what follows a barrier are in registers by then, so
+// that no wave meets an empty matrix pipe behind it.  The sums of a column unit take all 256 accumulation registers and its
+// stationary fragments half of the vector registers; dQ's sums and stationary fragments share the accumulation registers.
+// Measured and left out: row units first, which publish D themselves, with a wait in front of the column units (loads past the
+// L2 and 250 increments of one counter: 44 instead of 23 us at 4096 tokens); the next unit's stationary tiles through LDS while
+// the last stages run (its bookkeeping costs each of those stages as much as the loads would); stages unrolled in pairs (a
+// third more code, no faster); output rows stored from registers, 32 bytes of a row at a time (a step at 32768 tokens in 35
+// documents 409 -> 420 us).
 // ----------------------------------------------------------------------------------------
 
-// A wave-uniform condition as a vector value: the branch is then by the execution mask, the two forms of a stage lie one behind the other and
-// the accumulators keep their registers (a scalar branch copies them).
+// A wave-uniform condition as a vector value: the branch is then by the execution mask, the two forms of a stage lie one behind
+// the other and the accumulators keep their registers (a scalar branch copies them).
 __device__ __forceinline__ bool by_exec_mask(bool x) {
   int v = x;
   asm volatile("" : "+v"(v));
@@ -131,24 +134,25 @@ struct BwdArgs {
   int* tickets;
 };
 
-// LDS of a workgroup, all there is: two stages of two streamed tiles (K and V, or Q and dO), next to each other; the 128 rows of the two
-// stationary tiles on their way to registers; the statistics of the streamed queries (-LSE / scale [64], -D [64] per stage, two copies, one
-// per pair of waves).  Between two sweeps results meet in the second stage's half and behind the stationary tiles, 16 KB a wave, while the next
-// unit's first stage and stationary rows are landing.
+// LDS of a workgroup, all there is: two stages of two streamed tiles (K and V, or Q and dO), next to each other; the 128 rows
+// of the two stationary tiles on their way to registers; the statistics of the streamed queries (-LSE / scale [64], -D [64] per
+// stage, two copies, one per pair of waves).  Between two sweeps results meet in the second stage's half and behind the
+// stationary tiles, 16 KB a wave, while the next unit's first stage and stationary rows are landing.
 template <int D>
 struct BwdLds {
   static constexpr int kHalf = kStep * D * 2, kStage = 2 * kHalf, kStat = 512, kFixed = kTile * D * 2, kMeet = 32 * D * 4;
   static constexpr int kFixeds = 2 * kStage, kStats = kFixeds + 2 * kFixed, kTicket = kStats + 4 * kStat;
   static __device__ __forceinline__ int meet(int wave) { return (wave & 2 ? kStats : kStage) + (wave & 1) * kMeet; }
-  // 64 columns of 32 output rows, in the second stage's half: 16-byte chunk x of row r at x * kOutChunk + 16 r, spread over the banks both ways
+  // 64 columns of 32 output rows, in the second stage's half: 16-byte chunk x of row r at x * kOutChunk + 16 r, spread over the
+  // banks both ways
   static constexpr int kOutChunk = 32 * 16 + 32, kOut = 8 * kOutChunk, kOuts = 4 * kOut <= kStage ? kStage : kStats + 2 * kMeet;
   static constexpr int kBytes = 4 * kOut <= kStage ? kStats + 2 * kMeet : kOuts + 4 * kOut;
 };
 static_assert(BwdLds<128>::kBytes == 160 * 1024, "of a compute unit");
 
-// Accumulator number I of a kernel that keeps its sums in accumulation registers 16 I .. 16 I + 15, by inline assembly: its values in vector
-// registers, or in LDS (four pieces of 1 KB a wave, from `OFFSET` on).  An element that the compiler takes out itself draws
-// the whole accumulator into vector registers, and all of them right behind the sweep, where they are spilled.
+// Accumulator number I of a kernel that keeps its sums in accumulation registers 16 I .. 16 I + 15, by inline assembly: its
+// values in vector registers, or in LDS (four pieces of 1 KB a wave, from `OFFSET` on).  An element that the compiler takes out
+// itself draws the whole accumulator into vector registers, and all of them right behind the sweep, where they are spilled.
 #define VARLEN_ATTN_ACCUMULATORS(X)                                                                                       \
   X(0, "0:15", "0:3", "4:7", "8:11", "12:15", 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15)                        \
   X(1, "16:31", "16:19", "20:23", "24:27", "28:31", 16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31) \
@@ -195,8 +199,9 @@ __device__ __forceinline__ void acc_to_lds(const f32x16& acc, unsigned lds_addr)
 #undef VARLEN_ATTN_WRITE
 }
 
-// The two halves of a stage meet: accumulators GIVE .. of this wave go to the wave of the other half (give(), a barrier behind it in take()), whose
-// accumulators come back in fragment order, to be added to TAKE ..  All waves; those without a row of the tile meet the barriers only.
+// The two halves of a stage meet: accumulators GIVE .. of this wave go to the wave of the other half (give(), a barrier behind
+// it in take()), whose accumulators come back in fragment order, to be added to TAKE ..  All waves; those without a row of the
+// tile meet the barriers only.
 template <int D, int GIVE>
 __device__ __forceinline__ void give(char* smem, int wave, bool any_rows, const f32x16 (&acc)[D / 32]) {
   if (!any_rows) return;
@@ -227,9 +232,10 @@ __device__ __forceinline__ void add(f32x4 (&x)[D / 8], const float (&mine)[D / 3
 
 // Has this wave a row of the unit's tile?
 __device__ __forceinline__ bool has_rows(const varlen_attn_unit& it, int wave) { return it.row0 + 64 * (wave & 1) < it.doc_end; }
-// The streamed rows of a unit end in the lower half of its only stage: what wave 0 has is the result, and no halves meet.  Two branches a unit of
-// other tiles.  32 rows a wave / meeting always / so, backward, resident buffers: 1250 documents of 32 tokens 56.8 / 60.2 / 51.9 us, 489 of
-// 8 to 100, 8 heads, 162.9 / 176.1 / 158.8; documents of 60 to 200 tokens 0.987 .. 1.005 of the speed without it, 32768 tokens in 35 1.005.
+// The streamed rows of a unit end in the lower half of its only stage: what wave 0 has is the result, and no halves meet.  Two
+// branches a unit of other tiles.  32 rows a wave / meeting always / so, backward, resident buffers: 1250 documents of 32
+// tokens 56.8 / 60.2 / 51.9 us, 489 of 8 to 100, 8 heads, 162.9 / 176.1 / 158.8; documents of 60 to 200 tokens 0.987 .. 1.005
+// of the speed without it, 32768 tokens in 35 1.005.
 __device__ __forceinline__ bool lower_half_only(const varlen_attn_unit& it, bool columns) {
   return it.doc_end - (columns ? it.row0 : it.doc_start) <= kStep / 2;
 }
@@ -301,8 +307,8 @@ struct PanelStream {
   __device__ __forceinline__ void aim(int row0, int row_last) { last = (unsigned)min(row_last - row0, kStep - 1) * stride; }
   __device__ __forceinline__ void advance() { a_next += stage_stride; b_next += stage_stride; }
   __device__ __forceinline__ unsigned offset() const { return min(own, last + col); }
-  // Piece P to this wave's first kilobyte `lds` of the first tile, the second tile behind the first: the destination, and, an instruction later at
-  // the earliest, the load.  The load's constant offset counts on both sides, in memory and in LDS.
+  // Piece P to this wave's first kilobyte `lds` of the first tile, the second tile behind the first: the destination, and, an
+  // instruction later at the earliest, the load.  The load's constant offset counts on both sides, in memory and in LDS.
   template <int P>
   static __device__ __forceinline__ void aim_piece(unsigned lds) {
     constexpr int i = P % kPanels;
@@ -404,8 +410,8 @@ struct DqUnit {
                            it.doc_end - 1, smem, wave);
   }
 
-  // S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dS^T.  `follows`: this wave issued stores of another unit, D / 16 at least, behind this unit's loads (none
-  // where it had no rows of that unit).
+  // S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dS^T.  `follows`: this wave issued stores of another unit, D / 16 at least, behind
+  // this unit's loads (none where it had no rows of that unit).
   template <typename Tickets>
   __device__ __forceinline__ void sweep(const BwdArgs<D>& a, bool follows, char* smem, int wave, f32x16 (&acc)[2][DB], Tickets& tickets) {
     float scale = a.scale;
@@ -427,7 +433,8 @@ struct DqUnit {
 #pragma unroll
         for (int i = 0; i < DB; ++i) acc_zero(acc[b][i], zeros);
     }
-    // (as instructions that the compiler sees: for the statistics' loads it would wait, with all that is in flight by then, inside the loop)
+    // (as instructions that the compiler sees: for the statistics' loads it would wait, with all that is in flight by then,
+    // inside the loop)
     if (follows) __builtin_amdgcn_s_waitcnt(0x0F70 + D / 16);
     else wait_all_vm_visible();
     __syncthreads();
@@ -483,7 +490,8 @@ struct DqUnit {
         }
       };
       auto fence = []() __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0); };
-      // vector work beside matrix instruction u of the 32 of S(1), dP(0), dP(1) and dQ(0) (the results of a phase are there two instructions on)
+      // vector work beside matrix instruction u of the 32 of S(1), dP(0), dP(1) and dQ(0) (the results of a phase are there two
+      // instructions on)
       auto beside = [&](auto u_c) __attribute__((always_inline)) {
         constexpr int u = decltype(u_c)::value;
         auto share = [](int n, int from, int to, int at) { return at <= from ? 0 : at >= to ? n : n * (at - from) / (to - from); };
@@ -1004,8 +1012,8 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_pool_kernel(BwdArgs<D>) {
   }
 }
 
-// Sums of the partial results of the pool, dealt as in fwd_combine_kernel: [dK | dV] of cut or grouped column tiles by the workgroups from the
-// front, dQ of cut row tiles by the workgroups from the back.
+// Sums of the partial results of the pool, dealt as in fwd_combine_kernel: [dK | dV] of cut or grouped column tiles by the
+// workgroups from the front, dQ of cut row tiles by the workgroups from the back.
 template <int D>
 __global__ void __launch_bounds__(kThreads)
 bwd_pool_combine_kernel(const varlen_attn_plan_header* __restrict__ hdr, const varlen_attn_combine_item* __restrict__ col_items,

@@ -11,18 +11,19 @@
 namespace {
 
 // ----------------------------------------------------------------------------------------
-// The forward of fwd.hpp (same units, order, reference, partial results) with two waves a workgroup, one a SIMD: wave w owns rows row0 + 64 w .. + 63
-// as two blocks of 32, so that a fragment of K or V from LDS feeds two matrix instructions, and the substeps of 32 keys are pipelined by hand:
-//   S of the next substep (16 matrix instructions) beside the upper 8 registers' exponentials of this one | check | O += P V of this one (16) beside the
-//   lower 8 registers' exponentials of the next one; in the middle of it the wait and the barrier.
-// One exponential (multiply-add, exp, sum, half a rounding: 30 of the 32 clocks that a matrix instruction takes) to a matrix instruction, held there
-// by inline assembly: two beside one and none beside the next, which is what
-// the compiler makes of the same source, took 1.07 times as long (424 -> 398 us on the first of the packs below).
-// K and V are double-buffered in steps of 64 keys (32 KB each); what a barrier frees is requested behind it and waited for two barriers on.
-// What bounds it: vector work and matrix work that are equally long, and on large microbatches the clock.  Forward alone, two-wave SIMDs / here:
-// 32768 tokens in 11 documents (4 heads) 435 -> 398 us, 32768 in 35 117 -> 110, 16384 (8 q heads on one) 169 -> 160; whole
-// steps 1557 -> 1524, 402 -> 392, 595 -> 582, 131072 in one document 30.7 -> 29.9 ms.  First loads and last stores have no other
-// wave to hide behind, which short chains pay for: wide_forward() in varlen_attn.hip.
+// The forward of fwd.hpp (same units, order, reference, partial results) with two waves a workgroup, one a SIMD: wave w owns
+// rows row0 + 64 w .. + 63 as two blocks of 32, so that a fragment of K or V from LDS feeds two matrix instructions, and the
+// substeps of 32 keys are pipelined by hand:
+//   S of the next substep (16 matrix instructions) beside the upper 8 registers' exponentials of this one | check |
+//   O += P V of this one (16) beside the lower 8 registers' exponentials of the next one; in the middle of it the wait and the barrier.
+// One exponential (multiply-add, exp, sum, half a rounding: 30 of the 32 clocks that a matrix instruction takes) to a matrix
+// instruction, held there by inline assembly: two beside one and none beside the next, which is what the compiler makes of the
+// same source, took 1.07 times as long (424 -> 398 us on the first of the packs below).  K and V are double-buffered in steps of
+// 64 keys (32 KB each); what a barrier frees is requested behind it and waited for two barriers on.  What bounds it: vector work
+// and matrix work that are equally long, and on large microbatches the clock.  Forward alone, two-wave SIMDs / here: 32768
+// tokens in 11 documents (4 heads) 435 -> 398 us, 32768 in 35 117 -> 110, 16384 (8 q heads on one) 169 -> 160; whole steps 1557
+// -> 1524, 402 -> 392, 595 -> 582, 131072 in one document 30.7 -> 29.9 ms.  First loads and last stores have no other wave to
+// hide behind, which short chains pay for: wide_forward() in varlen_attn.hip.
 // ----------------------------------------------------------------------------------------
 template <bool SELF>
 __global__ void __launch_bounds__(128, 1)
@@ -180,11 +181,12 @@ fwd_wide_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
       fence();
     }
   };
-  // Rare: block b against a new reference.  Its scores are gone by now and the probabilities at hand are scaled, which gives a row's largest the same
-  // 2^-12 exactly.  To form the scores again from memory (the K tile may be landing on already) stops both waves for the time of a load, and is
-  // done for sums beyond 2^100, whose scaling would leave the range, and NaN.  Forward at 32768 tokens in 35 documents, 16384 (8 q heads on
-  // one) and 32768 in 11, scores with a standard deviation of 9, from memory each time 153.6, 191.6 and 472 us, scaled 126.0, 166.3 and 437;
-  // with a standard deviation of 1 114.1, 148.9 and 402, scaled 113.3, 148.8 and 402.
+  // Rare: block b against a new reference.  Its scores are gone by now and the probabilities at hand are scaled, which gives a
+  // row's largest the same 2^-12 exactly.  To form the scores again from memory (the K tile may be landing on already) stops
+  // both waves for the time of a load, and is done for sums beyond 2^100, whose scaling would leave the range, and NaN.
+  // Forward at 32768 tokens in 35 documents, 16384 (8 q heads on one) and 32768 in 11, scores with a standard deviation of 9,
+  // from memory each time 153.6, 191.6 and 472 us, scaled 126.0, 166.3 and 437; with a standard deviation of 1 114.1, 148.9 and
+  // 402, scaled 113.3, 148.8 and 402.
   auto renew = [&](f32x16& s, int b, int kv0, bool triangle) __attribute__((always_inline)) {
     if (__builtin_expect(__any(!(psum[b] <= 0x1p100f)), 0)) {
       const __bf16* row = k + ((size_t)min(kv0 + c, it.doc_end - 1) * Hkv + kvh) * D + 8 * h;
@@ -215,8 +217,8 @@ fwd_wide_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
     rescale(b, m_new);
   };
   int t = 0;
-  // Substep x = 32 HALF .. of step t: S of the next substep beside the upper half of x's exponentials, then O += P V of x beside the lower half
-  // of the next one's.
+  // Substep x = 32 HALF .. of step t: S of the next substep beside the upper half of x's exponentials, then O += P V of x
+  // beside the lower half of the next one's.
   auto iter = [&](auto half_c, auto diag_c, f32x16 (&cur)[2], f32x16 (&nxt)[2], bool next_diag) __attribute__((always_inline)) {
     constexpr int HALF = decltype(half_c)::value;
     constexpr bool DIAG = decltype(diag_c)::value, NEXT = !(DIAG && HALF);
@@ -243,7 +245,8 @@ fwd_wide_kernel(const __bf16* __restrict__ q, const __bf16* __restrict__ k, cons
         if constexpr (kk == 0) mfma_vgpr_agpr_first(nxt[0], kf[kk], qf[0][kk]);
         else mfma_vgpr_agpr(nxt[0], kf[kk], qf[0][kk]);
       } else {
-        asm volatile("s_nop 0");   // (a load to LDS takes m0 one wait state behind its write at the earliest; elsewhere the matrix instruction is that)
+        // (a load to LDS takes m0 one wait state behind its write at the earliest; elsewhere the matrix instruction is that)
+        asm volatile("s_nop 0");
       }
       if constexpr (NEXT && kk < KK / 2) kf[kk + KK / 2] = fo.row_frag(kt, kk + KK / 2);
       upper(std::integral_constant<int, 2 * kk>{});

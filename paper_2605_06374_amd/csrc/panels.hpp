@@ -7,8 +7,8 @@
 
 namespace {
 
-// Scores and their gradients: accumulators in vector registers; nothing touches the results until two further matrix instructions have been issued (tiles.hpp).
-// Stationary operand in accumulation registers:
+// Scores and their gradients: accumulators in vector registers; nothing touches the results until two further matrix
+// instructions have been issued (tiles.hpp). Stationary operand in accumulation registers:
 __device__ __forceinline__ void mfma_vgpr_agpr(f32x16& c, const bf16x8& a, const bf16x8& b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "a"(b));
 }

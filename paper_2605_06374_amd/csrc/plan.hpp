@@ -201,12 +201,11 @@ __device__ __forceinline__ unsigned long long wave_total_wide(unsigned long long
 }
 
 // ----------------------------------------------------------------------------------------
-// The u-th row unit of a microbatch of at most 64 documents and 256 tiles, in the order
-// (tile, chunk) or, `longest_first`, (chunk length of the tile, tile, chunk), worked out by one wave from cu_seqlens alone with the plan's own rules (chunk
-// length, nearly equal chunks, slots of cut tiles numbered in tile order): a forward workgroup
-// of a small microbatch finds its unit this way instead of waiting for the plan.  All 64
-// lanes must call it; every lane gets the same answer.  False: cu_seqlens is malformed (the
-// plan reports it) or u is past the last unit.
+// The u-th row unit of a microbatch of at most 64 documents and 256 tiles, in the order (tile, chunk) or, `longest_first`,
+// (chunk length of the tile, tile, chunk), worked out by one wave from cu_seqlens alone with the plan's own rules (chunk
+// length, nearly equal chunks, slots of cut tiles numbered in tile order): a forward workgroup of a small microbatch finds its
+// unit this way instead of waiting for the plan.  All 64 lanes must call it; every lane gets the same answer.  False:
+// cu_seqlens is malformed (the plan reports it) or u is past the last unit.
 // ----------------------------------------------------------------------------------------
 __device__ __forceinline__ bool derive_row_unit(const int32_t* __restrict__ cu, int B, int N, int Hq,
                                                 int no_split, const ChunkRule& rule, int forced, int slots_cap, int u,

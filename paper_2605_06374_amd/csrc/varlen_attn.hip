@@ -234,9 +234,10 @@ void chunk_rules(const varlen_attn_params* p, PlanArgs* a) {
     a->rule[0] = ChunkRule{1.3125f * kSlot, 3, kSlot, wide_forward(p) ? 11.f : 19.f, resident, kMinChunkSteps + 1};
   }
   if (pooled) {
-    // Heads of 64 go by the lines of 128 where queries are grouped (57 packs with more than two q heads a kv head, 33 with two; 0.6, 0.8, 1.25 and 1.6
-    // times the length: 0.96, 0.98, 0.94, 0.86 and 0.95, 0.98, 0.99, 0.93 times as fast; half or twice the heads a unit: 0.95 and 0.55, 0.90
-    // and 0.99; the best of each pack 1.014 and 1.010), by a longer one where they are not (50 packs, the same lengths: 0.96, 0.99, 0.96, 0.91; best 1.005).
+    // Heads of 64 go by the lines of 128 where queries are grouped (57 packs with more than two q heads a kv head, 33 with two;
+    // 0.6, 0.8, 1.25 and 1.6 times the length: 0.96, 0.98, 0.94, 0.86 and 0.95, 0.98, 0.99, 0.93 times as fast; half or twice
+    // the heads a unit: 0.95 and 0.55, 0.90 and 0.99; the best of each pack 1.014 and 1.010), by a longer one where they are
+    // not (50 packs, the same lengths: 0.96, 0.99, 0.96, 0.91; best 1.005).
     a->rule[1] = grouped ? ChunkRule{2.5f * kSlot, 2, 1.6f * kSlot, 26, 0, 0}
                  : p->head_dim == 64 ? ChunkRule{3.75f * kSlot, 3, 2 * kSlot, 33, 0, 0} : ChunkRule{3 * kSlot, 3, 1.6f * kSlot, 27, 0, 0};
     a->sweep = SweepRule{0.75f, 128, 3 * kSlot, 200, 2.5f * kSlot, 32};
@@ -326,16 +327,17 @@ inline bool short_path(const varlen_attn_params* p, bool backward) {
 //   more than two q heads a kv head, documents of 128 to 400 tokens on average: 1.04 .. 1.72, 1.14 in the mean (45 packs), up to
 //   160000 rows; above, where the two kernels have column units enough that sweep whole groups, 0.85 .. 1.16 (13 packs).
 // (The host does not know the longest document.  Documents of equal length are the pool's worst case inside the rule: 0.95 with
-// 32 of 512 tokens, 4 heads; of up to 127 tokens 0.90 .. 1.38, 1.07 in the mean of 20 packs, where all chains are 1 or 2 steps.)
-// With VARLEN_ATTN_FLAG_NO_SPLIT a document's bits must not depend on what else is in the pack, hence neither may the route: there
-// the heads alone decide.  With at most two q heads a kv head, 160 uncut packs: 0.98 .. 2.04, 1.52 in the mean, up to 24000 rows, 0.93 .. 1.86,
-// 1.28 in the mean, up to 80000, and 0.87 .. 1.25, 0.98 in the mean, above.
-// Heads of 64: the two kernels run two waves a SIMD, which hide each other's vector work (as long as the matrix instructions there) once there
-// are units enough for both; below that the pool's one launch, whole dQ chains and single tail win.  Units cost the pool more, and their
-// number goes with (document, q head) pairs, since each has a tile that it does not fill; documents of one length just above a
-// multiple of 128 have the most for their rows, and chains that do not differ.  Two kernels / pool, on buffers that no cache holds and
-// on resident ones (geometric mean of the two), 860 packs of 10000 to 112000 rows, half of them of equal or nearly equal documents, of 90 to
-// 2500 tokens on average:
+// 32 of 512 tokens, 4 heads; of up to 127 tokens 0.90 .. 1.38, 1.07 in the mean of 20 packs, where all chains are 1 or 2
+// steps.)
+// With VARLEN_ATTN_FLAG_NO_SPLIT a document's bits must not depend on what else is in the pack, hence neither may the
+// route: there the heads alone decide.  With at most two q heads a kv head, 160 uncut packs: 0.98 .. 2.04, 1.52 in the mean, up
+// to 24000 rows, 0.93 .. 1.86, 1.28 in the mean, up to 80000, and 0.87 .. 1.25, 0.98 in the mean, above.
+// Heads of 64: the two kernels run two waves a SIMD, which hide each other's vector work (as long as the matrix instructions there) once there are
+// units enough for both; below that the pool's one launch, whole dQ chains and single tail win.  Units cost the pool more, and
+// their number goes with (document, q head) pairs, since each has a tile that it does not fill; documents of one length just
+// above a multiple of 128 have the most for their rows, and chains that do not differ.  Two kernels / pool, on buffers that no
+// cache holds and on resident ones (geometric mean of the two), 860 packs of 10000 to 112000 rows, half of them of equal or
+// nearly equal documents, of 90 to 2500 tokens on average:
 //   one q head a kv head, inside the rule 0.99 .. 1.42, 1.15 in the mean;  up to 50000 rows in more than 110 pairs 0.73 .. 1.21, 0.94 (216
 //   documents of 130 tokens: 20.7 / 27.3 us);  more rows (other packs, most of them ragged) 0.73 .. 1.11, 0.93;
 //   two q heads a kv head, inside 0.93 .. 1.29, 1.14;  more than 450 pairs 0.73 .. 1.18, 1.00;  more rows (other packs) 0.76 .. 1.13, 0.94;
