@@ -1013,12 +1013,13 @@ __global__ void __launch_bounds__(kThreads, 1) bwd_pool_kernel(BwdArgs<D>) {
 }
 
 // Sums of the partial results of the pool, dealt as in fwd_combine_kernel: [dK | dV] of cut or grouped column tiles by the
-// workgroups from the front, dQ of cut row tiles by the workgroups from the back.
+// workgroups from the front, dQ of cut tiles of the units it came from (dQ units or, where the plan has none, row units) by
+// the workgroups from the back.
 template <int D>
 __global__ void __launch_bounds__(kThreads)
 bwd_pool_combine_kernel(const varlen_attn_plan_header* __restrict__ hdr, const varlen_attn_combine_item* __restrict__ col_items,
                         int max_col, const float* __restrict__ col_partials, const varlen_attn_combine_item* __restrict__ dq_items,
-                        int max_row, const float* __restrict__ row_partials, __bf16* __restrict__ dq, __bf16* __restrict__ dk,
+                        const varlen_attn_combine_item* __restrict__ row_items, int max_row, const float* __restrict__ row_partials, __bf16* __restrict__ dq, __bf16* __restrict__ dk,
                         __bf16* __restrict__ dv, int Hq, int Hkv, float scale) {
   constexpr int DB = D / 32, kWavePieces = 4 * DB / 2;
   constexpr int kFlight = 4;
@@ -1026,7 +1027,10 @@ bwd_pool_combine_kernel(const varlen_attn_plan_header* __restrict__ hdr, const v
   __shared__ __attribute__((aligned(16))) char tiles[2][Tile::kBytes];
   int buf = 0;
   const int lane = threadIdx.x & 63, rq = threadIdx.x >> 6, h = lane >> 5, c = lane & 31;
-  const int n_col = min(hdr->n_col_combine, max_col), n_row = min(hdr->n_dq_combine, max_row), hpu = hdr->col_heads_per_unit;
+  const int n_col = min(hdr->n_col_combine, max_col), hpu = hdr->col_heads_per_unit;
+  const bool own_dq = hdr->n_dq_units > 0;
+  const int n_row = min(own_dq ? hdr->n_dq_combine : hdr->n_row_combine, max_row);
+  if (!own_dq) dq_items = row_items;
   const int G = Hq / Hkv;
   auto piece = [&](const varlen_attn_combine_item& it, int wave, int db, const float* p0, int n_parts, auto offset, float mul, __bf16* out, int out_heads, int out_head)
       __attribute__((always_inline)) {

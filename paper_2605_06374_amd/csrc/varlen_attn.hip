@@ -486,7 +486,7 @@ void launch_bwd(const varlen_attn_params* p, const void* q, const void* k, const
       const long long pieces = (long long)col_items * Hkv * (D / 8) + (long long)dq_items * Hq * (D / 16);
       ScopedKernelTimer timer(kBwdPoolCombine, stream);
       bwd_pool_combine_kernel<D><<<dim3((unsigned)std::min<long long>(pieces, 2 * kCombineGroups)), kThreads, 0, stream>>>(
-          R.hdr, R.col_comb, col_items, R.col_part, R.dq_comb, dq_items, R.row_part, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, Hq, Hkv, scale);
+          R.hdr, R.col_comb, col_items, R.col_part, R.dq_comb, R.row_comb, dq_items, R.row_part, (__bf16*)dq, (__bf16*)dk, (__bf16*)dv, Hq, Hkv, scale);
     }
     return;
   }
